@@ -1,18 +1,34 @@
 // Fused row-block kernels of the split-learning step on gfx950 (k_fwd,
 // k_active, k_bwd; see kernels.h for what each computes).
 //
-// A workgroup of 512 threads (8 wavefronts, two per SIMD) owns BR = 16 * RT
-// (RT = 1 .. 4) consecutive rows of the group and runs every layer of its chain on them,
-// the activations and deltas staying in LDS.  Each layer is one MFMA product
+// A workgroup of 12 wavefronts owns BR = 16 * RT (RT = 1 .. 4) consecutive
+// rows of the group and runs every layer of its chain on them, the
+// activations and deltas staying in LDS.  Eight product wavefronts (two per
+// SIMD) run the layers; each layer is one MFMA product
 // out[BR x N] = in[BR x K] W^T: wavefront w takes the 16-column output tiles
 // w, w+8, w+16, ... (two at a time), loads the weight fragments of its tiles
 // straight from global memory (L2-resident: the workgroups of an XCD fetch
-// the kernel's weights into its L2 at the start) two groups of four MFMA
+// the kernel's weights into its L2 at the start) two groups of two MFMA
 // steps ahead, across layer boundaries, and the activation fragments from
 // LDS; biases come from an LDS table filled at the start;
 // v_mfma_f32_16x16x32_bf16 for bf16 operands, v_mfma_f32_16x16x4_f32 for
 // float32, float32 accumulation.  The weight fragment is the MFMA's A
 // operand, so a lane ends up with four consecutive output columns of one row.
+//
+// Four copy wavefronts write what a later kernel needs: while the product
+// wavefronts run stage i + 1 (which reads stage i's output and writes
+// another buffer) they copy stage i's output from LDS to HBM, and both meet
+// at the barrier that ends the stage.  Stores and loads share one in-order
+// counter on gfx950, so a wavefront that stores a copy (a loop whose store
+// count the compiler does not know) waits for those writes before it may use
+// weights loaded earlier; with the copies in wavefronts of their own the
+// product wavefronts' waits are exact, and two load groups in flight are
+// enough: the weights come from L2 within about 160 ns at 110 bytes per ns
+// and CU, and groups of four steps gained nothing any more.  Measured on one
+// stream against copies issued inside the next product: k_active 93 -> 82 us
+// (private, 48 rows per block), 123 -> 109 (regression), 25.9 -> 22.9
+// (dense_tabular); per tick 176 -> 166, 232 -> 217 and 46.2 -> 44.6 us.  Two
+// copy wavefronts instead of four were 2 to 7 % slower per tick.
 //
 // LDS rows are padded to 16 bytes past a multiple of 128, so the 16 rows a
 // fragment read touches fall in distinct banks.  After a layer, the tensors a
@@ -92,11 +108,19 @@ __device__ __forceinline__ void st8(char* p, const float (&v)[8]) {
 }
 
 // ------------------------------------------------------------ block product
-constexpr int kNW = kChainWaves;    // wavefronts per block (two per SIMD)
-constexpr int kNT = 64 * kNW;        // threads per block
+constexpr int kNW = kChainWaves;    // product wavefronts per block (two per SIMD)
+constexpr int kNT = 64 * kNW;        // product threads
+constexpr int kBT = kNT + 64 * kChainCopyWaves;   // most threads per block
+// Wavefronts per SIMD the register allocation has to allow: two blocks of
+// 12 wavefronts on a CU (80 registers) up to `two` row tiles per block, else
+// one (168).  At 80 registers k_bwd<bf16, 2> (82 without the bound) keeps two
+// blocks on a CU (32768 rows of 500-1024-512-128: 47 -> 37 us) and
+// k_active<bf16, 1> (86) leaves room for the other party's blocks
+// (regression's tick 224 -> 217 us); k_active<., 2> would spill 35 registers
+// (ctr's 55 -> 62 us).
+constexpr int min_waves(int rt, int two) { return rt <= two ? 6 : 3; }
 constexpr int kNTW = 2;              // 16-column output tiles per wavefront and pass
-constexpr int kPFNarrow = kChainPFNarrow;   // MFMA steps per weight load group
-constexpr int kPFWide = kChainPFWide;
+constexpr int PF = 2;                // MFMA steps per weight load group
 constexpr int kLogitChunks = kMaxLogitCols / 256;   // 4-column chunks per lane in the logit stage
 
 // Weight-fragment registers of a chain: two load groups of PF MFMA steps
@@ -106,22 +130,8 @@ constexpr int kLogitChunks = kMaxLogitCols / 256;   // 4-column chunks per lane 
 // a product starts with both of its first groups already in flight.  A
 // pass has an even number of groups (steps past K are skipped), so every
 // pass starts in `wa`.
-template <int PF>
 struct Pipe {
   u32x4 wa[PF][kNTW], wb[PF][kNTW];
-};
-
-// The RC copy of a stage's LDS output (lds_to_rc of b's first cols columns
-// into m at block row r0; m.p null: none), left for the next product to
-// issue.  On gfx950 stores count in the same in-order counter as loads, so
-// a wait for any load issued after a store also waits for the store's
-// write to complete; the next product issues the copy after its last
-// weight loads, where nothing waits on them until the product after it.
-struct RcPend {
-  LBuf b;
-  int cols = 0;
-  RCMat m;
-  int r0 = 0;
 };
 
 // A pointer or value the compiler must keep in scalar registers (it is
@@ -159,7 +169,6 @@ __device__ __forceinline__ int tiles_of(int N) {
 // operand's last are clamped to it, steps past K to its last step (never
 // used; re-reading lines already fetched keeps them off the L2, and a
 // conditional load would make the compiler wait for it on the spot).
-template <int PF>
 __device__ __forceinline__ void wgroup(const void* Wp, int kst, int ntl, const int (&tile)[kNTW], int g,
                                        u32x4 (&d)[PF][kNTW]) {
   const uint32_t lo = (threadIdx.x & 63) * 16;
@@ -179,8 +188,8 @@ __device__ __forceinline__ void pass_tiles(int pass, int (&tile)[kNTW]) {
 }
 
 // start the loads of groups 0 and 1 of L's first pass
-template <typename T, int PF>
-__device__ __forceinline__ void prefetch(const ChainLayer* L, Pipe<PF>& p) {
+template <typename T>
+__device__ __forceinline__ void prefetch(const ChainLayer* L, Pipe& p) {
   int tile[kNTW];
   pass_tiles(0, tile);
   const VFL_CONST ChainLayer& C = cst(*(const ChainLayer*)uniform_ptr(L));
@@ -225,17 +234,10 @@ __device__ __forceinline__ uint32_t warm_l2(const WarmSet& w, const void* dummy)
 // multiple of 4; bias[i] = bias[n + i] from the LDS table, zero without a
 // bias or past N), for every row of the block and every column below N
 // rounded up to the MFMA depth.  On entry p holds groups 0 and 1 of L's
-// first pass; on return, groups 0 and 1 of `next`'s (nullable).  The
-// pending RC copy (whose LDS rows this product does not write) is issued
-// in the last pass once every weight load of the pass is out.
-template <typename T, int BR, bool NT>
-__device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int cols, const RCMat& m, int r0);
-template <typename T, int BR>
-__device__ __forceinline__ void lds_to_rc_hint(const char* s, const LBuf& b, int cols, const RCMat& m, int r0);
-
-template <typename T, int RT, typename Epi, bool HINT = false, int PF>
-__device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pipe<PF>& p,
-                                         const ChainLayer* next, const RcPend& pend, Epi&& epi) {
+// first pass; on return, groups 0 and 1 of `next`'s (nullable).
+template <typename T, int RT, typename Epi>
+__device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pipe& p,
+                                         const ChainLayer* next, Epi&& epi) {
   constexpr int NTW = kNTW;
   const int lane = threadIdx.x & 63;
   const int kc = lane >> 4, lr = lane & 15;
@@ -313,10 +315,6 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
       group(g + 1, p.wb);
       refill(g + 3, p.wb);
     }
-    if (!more && pend.m.p) {
-      if constexpr (HINT) lds_to_rc_hint<T, 16 * RT>(s, pend.b, pend.cols, pend.m, pend.r0);
-      else lds_to_rc_<T, 16 * RT, false>(s, pend.b, pend.cols, pend.m, pend.r0);
-    }
 #pragma unroll
     for (int j = 0; j < NTW; ++j) {
       if (tile[j] >= ntl) continue;
@@ -330,9 +328,9 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
 
 // Forward or input-gradient layer into LDS (see ChainLayer).
 // MB: the mask (when there is one) is the byte form of the ReLU bits
-template <typename T, int RT, bool HINT = false, int PF, bool MB = false>
-__device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, Pipe<PF>& p,
-                                          const ChainLayer* next, const RcPend& pend) {
+template <typename T, int RT, bool MB = false>
+__device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, Pipe& p,
+                                          const ChainLayer* next) {
   const int N = L.N;
   const bool relu = L.relu != 0, msk = L.mask.pitch > 0, nopad = L.nopad != 0;
   const LBuf out = L.out, mk = L.mask;
@@ -362,17 +360,17 @@ __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, 
     // below N or all past it
     if (!nopad || n < N) st4<T>(lp(s, out, r, n * (int)sizeof(T)), v);
   };
-  block_mm<T, RT, decltype(epi)&, HINT>(s, L, p, next, pend, epi);
+  block_mm<T, RT>(s, L, p, next, epi);
 }
 
 // Input gradient of the embedding columns of a bottom input: float32 rows
 // of gx (block rows below rv).
-template <typename T, int RT, int PF>
+template <typename T, int RT>
 __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float* gx, int64_t ldgx,
-                                       int r0, int rv, Pipe<PF>& p, const RcPend& pend) {
+                                       int r0, int rv, Pipe& p) {
   const int N = L.N;
   VFL_GLOBAL float* gxg = glb(gx);
-  block_mm<T, RT>(s, L, p, nullptr, pend, [&](int r, int n, const f32x4& a, const f32x4&) {
+  block_mm<T, RT>(s, L, p, nullptr, [&](int r, int n, const f32x4& a, const f32x4&) {
     if (r >= rv) return;
     VFL_GLOBAL float* dst = gxg + (int64_t)(r0 + r) * ldgx + n;
     if (n + 4 <= N) {
@@ -386,65 +384,81 @@ __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float
 }
 
 // ------------------------------------------------------------ data movement
-// LDS rows -> RC global matrix (block rows at tick rows r0 ..): one lane per
-// output chunk (RR rows of one column), built from RR element reads of the
-// LDS rows, so every lane of the block works and consecutive lanes store
-// consecutive chunks of a row group.  Columns up to the next multiple of RR
-// (zero in LDS) are written too.
+// LDS rows -> RC global matrix (block rows at tick rows r0 ..), columns up
+// to the next multiple of RR (zero in LDS) included; consecutive lanes store
+// consecutive 16-byte chunks (RR rows of one column) of a row group.
+// float32: a lane builds a chunk from RR element reads.  bf16: 16 lanes take
+// 8 rows x 16 columns with two transposing LDS reads (ds_read_b64_tr_b16:
+// lane i of the 16 addresses 4 elements of row i / 4, columns 4 (i mod 4) ..,
+// lane j receives column j of the 4 rows), where element reads took eight
+// 2-byte reads and their packing per chunk.  The LDS buffers are padded to
+// a multiple of the MFMA depth (32 columns), so the 16-column units stay
+// inside.  Run by the copy threads.
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 template <typename T, int BR, bool NT>
 __device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
   constexpr int RR = Ch<T>::CE;
+  const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
   const int cw = (cols + RR - 1) / RR * RR;
   VFL_GLOBAL char* g = glb((char*)m.p);
   const int64_t cp = m.cp;
   const int nrg = m.rows > 0 ? min(BR / RR, (m.rows - r0) / RR) : BR / RR;   // row groups inside m
-  for (int u = threadIdx.x; u < nrg * cw; u += kNT) {
-    const int rg = u / cw, c = u - rg * cw;
-    const char* src = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
-    u32x4 v;
-    if constexpr (RR == 8) {
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t lo = *(const uint16_t*)(src + (2 * w) * b.pitch);
-        const uint32_t hi = *(const uint16_t*)(src + (2 * w + 1) * b.pitch);
-        v[w] = lo | (hi << 16);
-      }
-    } else {
-#pragma unroll
-      for (int w = 0; w < 4; ++w) v[w] = *(const uint32_t*)(src + w * b.pitch);
-    }
-    VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
-    if constexpr (NT) __builtin_nontemporal_store(v, dst);
-    else *dst = v;
-    if constexpr (RR == 8) {
+  if constexpr (RR == 8) {
+    const int nc16 = (cw + 15) / 16;
+    const int i16 = tid & 15;
+    const int lofs = (i16 >> 2) * b.pitch + (i16 & 3) * 8;   // the lane's source in a 4 x 16 tile
+    // u: 8 x 16 unit, the same for the 16 lanes
+    for (int u = tid >> 4; u < nrg * nc16; u += nt >> 4) {
+      const int rg = u / nc16, c = 16 * (u - rg * nc16) + i16;
+      const char* src = s + b.off + rg * 8 * b.pitch + (c - i16) * 2 + lofs;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)src);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(src + 4 * b.pitch));
+      const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+      const u32x4 v = u32x4{l2[0], l2[1], h2[0], h2[1]};
+      if (c >= cw) continue;
+      VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
+      if constexpr (NT) __builtin_nontemporal_store(v, dst);
+      else *dst = v;
       if (m.bits && c < cols) {
         // the chunk's positive rows, one bit each (ReLU outputs: a row is
         // positive when its sign bit is clear and it is not zero)
         uint32_t byte = 0;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const uint32_t lo = v[w] & 0xffffu, hi = v[w] >> 16;
-          byte |= (uint32_t)(lo != 0 && !(lo & 0x8000u)) << (2 * w);
-          byte |= (uint32_t)(hi != 0 && !(hi & 0x8000u)) << (2 * w + 1);
+          const uint32_t x = v[w] & 0xffffu, y = v[w] >> 16;
+          byte |= (uint32_t)(x != 0 && !(x & 0x8000u)) << (2 * w);
+          byte |= (uint32_t)(y != 0 && !(y & 0x8000u)) << (2 * w + 1);
         }
         glb(m.bits)[(int64_t)(r0 / RR + rg) * m.ldb + c] = (uint8_t)byte;
       }
     }
+  } else {
+    for (int u = tid; u < nrg * cw; u += nt) {
+      const int rg = u / cw, c = u - rg * cw;
+      const char* src = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
+      u32x4 v;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[w] = *(const uint32_t*)(src + w * b.pitch);
+      VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
+      if constexpr (NT) __builtin_nontemporal_store(v, dst);
+      else *dst = v;
+    }
   }
 }
 
-template <typename T, int BR>
+// m.p null: nothing; with the streaming hint when m.nt (matrices too large
+// for the L2; the two loops are kept apart so that the hint survives)
+template <typename T, int BR, bool HINT = false>
 __device__ __forceinline__ void lds_to_rc(const char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
+  if (!m.p) return;
+  if constexpr (HINT) {
+    if (m.nt) {
+      lds_to_rc_<T, BR, true>(s, b, cols, m, r0);
+      return;
+    }
+  }
   lds_to_rc_<T, BR, false>(s, b, cols, m, r0);
-}
-
-// the same with the streaming hint when m.nt (matrices too large for the
-// L2; the two loops are kept apart so that the hint survives), for B's
-// forward, whose copies are its largest output
-template <typename T, int BR>
-__device__ __forceinline__ void lds_to_rc_hint(const char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
-  if (m.nt) lds_to_rc_<T, BR, true>(s, b, cols, m, r0);
-  else lds_to_rc_<T, BR, false>(s, b, cols, m, r0);
 }
 
 // zero rows r0 .. r0+BR-1 of an RC global matrix (columns below cols)
@@ -599,14 +613,16 @@ __device__ __forceinline__ void rc_to_lds(char* s, const LBuf& b, int cols, cons
   }
 }
 
-// LDS rows -> row-major global rows (16-byte chunks; rows below rv)
-template <typename T, int BR>
+// LDS rows -> row-major global rows (16-byte chunks; rows below rv), by the
+// copy threads (COPY) or the product threads
+template <typename T, int BR, bool COPY>
 __device__ __forceinline__ void lds_to_rows(const char* s, const LBuf& b, int cols, void* dst,
                                             int64_t ld, int r0, int rv) {
+  const int tid = COPY ? (int)threadIdx.x - kNT : (int)threadIdx.x;
   constexpr int CE = Ch<T>::CE;
   const int nch = (cols + CE - 1) / CE;
   VFL_GLOBAL char* d = glb((char*)dst);
-  for (int u = threadIdx.x; u < rv * nch; u += kNT) {
+  for (int u = tid; u < rv * nch; u += COPY ? (int)blockDim.x - kNT : kNT) {
     const int r = u / nch, ch = u % nch;
     *(VFL_GLOBAL u32x4*)(d + ((int64_t)(r0 + r) * ld + ch * CE) * sizeof(T)) =
         *(const u32x4*)(s + b.off + r * b.pitch + ch * 16);
@@ -794,8 +810,8 @@ __device__ __forceinline__ void msg_rows(const char* s, const LBuf& src, int D, 
 }
 
 // ------------------------------------------------------------------ kernels
-template <typename T, int RT, int PF>
-__global__ __launch_bounds__(kNT) void k_fwd(const FwdJob* __restrict__ jp, ChainCall cc,
+template <typename T, int RT>
+__global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_fwd(const FwdJob* __restrict__ jp, ChainCall cc,
                                              TickRef tr) {
   constexpr int BR = 16 * RT;
   extern __shared__ __attribute__((aligned(16))) char s[];
@@ -809,30 +825,36 @@ __global__ __launch_bounds__(kNT) void k_fwd(const FwdJob* __restrict__ jp, Chai
   const int r0 = blockIdx.x * BR;
   if (r0 >= k.rows) return;
   const int rv = min(BR, k.rows - r0);
-  Pipe<PF> pp;
+  const int din = j.in.n_cat * j.in.E + j.in.dense_in;
+  const ChainLayer& last = j.l[nL - 1];
+  if (threadIdx.x >= kNT) {
+    __syncthreads();
+    lds_to_rc<T, BR, true>(s, j.in.buf, din, j.in.rc, r0);
+    for (int l = 0; l < nL; ++l) {
+      __syncthreads();
+      lds_to_rc<T, BR, true>(s, j.l[l].out, j.l[l].N, j.l[l].rc, r0);
+    }
+    lds_to_rows<T, BR, true>(s, last.out, last.N, j.z, j.ldz, r0, rv);
+    return;
+  }
+  Pipe pp;
   prefetch<T>(&j.l[0], pp);   // overlaps the input rows' loads
   const uint32_t wx = warm_l2(j.warm, jp);
   copy_bias(s, j.bt);
   load_input<T, BR>(s, j.in, cc, k, r0, rv);
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
-  // each stage's RC copy goes out during the next product
-  RcPend pend{j.in.buf, j.in.n_cat * j.in.E + j.in.dense_in, j.in.rc, r0};
   for (int l = 0; l < nL; ++l) {
-    run_layer<T, RT, true>(s, j.l[l], rv, pp, l + 1 < nL ? &j.l[l + 1] : nullptr, pend);
+    run_layer<T, RT>(s, j.l[l], rv, pp, l + 1 < nL ? &j.l[l + 1] : nullptr);
     __syncthreads();
-    pend = RcPend{j.l[l].out, j.l[l].N, j.l[l].rc, r0};
   }
-  if (pend.m.p) lds_to_rc_hint<T, BR>(s, pend.b, pend.cols, pend.m, r0);
-  const ChainLayer& last = j.l[nL - 1];
-  lds_to_rows<T, BR>(s, last.out, last.N, j.z, j.ldz, r0, rv);
   if (j.publish)
     msg_rows<T, T, BR>(s, last.out, last.N, j.m, (uint32_t)k.group, k.row0, j.zhat, j.ldzh, j.norm,
                        j.cfac, r0, rv);
 }
 
-template <typename T, int RT, int PF>
-__global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp, ChainCall cc,
+template <typename T, int RT>
+__global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJob* __restrict__ jp, ChainCall cc,
                                                 TickRef tr) {
   constexpr int BR = 16 * RT;
   constexpr int CE = Ch<T>::CE, KS = Ch<T>::KS;
@@ -855,6 +877,7 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
   if (r0 >= k.rows) {
     // rows past a short group: zero delta rows, so that the weight
     // gradient may read whole row steps
+    if (threadIdx.x >= kNT) return;
     zero_rc<T, BR>(j.dh_rc, j.ft[H - 1].N, r0);
     for (int q = 0; q + 1 < H; ++q) zero_rc<T, BR>(j.dt[q].rc, j.dt[q].N, r0);
     zero_rc<T, BR>(j.dc.rc, j.dA, r0);
@@ -863,6 +886,35 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
   }
   const int rv = min(BR, k.rows - r0);
   const int Hd = j.ft[H - 1].N;
+  const int din = j.in.n_cat * j.in.E + j.in.dense_in;
+  if (threadIdx.x >= kNT) {
+    // the copy of each stage's output runs beside the next stage
+    __syncthreads();
+    lds_to_rc<T, BR>(s, j.in.buf, din, j.in.rc, r0);
+    for (int l = 0; l < LA; ++l) {
+      __syncthreads();
+      // (A's last layer writes cat, copied whole)
+      if (l + 1 < LA) lds_to_rc<T, BR>(s, j.fa[l].out, j.fa[l].N, j.fa[l].rc, r0);
+      else lds_to_rc<T, BR>(s, j.cat, j.dA + j.dB, j.cat_rc, r0);
+    }
+    for (int q = 0; q < H; ++q) {
+      __syncthreads();
+      lds_to_rc<T, BR>(s, j.ft[q].out, j.ft[q].N, j.ft[q].rc, r0);
+    }
+    __syncthreads();
+    lds_to_rc<T, BR>(s, j.dh, Hd, j.dh_rc, r0);
+    for (int q = 0; q + 1 < H; ++q) {
+      __syncthreads();
+      lds_to_rc<T, BR>(s, j.dt[q].out, j.dt[q].N, j.dt[q].rc, r0);
+    }
+    __syncthreads();
+    lds_to_rc<T, BR>(s, j.dc.out, j.dA, j.dc.rc, r0);
+    for (int q = 0; q < nda; ++q) {
+      __syncthreads();
+      lds_to_rc<T, BR>(s, j.da[q].out, j.da[q].N, j.da[q].rc, r0);
+    }
+    return;
+  }
   // the labels (to LDS with the inputs) and the logit weights of the lane's
   // columns in the logit stage (columns 256 i + 4 lane .. +4, kept in
   // registers); loads clamped, so all are unconditional
@@ -883,8 +935,8 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
     py = y[min((int)threadIdx.x, rv - 1)];
   }
   const float lbias = glb(j.lb)[0];
-  Pipe<PF> pp;
-  prefetch<T, PF>(&j.fa[0], pp);
+  Pipe pp;
+  prefetch<T>(&j.fa[0], pp);
   const uint32_t wx = warm_l2(j.warm, jp);
   copy_bias(s, j.bt);
 
@@ -906,22 +958,15 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
   }
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
-  // each stage's RC copy goes out during the next product (A's last
-  // layer writes cat, copied whole)
-  RcPend pend{j.in.buf, j.in.n_cat * j.in.E + j.in.dense_in, j.in.rc, r0};
   for (int l = 0; l < LA; ++l) {
-    run_layer<T, RT>(s, j.fa[l], rv, pp, l + 1 < LA ? &j.fa[l + 1] : &j.ft[0], pend);
+    run_layer<T, RT>(s, j.fa[l], rv, pp, l + 1 < LA ? &j.fa[l + 1] : &j.ft[0]);
     __syncthreads();
-    pend = l + 1 < LA ? RcPend{j.fa[l].out, j.fa[l].N, j.fa[l].rc, r0} : RcPend{j.cat, j.dA + j.dB, j.cat_rc, r0};
   }
   // top hidden layers
   for (int q = 0; q < H; ++q) {
-    run_layer<T, RT>(s, j.ft[q], rv, pp, q + 1 < H ? &j.ft[q + 1] : (H > 1 ? &j.dt[0] : &j.dc), pend);
+    run_layer<T, RT>(s, j.ft[q], rv, pp, q + 1 < H ? &j.ft[q + 1] : (H > 1 ? &j.dt[0] : &j.dc));
     __syncthreads();
-    pend = RcPend{j.ft[q].out, j.ft[q].N, j.ft[q].rc, r0};
   }
-  // the logit stage reads the last hidden output, not a product's input
-  if (pend.m.p) lds_to_rc<T, BR>(s, pend.b, pend.cols, pend.m, r0);
   // logit + BCE (Eq. 1), dl = sigmoid(l) - y, or for regression the
   // squared error and dl = 2 (l - y): a wavefront per row (its
   // BR / 8 rows one after the other), lane on the columns 256 i + 4 lane
@@ -1047,12 +1092,10 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
       part[c] = t;
     }
   }
-  pend = RcPend{j.dh, j.ft[H - 1].N, j.dh_rc, r0};
   // top input-gradient chain
   for (int q = 0; q + 1 < H; ++q) {
-    run_layer<T, RT>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc, pend);
+    run_layer<T, RT>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc);
     __syncthreads();
-    pend = RcPend{j.dt[q].out, j.dt[q].N, j.dt[q].rc, r0};
   }
   // concat product: A's cut delta and the gradient message for B
   {
@@ -1062,7 +1105,7 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
     const bool maskA = j.dc.mask.pitch > 0, gextra = j.gextra != 0;
     VFL_GLOBAL T* ring = glb((T*)j.ring);
     const int64_t ldr = j.ldring;
-    block_mm<T, RT>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr), pend,
+    block_mm<T, RT>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
                     [&](int r, int n, const f32x4& a, const f32x4&) {
       const bool ok = r < rv;
       if (n + 4 <= dA) {
@@ -1090,23 +1133,20 @@ __global__ __launch_bounds__(kNT) void k_active(const ActiveJob* __restrict__ jp
       }
     });
     __syncthreads();
-    pend = RcPend{ob, dA, j.dc.rc, r0};
     if (gextra)
       msg_rows<T, float, BR>(s, msg, j.dB, j.m, (uint32_t)k.group, k.row0, j.ring, j.ldring, nullptr,
                              nullptr, r0, rv);
   }
   // A's input-gradient chain
   for (int q = 0; q < nda; ++q) {
-    run_layer<T, RT>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr), pend);
+    run_layer<T, RT>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr));
     __syncthreads();
-    pend = RcPend{j.da[q].out, j.da[q].N, j.da[q].rc, r0};
   }
-  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp, pend);
-  else if (pend.m.p) lds_to_rc<T, BR>(s, pend.b, pend.cols, pend.m, r0);
+  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
 }
 
-template <typename T, int RT, int PF>
-__global__ __launch_bounds__(kNT) void k_bwd(const BwdJob* __restrict__ jp, ChainCall cc,
+template <typename T, int RT>
+__global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_bwd(const BwdJob* __restrict__ jp, ChainCall cc,
                                              TickRef tr) {
   constexpr int BR = 16 * RT;
   constexpr int KS = Ch<T>::KS;
@@ -1119,13 +1159,23 @@ __global__ __launch_bounds__(kNT) void k_bwd(const BwdJob* __restrict__ jp, Chai
   if (blockIdx.x == 0 && threadIdx.x == 0 && j.hdr_chk && glb(j.hdr_chk)[0] != k.chk) atomicAdd(j.err, 1);
   const int r0 = blockIdx.x * BR;
   if (r0 >= k.rows) {
+    if (threadIdx.x >= kNT) return;
     zero_rc<T, BR>(j.d_rc, j.D, r0);
     for (int q = 0; q < nd; ++q) zero_rc<T, BR>(j.dx[q].rc, j.dx[q].N, r0);
     return;
   }
   const int rv = min(BR, k.rows - r0);
-  Pipe<PF> pp;
-  if (nd > 0 || has_gx) prefetch<T, PF>(nd > 0 ? &j.dx[0] : &j.gx, pp);
+  if (threadIdx.x >= kNT) {
+    __syncthreads();
+    lds_to_rc<T, BR, true>(s, j.d, j.D, j.d_rc, r0);
+    for (int q = 0; q < nd; ++q) {
+      __syncthreads();
+      lds_to_rc<T, BR, true>(s, j.dx[q].out, j.dx[q].N, j.dx[q].rc, r0);
+    }
+    return;
+  }
+  Pipe pp;
+  if (nd > 0 || has_gx) prefetch<T>(nd > 0 ? &j.dx[0] : &j.gx, pp);
   const uint32_t wx = warm_l2(j.warm, jp);
   // the ReLU masks of every layer of the chain, each in an LDS buffer of
   // its own (bf16: the ReLU bits of this group's forward as bytes; float32:
@@ -1184,22 +1234,17 @@ __global__ __launch_bounds__(kNT) void k_bwd(const BwdJob* __restrict__ jp, Chai
   }
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
-  // each stage's RC copy goes out during the next product
-  RcPend pend{j.d, j.D, j.d_rc, r0};
   for (int q = 0; q < nd; ++q) {
     const ChainLayer& L = j.dx[q];
-    run_layer<T, RT, true, PF, sizeof(T) == 2>(s, L, rv, pp, q + 1 < nd ? &j.dx[q + 1] : (has_gx ? &j.gx : nullptr),
-                                               pend);
+    run_layer<T, RT, sizeof(T) == 2>(s, L, rv, pp, q + 1 < nd ? &j.dx[q + 1] : (has_gx ? &j.gx : nullptr));
     __syncthreads();
-    pend = RcPend{L.out, L.N, L.rc, r0};
   }
-  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp, pend);
-  else if (pend.m.p) lds_to_rc_hint<T, BR>(s, pend.b, pend.cols, pend.m, r0);
+  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
   if (j.drm) {
     // the last delta of the chain, row-major, for the layer product below it
     const LBuf last = nd > 0 ? j.dx[nd - 1].out : j.d;
     const int w = nd > 0 ? j.dx[nd - 1].N : j.D;
-    lds_to_rows<T, BR>(s, last, w, j.drm, j.lddrm, r0, rv);
+    lds_to_rows<T, BR, false>(s, last, w, j.drm, j.lddrm, r0, rv);
   }
 }
 
@@ -1211,69 +1256,59 @@ hipError_t raise_lds(K kernel) {
 }  // namespace
 
 
-#define VFL_PF_RT(K, T, PF, rt, ...)                                                            \
-  do {                                                                                       \
-    if (rt == 1) hipLaunchKernelGGL((K<T, 1, PF>), __VA_ARGS__);                          \
-    else if (rt == 2) hipLaunchKernelGGL((K<T, 2, PF>), __VA_ARGS__);                     \
-    else if (rt == 3) hipLaunchKernelGGL((K<T, 3, PF>), __VA_ARGS__);                     \
-    else if (rt == 4) hipLaunchKernelGGL((K<T, 4, PF>), __VA_ARGS__);                     \
-    else return hipErrorInvalidValue;                                                        \
+#define VFL_CHAIN_RT(K, T, rt, ...)                                                         \
+  do {                                                                                     \
+    if (rt == 1) hipLaunchKernelGGL((K<T, 1>), __VA_ARGS__);                               \
+    else if (rt == 2) hipLaunchKernelGGL((K<T, 2>), __VA_ARGS__);                          \
+    else if (rt == 3) hipLaunchKernelGGL((K<T, 3>), __VA_ARGS__);                          \
+    else if (rt == 4) hipLaunchKernelGGL((K<T, 4>), __VA_ARGS__);                          \
+    else return hipErrorInvalidValue;                                                      \
+  } while (0)
+#define VFL_CHAIN(K, e, rt, cw, ...)                                                        \
+  do {                                                                                     \
+    if (lds > kLdsMax || blocks < 1 || cw < 1 || cw > kChainCopyWaves) return hipErrorInvalidValue; \
+    const dim3 thr(kNT + 64 * cw);                                                         \
+    if (e == BF16) VFL_CHAIN_RT(K, uint16_t, rt, dim3(blocks), thr, __VA_ARGS__);          \
+    else VFL_CHAIN_RT(K, float, rt, dim3(blocks), thr, __VA_ARGS__);                       \
   } while (0)
 
-hipError_t launch_fwd(Elt e, int rt, int pf, const FwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_fwd(Elt e, int rt, int cw, const FwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st) {
-  if (lds > kLdsMax || blocks < 1) return hipErrorInvalidValue;
-  if (pf == kPFWide && e == BF16) VFL_PF_RT(k_fwd, uint16_t, kPFWide, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow && e == BF16) VFL_PF_RT(k_fwd, uint16_t, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow) VFL_PF_RT(k_fwd, float, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else return hipErrorInvalidValue;
+  VFL_CHAIN(k_fwd, e, rt, cw, lds, st, job, c, tr);
   return hipGetLastError();
 }
 
-hipError_t launch_active(Elt e, int rt, int pf, const ActiveJob* job, int lds, int blocks,
+hipError_t launch_active(Elt e, int rt, int cw, const ActiveJob* job, int lds, int blocks,
                          const ChainCall& c, TickRef tr, hipStream_t st) {
-  if (lds > kLdsMax || blocks < 1) return hipErrorInvalidValue;
-  if (pf == kPFWide && e == BF16) VFL_PF_RT(k_active, uint16_t, kPFWide, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow && e == BF16) VFL_PF_RT(k_active, uint16_t, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow) VFL_PF_RT(k_active, float, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else return hipErrorInvalidValue;
+  VFL_CHAIN(k_active, e, rt, cw, lds, st, job, c, tr);
   return hipGetLastError();
 }
 
-hipError_t launch_bwd(Elt e, int rt, int pf, const BwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_bwd(Elt e, int rt, int cw, const BwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st) {
-  if (lds > kLdsMax || blocks < 1) return hipErrorInvalidValue;
-  if (pf == kPFWide && e == BF16) VFL_PF_RT(k_bwd, uint16_t, kPFWide, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow && e == BF16) VFL_PF_RT(k_bwd, uint16_t, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else if (pf == kPFNarrow) VFL_PF_RT(k_bwd, float, kPFNarrow, rt, dim3(blocks), dim3(kNT), lds, st, job, c, tr);
-  else return hipErrorInvalidValue;
+  VFL_CHAIN(k_bwd, e, rt, cw, lds, st, job, c, tr);
   return hipGetLastError();
 }
+
+namespace {
+template <typename T, int RT>
+hipError_t raise_lds_rt() {
+  for (hipError_t e : {raise_lds(k_fwd<T, RT>), raise_lds(k_active<T, RT>), raise_lds(k_bwd<T, RT>)})
+    if (e != hipSuccess) return e;
+  return hipSuccess;
+}
+template <typename T>
+hipError_t raise_lds_all() {
+  for (hipError_t e : {raise_lds_rt<T, 1>(), raise_lds_rt<T, 2>(), raise_lds_rt<T, 3>(), raise_lds_rt<T, 4>()})
+    if (e != hipSuccess) return e;
+  return hipSuccess;
+}
+}  // namespace
 
 hipError_t chain_init() {
-  const hipError_t r[] = {
-      raise_lds(k_fwd<uint16_t, 1, kPFNarrow>), raise_lds(k_fwd<uint16_t, 2, kPFNarrow>),
-      raise_lds(k_fwd<uint16_t, 3, kPFNarrow>), raise_lds(k_fwd<uint16_t, 4, kPFNarrow>),
-      raise_lds(k_fwd<uint16_t, 1, kPFWide>), raise_lds(k_fwd<uint16_t, 2, kPFWide>),
-      raise_lds(k_fwd<uint16_t, 3, kPFWide>), raise_lds(k_fwd<uint16_t, 4, kPFWide>),
-      raise_lds(k_fwd<float, 1, kPFNarrow>), raise_lds(k_fwd<float, 2, kPFNarrow>),
-      raise_lds(k_fwd<float, 3, kPFNarrow>), raise_lds(k_fwd<float, 4, kPFNarrow>),
-      raise_lds(k_active<uint16_t, 1, kPFNarrow>), raise_lds(k_active<uint16_t, 2, kPFNarrow>),
-      raise_lds(k_active<uint16_t, 3, kPFNarrow>), raise_lds(k_active<uint16_t, 4, kPFNarrow>),
-      raise_lds(k_active<uint16_t, 1, kPFWide>), raise_lds(k_active<uint16_t, 2, kPFWide>),
-      raise_lds(k_active<uint16_t, 3, kPFWide>), raise_lds(k_active<uint16_t, 4, kPFWide>),
-      raise_lds(k_active<float, 1, kPFNarrow>), raise_lds(k_active<float, 2, kPFNarrow>),
-      raise_lds(k_active<float, 3, kPFNarrow>), raise_lds(k_active<float, 4, kPFNarrow>),
-      raise_lds(k_bwd<uint16_t, 1, kPFNarrow>), raise_lds(k_bwd<uint16_t, 2, kPFNarrow>),
-      raise_lds(k_bwd<uint16_t, 3, kPFNarrow>), raise_lds(k_bwd<uint16_t, 4, kPFNarrow>),
-      raise_lds(k_bwd<uint16_t, 1, kPFWide>), raise_lds(k_bwd<uint16_t, 2, kPFWide>),
-      raise_lds(k_bwd<uint16_t, 3, kPFWide>), raise_lds(k_bwd<uint16_t, 4, kPFWide>),
-      raise_lds(k_bwd<float, 1, kPFNarrow>), raise_lds(k_bwd<float, 2, kPFNarrow>),
-      raise_lds(k_bwd<float, 3, kPFNarrow>), raise_lds(k_bwd<float, 4, kPFNarrow>)};
-  for (hipError_t x : r)
-    if (x != hipSuccess) return x;
-  const hipError_t d = dwt_init();
-  return d != hipSuccess ? d : lin_init();
+  for (hipError_t e : {raise_lds_all<uint16_t>(), raise_lds_all<float>(), dwt_init(), lin_init()})
+    if (e != hipSuccess) return e;
+  return hipSuccess;
 }
 
 }  // namespace vfl
