@@ -129,8 +129,26 @@ struct Lds {
 
 struct FwdLds { LBuf buf[2], bias; int bytes = 0; };
 struct ActLds {
-  LBuf in, fa[VFL_MAX_LAYERS], cat, ft[VFL_MAX_LAYERS], P[2], msg, red, bias;
+  LBuf X[2], cat, msg, red, bias;
+  LBuf mfa[VFL_MAX_LAYERS], mft[VFL_MAX_LAYERS];   // ReLU masks of A's layers, the top's hidden layers
   int bytes = 0;
+};
+
+// Which of the two activation buffers each of k_active's stages writes
+// (A's last layer writes cat): a stage reads the one the stage before wrote,
+// whose RC copy runs beside it, and writes the other.
+struct ActBufs {
+  int in = 1, fa[VFL_MAX_LAYERS]{}, ft[VFL_MAX_LAYERS]{}, dh = 0, dt[VFL_MAX_LAYERS]{}, dc = 0, da[VFL_MAX_LAYERS]{};
+  ActBufs(int LA, int H) {
+    int x = 0;
+    auto next = [&] { x ^= 1; return x ^ 1; };
+    for (int l = 0; l + 1 < LA; ++l) fa[l] = next();
+    for (int j = 0; j < H; ++j) ft[j] = next();
+    dh = next();
+    for (int q = 0; q + 1 < H; ++q) dt[q] = next();
+    dc = next();
+    for (int q = 0; q + 1 < LA; ++q) da[q] = next();
+  }
 };
 struct BwdLds { LBuf P[2], mask[VFL_MAX_LAYERS]; int bytes = 0; };
 
@@ -368,22 +386,37 @@ void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
   l.KS = p.e == BF16 ? 32 : 16;
   l.BR = BR;
   const int es = elt_size(p.e);
-  for (int i = 0; i + 1 < p.A.L; ++i) a.fa[i] = l.take(p.A.out[i], es);
-  a.cat = l.take(p.dA + p.dB, es);
-  for (int j = 0; j + 1 < p.T.H; ++j) a.ft[j] = l.take(p.T.out[j], es);
-  int w = 1;
-  for (int j = 0; j < p.T.H; ++j) w = std::max(w, p.T.out[j]);
-  for (int i = 0; i < p.A.L; ++i) w = std::max(w, p.A.out[i]);
-  a.P[0] = l.take(w, es);
-  // buffers never live at the same time share LDS: the input (read by A's
-  // first layer only) with P[1] (first written after the logit stage), and
-  // the last top hidden output (dead once the logit stage has formed dh)
-  // with the float32 gradient-message staging (written by the concat
-  // product)
-  l.take_shared(a.in, p.A.din, es, a.P[1], w, es);
-  if (gextra) l.take_shared(a.ft[p.T.H - 1], p.T.out[p.T.H - 1], es, a.msg, p.dB, 4);
-  else a.ft[p.T.H - 1] = l.take(p.T.out[p.T.H - 1], es);
-  // logit weights [Hd], the block's labels, dl and loss [BR each]
+  const ActBufs x(p.A.L, p.T.H);
+  int w[2] = {1, 1};
+  auto holds = [&](int i, int width) { w[i] = std::max(w[i], width); };
+  holds(x.in, p.A.din);
+  for (int i = 0; i + 1 < p.A.L; ++i) holds(x.fa[i], p.A.out[i]);
+  for (int j = 0; j < p.T.H; ++j) holds(x.ft[j], p.T.out[j]);
+  holds(x.dh, p.T.out[p.T.H - 1]);
+  for (int q = 0; q + 1 < p.T.H; ++q) holds(x.dt[q], p.T.in[p.T.H - 1 - q]);
+  holds(x.dc, p.dA);
+  for (int q = 0; q + 1 < p.A.L; ++q) holds(x.da[q], p.A.in[p.A.L - 1 - q]);
+  a.X[0] = l.take(w[0], es);
+  a.X[1] = l.take(w[1], es);
+  // the float32 gradient-message staging (written by the concat product)
+  // takes the place of cat (last read by the top's first layer)
+  if (gextra) l.take_shared(a.cat, p.dA + p.dB, es, a.msg, p.dB, 4);
+  else a.cat = l.take(p.dA + p.dB, es);
+  // the backward needs only the ReLU masks of the forward's outputs, a byte
+  // per RC chunk.  With the outputs themselves kept to the end, ten 256-wide
+  // layers left room for 16 rows per block instead of 32 (8192 rows: k_active
+  // 109 -> 75 us), 64-256-128 with a 256-wide top for 48 instead of 64
+  // (32768 rows: 82 -> 73 us)
+  auto mask = [&](bool relu, int width) {
+    LBuf m;
+    if (!relu) return m;
+    const int pitch = (width + 31) / 32 * 32 + 16;
+    m = l.raw(BR * es / 16 * pitch);
+    m.pitch = pitch;
+    return m;
+  };
+  for (int i = 0; i < p.A.L; ++i) a.mfa[i] = mask(p.A.relu[i], p.A.out[i]);
+  for (int j = 0; j + 1 < p.T.H; ++j) a.mft[j] = mask(p.T.relu[j], p.T.out[j]);
   // the block's labels, per-wavefront partials of the logit layer's
   // weight gradient [kChainWaves][Hd rounded to 4] and of {loss, dl}
   a.red = l.raw(4 * (BR + kChainWaves * ((p.T.out[p.T.H - 1] + 3) / 4 * 4) + 2 * kChainWaves));
@@ -740,13 +773,19 @@ bool layer_fits(const Plan& p, const ChainLayer& L, int BR, int lds, bool lds_ou
   if (L.bl >= 0 && (L.bl % 16 || L.bl + 4 * ((L.N + 31) / 32 * 32) > lds)) return false;
   if (!inside(L.in, L.K)) return false;
   if (lds_out && !inside(L.out, out_cols < 0 ? L.N : out_cols)) return false;
+  // byte masks: a byte per 16 / es rows and column, read four columns at a
+  // time up to the MFMA depth; those loaded from the stash are copied 16
+  // columns at a time
+  auto bytes_inside = [&](const LBuf& m, int cols) {
+    return m.off >= 0 && m.off % 16 == 0 && m.pitch % 16 == 0 && m.pitch >= (cols + KS - 1) / KS * KS &&
+           m.off + m.pitch * (BR * es / 16) <= lds;
+  };
+  const int mcols = out_cols < 0 ? L.N : out_cols;
+  if (L.mask_out.pitch && !bytes_inside(L.mask_out, L.N)) return false;
   if (L.mask.pitch && L.mask_bits) {
-    // a byte per 8 rows and column, copied 16 columns at a time
     const int nb = (L.N + 15) / 16 * 16;
-    if (BR % 8 || L.mask.off < 0 || L.mask.off % 16 || L.mask.pitch % 16 || L.mask.pitch < nb ||
-        L.mask.off + L.mask.pitch * (BR / 8) > lds || !L.mask_src.bits || L.mask_src.ldb < nb ||
-        L.mask_src.ldb % 16)
-      return false;
+    if (!bytes_inside(L.mask, mcols)) return false;
+    if (L.mask_src.p && (!L.mask_src.bits || L.mask_src.ldb < nb || L.mask_src.ldb % 16)) return false;
   } else if (L.mask.pitch && !inside(L.mask, L.N)) {
     return false;
   }
@@ -838,7 +877,8 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.in.T = A.spec.n_cat ? at_f(A.T) : nullptr;
     a.in.idt = A.spec.n_cat ? (int32_t*)(ws + A.idt[0]) : nullptr; a.in.ldi = p.R;
     a.in.bad_ids = (int32_t*)(ws + p.hdr) + 2 * kMaxSlots * 4 + 1;
-    a.in.buf = la.in;
+    const ActBufs x(A.L, T.H);
+    a.in.buf = la.X[x.in];
     a.in.rc = rcm(c, A.x0rc[0], A.din);
     a.bt.src = at_f(p.bias_a); a.bt.off = la.bias.off; a.bt.n4 = p.nbias_a / 4;
     a.warm.p[0] = c->ws + A.Wq[0][0];
@@ -847,12 +887,13 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.warm.lines[1] = (int32_t)((T.packed_end - T.Wq[0]) / 128);
     a.LA = A.L;
     for (int l = 0; l < A.L; ++l) {
-      const LBuf src = l == 0 ? la.in : la.fa[l - 1];
-      const LBuf dst = l + 1 < A.L ? la.fa[l] : la.cat;
+      const LBuf src = la.X[l == 0 ? x.in : x.fa[l - 1]];
+      const LBuf dst = l + 1 < A.L ? la.X[x.fa[l]] : la.cat;
       a.fa[l] = layer(c->ws + A.Wq[0][l], A.kq[l], la.bias.off + 4 * A.bo[l], A.out[l], A.in[l], A.relu[l],
                       src, dst);
       if (l + 1 < A.L) a.fa[l].rc = rcm(c, A.arc[0][l], A.out[l]);
       else a.fa[l].nopad = 1;   // B's embedding is already in cat past dA
+      a.fa[l].mask_out = la.mfa[l];
     }
     a.cat = la.cat; a.cat_rc = rcm(c, p.cat_rc, p.dA + p.dB); a.dA = p.dA; a.dB = p.dB;
     a.zb = c->ws + P.zhat[q]; a.ldzb = (int32_t)ld_of(p.dB);
@@ -860,26 +901,32 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.H = T.H;
     for (int j = 0; j < T.H; ++j) {
       a.ft[j] = layer(c->ws + T.Wq[j], T.kq[j], la.bias.off + 4 * T.bo[j], T.out[j], T.in[j], T.relu[j],
-                      j == 0 ? la.cat : la.ft[j - 1], la.ft[j]);
-      if (j + 1 < T.H) a.ft[j].rc = rcm(c, T.arc[j], T.out[j]);
+                      j == 0 ? la.cat : la.X[x.ft[j - 1]], la.X[x.ft[j]]);
+      if (j + 1 < T.H) {
+        a.ft[j].rc = rcm(c, T.arc[j], T.out[j]);
+        a.ft[j].mask_out = la.mft[j];
+      }
     }
     a.lw = at_f(T.W[T.H]); a.lb = at_f(T.b[T.H]); a.relu_h = T.relu[T.H - 1];
     a.mse = (o.flags & VFL_LOSS_MSE) != 0;
-    a.dh = la.P[0]; a.dh_rc = rcm(c, T.drc[T.H - 1], T.out[T.H - 1]);
+    a.dh = la.X[x.dh]; a.dh_rc = rcm(c, T.drc[T.H - 1], T.out[T.H - 1]);
     a.part = at_f(T.logit_part);
     a.red = la.red;
     for (int qq = 0; qq + 1 < T.H; ++qq) {
       const int j = T.H - 1 - qq;           // delta of top layer j -> layer j-1
       ChainLayer& L = a.dt[qq];
-      L = layer(c->ws + T.Wtq[j], T.kt[j], -1, T.in[j], T.out[j], false, la.P[qq % 2], la.P[(qq + 1) % 2]);
-      if (T.relu[j - 1]) L.mask = la.ft[j - 1];
+      L = layer(c->ws + T.Wtq[j], T.kt[j], -1, T.in[j], T.out[j], false, la.X[qq ? x.dt[qq - 1] : x.dh],
+                la.X[x.dt[qq]]);
+      L.mask = la.mft[j - 1];
+      L.mask_bits = 1;
       L.rc = rcm(c, T.drc[j - 1], T.out[j - 1]);
     }
     {
-      const int h = T.H - 1;
       ChainLayer& L = a.dc;
-      L = layer(c->ws + T.Wtq[0], T.kt[0], -1, p.dA + p.dB, T.out[0], false, la.P[h % 2], la.P[(h + 1) % 2]);
-      if (A.relu[A.L - 1]) L.mask = la.cat;
+      L = layer(c->ws + T.Wtq[0], T.kt[0], -1, p.dA + p.dB, T.out[0], false,
+                la.X[T.H > 1 ? x.dt[T.H - 2] : x.dh], la.X[x.dc]);
+      L.mask = la.mfa[A.L - 1];
+      L.mask_bits = 1;
       L.rc = rcm(c, A.drc[A.L - 1], p.dA);
     }
     a.gextra = gextra;
@@ -890,17 +937,17 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.nda = A.L - 1;
     for (int qq = 0; qq + 1 < A.L; ++qq) {
       const int l = A.L - 1 - qq;           // delta of A's layer l -> layer l-1
-      const int h = T.H + qq;
       ChainLayer& L = a.da[qq];
-      L = layer(c->ws + A.Wtq[0][l], A.kt[l], -1, A.in[l], A.out[l], false, la.P[h % 2], la.P[(h + 1) % 2]);
-      if (A.relu[l - 1]) L.mask = la.fa[l - 1];
+      L = layer(c->ws + A.Wtq[0][l], A.kt[l], -1, A.in[l], A.out[l], false, la.X[qq ? x.da[qq - 1] : x.dc],
+                la.X[x.da[qq]]);
+      L.mask = la.mfa[l - 1];
+      L.mask_bits = 1;
       L.rc = rcm(c, A.drc[l - 1], A.out[l - 1]);
     }
     a.has_gx = A.spec.n_cat > 0;
     if (a.has_gx) {
-      const int h = T.H + A.L - 1;
       a.gx = layer(c->ws + A.Wtq[0][0], A.kt[0], -1, A.spec.n_cat * A.spec.emb_dim, A.out[0], false,
-                   la.P[h % 2], LBuf());
+                   la.X[A.L > 1 ? x.da[A.L - 2] : x.dc], LBuf());
       a.gxp = at_f(A.gx); a.ldgx = (int32_t)A.ldgx;
     }
 

@@ -327,7 +327,8 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
 }
 
 // Forward or input-gradient layer into LDS (see ChainLayer).
-// MB: the mask (when there is one) is the byte form of the ReLU bits
+// MB: the mask (when there is one) holds a byte per RR rows and column
+// instead of elements
 template <typename T, int RT, bool MB = false>
 __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, Pipe& p,
                                           const ChainLayer* next) {
@@ -341,9 +342,9 @@ __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, 
     if constexpr (MB) {
       if (msk) {
         // the 4 columns' bytes of r's row group in one word
-        const uint32_t w = *(const uint32_t*)(s + mk.off + (r >> 3) * mk.pitch + n);
+        const uint32_t w = *(const uint32_t*)(s + mk.off + (r / Ch<T>::CE) * mk.pitch + n);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = (w >> (8 * i + (r & 7))) & 1u ? 1.f : 0.f;
+        for (int i = 0; i < 4; ++i) m[i] = (w >> (8 * i + r % Ch<T>::CE)) & 1u ? 1.f : 0.f;
       }
     } else {
       if (msk) ld4<T>(lp(s, mk, r, n * (int)sizeof(T)), m);
@@ -397,13 +398,15 @@ __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 template <typename T, int BR, bool NT>
-__device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
+__device__ __forceinline__ void lds_to_rc_(char* s, const LBuf& b, int cols, const RCMat& m, int r0,
+                                           const LBuf& mask, int mcols) {
   constexpr int RR = Ch<T>::CE;
   const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
   const int cw = (cols + RR - 1) / RR * RR;
   VFL_GLOBAL char* g = glb((char*)m.p);
   const int64_t cp = m.cp;
   const int nrg = m.rows > 0 ? min(BR / RR, (m.rows - r0) / RR) : BR / RR;   // row groups inside m
+  const bool lds_mask = mask.pitch > 0;
   if constexpr (RR == 8) {
     const int nc16 = (cw + 15) / 16;
     const int i16 = tid & 15;
@@ -420,7 +423,7 @@ __device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int col
       VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
       if constexpr (NT) __builtin_nontemporal_store(v, dst);
       else *dst = v;
-      if (m.bits && c < cols) {
+      if ((m.bits || lds_mask) && c < mcols) {
         // the chunk's positive rows, one bit each (ReLU outputs: a row is
         // positive when its sign bit is clear and it is not zero)
         uint32_t byte = 0;
@@ -430,7 +433,8 @@ __device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int col
           byte |= (uint32_t)(x != 0 && !(x & 0x8000u)) << (2 * w);
           byte |= (uint32_t)(y != 0 && !(y & 0x8000u)) << (2 * w + 1);
         }
-        glb(m.bits)[(int64_t)(r0 / RR + rg) * m.ldb + c] = (uint8_t)byte;
+        if (m.bits) glb(m.bits)[(int64_t)(r0 / RR + rg) * m.ldb + c] = (uint8_t)byte;
+        if (lds_mask) s[mask.off + rg * mask.pitch + c] = (char)byte;
       }
     }
   } else {
@@ -443,22 +447,32 @@ __device__ __forceinline__ void lds_to_rc_(const char* s, const LBuf& b, int col
       VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
       if constexpr (NT) __builtin_nontemporal_store(v, dst);
       else *dst = v;
+      if (lds_mask && c < mcols) {
+        uint32_t byte = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) byte |= (uint32_t)(__uint_as_float(v[w]) > 0.f) << w;
+        s[mask.off + rg * mask.pitch + c] = (char)byte;
+      }
     }
   }
 }
 
 // m.p null: nothing; with the streaming hint when m.nt (matrices too large
-// for the L2; the two loops are kept apart so that the hint survives)
+// for the L2; the two loops are kept apart so that the hint survives).
+// mask (its pitch 0: none): the ReLU derivative of the first mcols columns
+// (0: cols) as well, in LDS, a byte per RR rows and column.
 template <typename T, int BR, bool HINT = false>
-__device__ __forceinline__ void lds_to_rc(const char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
+__device__ __forceinline__ void lds_to_rc(char* s, const LBuf& b, int cols, const RCMat& m, int r0,
+                                          const LBuf& mask = LBuf(), int mcols = 0) {
   if (!m.p) return;
+  if (mcols == 0) mcols = cols;
   if constexpr (HINT) {
     if (m.nt) {
-      lds_to_rc_<T, BR, true>(s, b, cols, m, r0);
+      lds_to_rc_<T, BR, true>(s, b, cols, m, r0, mask, mcols);
       return;
     }
   }
-  lds_to_rc_<T, BR, false>(s, b, cols, m, r0);
+  lds_to_rc_<T, BR, false>(s, b, cols, m, r0, mask, mcols);
 }
 
 // zero rows r0 .. r0+BR-1 of an RC global matrix (columns below cols)
@@ -894,12 +908,12 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     for (int l = 0; l < LA; ++l) {
       __syncthreads();
       // (A's last layer writes cat, copied whole)
-      if (l + 1 < LA) lds_to_rc<T, BR>(s, j.fa[l].out, j.fa[l].N, j.fa[l].rc, r0);
-      else lds_to_rc<T, BR>(s, j.cat, j.dA + j.dB, j.cat_rc, r0);
+      if (l + 1 < LA) lds_to_rc<T, BR>(s, j.fa[l].out, j.fa[l].N, j.fa[l].rc, r0, j.fa[l].mask_out);
+      else lds_to_rc<T, BR>(s, j.cat, j.dA + j.dB, j.cat_rc, r0, j.fa[l].mask_out, j.dA);
     }
     for (int q = 0; q < H; ++q) {
       __syncthreads();
-      lds_to_rc<T, BR>(s, j.ft[q].out, j.ft[q].N, j.ft[q].rc, r0);
+      lds_to_rc<T, BR>(s, j.ft[q].out, j.ft[q].N, j.ft[q].rc, r0, j.ft[q].mask_out);
     }
     __syncthreads();
     lds_to_rc<T, BR>(s, j.dh, Hd, j.dh_rc, r0);
@@ -1094,25 +1108,26 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   }
   // top input-gradient chain
   for (int q = 0; q + 1 < H; ++q) {
-    run_layer<T, RT>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc);
+    run_layer<T, RT, true>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc);
     __syncthreads();
   }
   // concat product: A's cut delta and the gradient message for B
   {
     const int dA = j.dA, dAB = j.dA + j.dB;
     const int dApad = (dA + KS - 1) / KS * KS;
-    const LBuf ob = j.dc.out, cat = j.cat, msg = j.msg;
-    const bool maskA = j.dc.mask.pitch > 0, gextra = j.gextra != 0;
+    const LBuf ob = j.dc.out, mk = j.dc.mask, msg = j.msg;
+    const bool maskA = mk.pitch > 0, gextra = j.gextra != 0;
     VFL_GLOBAL T* ring = glb((T*)j.ring);
     const int64_t ldr = j.ldring;
     block_mm<T, RT>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
                     [&](int r, int n, const f32x4& a, const f32x4&) {
       const bool ok = r < rv;
-      if (n + 4 <= dA) {
-        float m[4] = {1.f, 1.f, 1.f, 1.f}, v[4];
-        if (maskA) ld4<T>(lp(s, cat, r, n * (int)sizeof(T)), m);
+      if (n < dA) {   // dA is a multiple of 8: all four columns are A's
+        uint32_t w = ~0u;
+        float v[4];
+        if (maskA) w = *(const uint32_t*)(s + mk.off + (r / CE) * mk.pitch + n);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (ok && m[i] > 0.f) ? a[i] : 0.f;
+        for (int i = 0; i < 4; ++i) v[i] = (ok && ((w >> (8 * i + r % CE)) & 1u)) ? a[i] : 0.f;
         st4<T>(lp(s, ob, r, n * (int)sizeof(T)), v);
         return;
       }
@@ -1120,13 +1135,8 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       for (int i = 0; i < 4; ++i) {
         const int c = n + i;
         const float x = ok ? a[i] : 0.f;
-        if (c < dA) {
-          const bool keep = !maskA || ld1<T>((const T*)lp(s, cat, r, 0) + c) > 0.f;
-          st1<T>((T*)lp(s, ob, r, 0) + c, keep ? x : 0.f);
-        } else if (c < dApad) {
-          st1<T>((T*)lp(s, ob, r, 0) + c, 0.f);
-        }
-        if (c >= dA && c < dAB) {
+        if (c < dApad) st1<T>((T*)lp(s, ob, r, 0) + c, 0.f);
+        if (c < dAB) {
           if (gextra) ((float*)lp(s, msg, r, 0))[c - dA] = x;
           else if (ok) st1<T>((T*)(ring + (int64_t)(r0 + r) * ldr + (c - dA)), x);
         }
@@ -1139,7 +1149,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   }
   // A's input-gradient chain
   for (int q = 0; q < nda; ++q) {
-    run_layer<T, RT>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr));
+    run_layer<T, RT, true>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr));
     __syncthreads();
   }
   if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);

@@ -134,11 +134,14 @@ struct ChainLayer {
   const void* W = nullptr;
   int32_t kst = 0, N = 0, K = 0, relu = 0;
   int32_t bl = -1, nopad = 0;
-  // mask_bits: `mask` holds a byte per 8 rows and column (bit r % 8 of byte
-  // (r / 8) * pitch + column: the ReLU bits as B's forward records them),
-  // else one element per row and column (kept where positive)
+  // mask_bits: `mask` holds a byte per RR rows and column (bit r % RR of byte
+  // (r / RR) * pitch + column, RR = 8 for bf16, 4 for float32: the ReLU bits
+  // as B's forward records them, or a forward layer's mask_out), else one
+  // element per row and column (kept where positive).  mask_out (forward
+  // layers of k_active; pitch 0: none): where the RC copy of the layer's
+  // output leaves such bytes.
   int32_t mask_bits = 0;
-  LBuf in, out, mask;
+  LBuf in, out, mask, mask_out;
   RCMat rc, mask_src;
 };
 
@@ -223,8 +226,8 @@ struct FwdJob {
 // (per-block partials {sum loss, sum dl, sum_r dl * h[r][c]} to
 // part[block]; `red`: LDS for the logit weights, labels, dl and loss of the
 // block's rows), the top input-gradient chain dt (j = H-1 .. 1), the concat
-// product dc (columns < dA: A's cut delta into dc.out, masked by cat when
-// A's last layer has a ReLU; columns >= dA: the gradient message, staged as
+// product dc (columns < dA: A's cut delta into dc.out, masked when A's
+// last layer has a ReLU; columns >= dA: the gradient message, staged as
 // float32 in `msg` when clip/noise run, else written to ring directly), and
 // A's chain da (l = LA-1 .. 1); with tables, gx = the float32 gradient of
 // the embedding columns.
