@@ -398,10 +398,10 @@ void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
   for (int q = 0; q + 1 < p.A.L; ++q) holds(x.da[q], p.A.in[p.A.L - 1 - q]);
   a.X[0] = l.take(w[0], es);
   a.X[1] = l.take(w[1], es);
-  // the float32 gradient-message staging (written by the concat product)
-  // takes the place of cat (last read by the top's first layer)
-  if (gextra) l.take_shared(a.cat, p.dA + p.dB, es, a.msg, p.dB, 4);
-  else a.cat = l.take(p.dA + p.dB, es);
+  // the gradient message's staging (written by the concat product; float32
+  // where clip or noise follow) takes the place of cat (last read by the
+  // top's first layer)
+  l.take_shared(a.cat, p.dA + p.dB, es, a.msg, p.dB, gextra ? 4 : es);
   // the backward needs only the ReLU masks of the forward's outputs, a byte
   // per RC chunk.  With the outputs themselves kept to the end, ten 256-wide
   // layers left room for 16 rows per block instead of 32 (8192 rows: k_active

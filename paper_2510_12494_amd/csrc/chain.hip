@@ -752,12 +752,57 @@ __device__ __forceinline__ void load_input(char* s, const RowInput& in, const Ch
   }
 }
 
+// lane i's value in every lane
+__device__ __forceinline__ float lane_value(float x, int i) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i));
+}
+
+// Sums of v[0 .. P-1] over the 64 lanes, P = 2, 4 or 8: lane l returns the
+// sum of v[l >> (6 - log2 P)].  A step at lane distance 32, 16 or 8 adds two
+// halves of the wavefront and deals the values out between them (the swaps
+// exchange a's upper with b's lower lanes); the rest sums in place.  The
+// pairs added are those of a butterfly at distances 32, 16, .. 1.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int P>
+__device__ __forceinline__ float rows_reduce(const float (&v)[P], int lane) {
+  constexpr int kRor8 = 0x128, kXor2 = 0x4e, kXor1 = 0xb1;   // row_ror:8, quad_perm [2,3,0,1], [1,0,3,2]
+  float x;
+  if constexpr (P == 2) {
+    x = swap_add32(v[0], v[1]);
+    x = swap_add16(x, x);
+    x += dpp<kRor8>(x);
+  } else if constexpr (P == 4) {
+    x = swap_add16(swap_add32(v[0], v[2]), swap_add32(v[1], v[3]));
+    x += dpp<kRor8>(x);
+  } else {
+    const float a = swap_add16(swap_add32(v[0], v[4]), swap_add32(v[2], v[6]));
+    const float b = swap_add16(swap_add32(v[1], v[5]), swap_add32(v[3], v[7]));
+    const bool up = (lane & 8) != 0;
+    x = (up ? b : a) + dpp<kRor8>(up ? a : b);
+  }
+  x += __shfl_xor(x, 4, 64);
+  x += dpp<kXor2>(x);
+  return x + dpp<kXor1>(x);
+}
+
 // Per-row clip + noise of an LDS message of D columns (element V) into
 // row-major element-T rows; norm/cfac (nullable) receive ||v|| and the clip
 // factor.  16 lanes per row (4 rows per wavefront at a time), each lane on
 // the 4-column groups cg, cg + 16, ...; the noise is keyed by the row's
 // sample id, two groups' Philox blocks at a time (independent instruction
-// streams, so one lane keeps the VALU busy).
+// streams, so one lane keeps the VALU busy).  Run by nwaves wavefronts, this
+// one the wave-th of them.
 template <typename V>
 __device__ __forceinline__ void msg_ld4(const char* row, int g, int D, float (&x)[4]) {
   ld4<V>(row + 4 * g * (int)sizeof(V), x);
@@ -777,11 +822,11 @@ __device__ __forceinline__ void msg_st4(VFL_GLOBAL T* o, int g, int D, const flo
 template <typename T, typename V, int BR>
 __device__ __forceinline__ void msg_rows(const char* s, const LBuf& src, int D, const MsgOp& m,
                                          uint32_t step, int64_t sample0, void* out, int64_t ldo,
-                                         float* norm, float* cfac, int r0, int rv) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                         float* norm, float* cfac, int r0, int rv, int wave, int nwaves) {
+  const int lane = threadIdx.x & 63;
   const int sub = lane >> 4, cg = lane & 15;
   const int ngrp = (D + 3) >> 2;
-  for (int rb = 0; rb < BR; rb += 4 * kNW) {
+  for (int rb = 0; rb < BR; rb += 4 * nwaves) {
     const int r = rb + wave * 4 + sub;
     if (r >= rv) continue;   // uniform within the row's 16 lanes
     const char* row = s + src.off + r * src.pitch;
@@ -864,7 +909,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_fwd(const FwdJob* __r
   }
   if (j.publish)
     msg_rows<T, T, BR>(s, last.out, last.N, j.m, (uint32_t)k.group, k.row0, j.zhat, j.ldzh, j.norm,
-                       j.cfac, r0, rv);
+                       j.cfac, r0, rv, (int)(threadIdx.x >> 6), kNW);
 }
 
 template <typename T, int RT>
@@ -900,11 +945,40 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   }
   const int rv = min(BR, k.rows - r0);
   const int Hd = j.ft[H - 1].N;
-  const int din = j.in.n_cat * j.in.E + j.in.dense_in;
+  const int Hd4 = (Hd + 3) / 4 * 4;
+  float* yl = (float*)(s + j.red.off);        // the rows' labels
+  float* wpart = yl + BR;                     // logit weight gradient [kNW][Hd4]
+  float* wl = wpart + kNW * Hd4;              // {loss, dl} [kNW][2]
+  const bool gextra = j.gextra != 0;
+  // the message with clip or noise: by the copy wavefronts beside A's
+  // input-gradient chain, or by all of them where there is none
+  const bool msg_all = nda == 0 && !has_gx;
+  auto send_noised = [&](int w0, int nw) {
+    msg_rows<T, float, BR>(s, j.msg, j.dB, j.m, (uint32_t)k.group, k.row0, j.ring, j.ldring, nullptr, nullptr,
+                           r0, rv, wave - w0, nw);
+  };
   if (threadIdx.x >= kNT) {
+    const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
+    // B's embedding into cat[:, dA:dA+dB) with zeros up to the MFMA depth
+    // (published before this launch; A's last layer fills cat[:, 0:dA) and
+    // leaves these columns alone) and the labels, beside A's input
+    {
+      const int dA = j.dA, dB = j.dB;
+      const int nch = ((dA + dB + KS - 1) / KS * KS - dA) / CE;
+      const VFL_GLOBAL T* zb = glb((const T*)j.zb);
+      const VFL_GLOBAL float* y = glb(cc.labels) + k.in_off + r0;
+      const float py = y[min(tid, rv - 1)];
+      for (int u = tid; u < BR * nch; u += nt) {
+        const int r = u / nch, ch = u % nch, c = ch * CE;
+        u32x4 v = u32x4{0u, 0u, 0u, 0u};
+        if (r < rv && c < dB) v = mask_tail<T>(*(const VFL_GLOBAL u32x4*)(zb + (int64_t)(r0 + r) * j.ldzb + c), dB - c);
+        *(u32x4*)(s + j.cat.off + r * j.cat.pitch + (dA + c) * (int)sizeof(T)) = v;
+      }
+      if (tid < BR) yl[tid] = tid < rv ? py : 0.f;
+    }
     // the copy of each stage's output runs beside the next stage
     __syncthreads();
-    lds_to_rc<T, BR>(s, j.in.buf, din, j.in.rc, r0);
+    lds_to_rc<T, BR>(s, j.in.buf, j.in.n_cat * j.in.E + j.in.dense_in, j.in.rc, r0);
     for (int l = 0; l < LA; ++l) {
       __syncthreads();
       // (A's last layer writes cat, copied whole)
@@ -916,6 +990,14 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       lds_to_rc<T, BR>(s, j.ft[q].out, j.ft[q].N, j.ft[q].rc, r0, j.ft[q].mask_out);
     }
     __syncthreads();
+    // the logit stage's sums over the product wavefronts, in order
+    VFL_GLOBAL float* part = glb(j.part) + (int64_t)blockIdx.x * (Hd + 2);
+    for (int c = tid; c < Hd + 2; c += nt) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < kNW; ++w) t += c < 2 ? wl[2 * w + c] : wpart[w * Hd4 + c - 2];
+      part[c] = t;
+    }
     lds_to_rc<T, BR>(s, j.dh, Hd, j.dh_rc, r0);
     for (int q = 0; q + 1 < H; ++q) {
       __syncthreads();
@@ -923,21 +1005,20 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     }
     __syncthreads();
     lds_to_rc<T, BR>(s, j.dc.out, j.dA, j.dc.rc, r0);
+    if (gextra) send_noised(msg_all ? 0 : kNW, (int)(blockDim.x >> 6) - (msg_all ? 0 : kNW));
+    else lds_to_rows<T, BR, true>(s, j.msg, j.dB, j.ring, j.ldring, r0, rv);
     for (int q = 0; q < nda; ++q) {
       __syncthreads();
       lds_to_rc<T, BR>(s, j.da[q].out, j.da[q].N, j.da[q].rc, r0);
     }
     return;
   }
-  // the labels (to LDS with the inputs) and the logit weights of the lane's
-  // columns in the logit stage (columns 256 i + 4 lane .. +4, kept in
-  // registers); loads clamped, so all are unconditional
-  float* yl = (float*)(s + j.red.off);
-  float py;
+  // the logit weights of the lane's columns in the logit stage (columns
+  // 256 i + 4 lane .. +4, kept in registers); loads clamped, so all are
+  // unconditional
   float lwr[kLogitChunks][4];
   {
     const VFL_GLOBAL float* lw = glb(j.lw);
-    const VFL_GLOBAL float* y = glb(cc.labels) + k.in_off + r0;
 #pragma unroll
     for (int i = 0; i < kLogitChunks; ++i)
 #pragma unroll
@@ -946,7 +1027,6 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
         const float v = lw[min(c, Hd - 1)];
         lwr[i][e] = c < Hd ? v : 0.f;
       }
-    py = y[min((int)threadIdx.x, rv - 1)];
   }
   const float lbias = glb(j.lb)[0];
   Pipe pp;
@@ -954,22 +1034,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   const uint32_t wx = warm_l2(j.warm, jp);
   copy_bias(s, j.bt);
 
-  // A's bottom input, and B's embedding into cat[:, dA:dA+dB) with zeros up
-  // to the MFMA depth (published before this launch; A's last layer fills
-  // cat[:, 0:dA) and leaves these columns alone)
   load_input<T, BR>(s, j.in, cc, k, r0, rv);
-  if ((int)threadIdx.x < BR) yl[threadIdx.x] = (int)threadIdx.x < rv ? py : 0.f;
-  {
-    const int dA = j.dA, dB = j.dB;
-    const int nch = ((dA + dB + KS - 1) / KS * KS - dA) / CE;
-    const VFL_GLOBAL T* zb = glb((const T*)j.zb);
-    for (int u = threadIdx.x; u < BR * nch; u += kNT) {
-      const int r = u / nch, ch = u % nch, c = ch * CE;
-      u32x4 v = u32x4{0u, 0u, 0u, 0u};
-      if (r < rv && c < dB) v = mask_tail<T>(*(const VFL_GLOBAL u32x4*)(zb + (int64_t)(r0 + r) * j.ldzb + c), dB - c);
-      *(u32x4*)(s + j.cat.off + r * j.cat.pitch + (dA + c) * (int)sizeof(T)) = v;
-    }
-  }
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
   for (int l = 0; l < LA; ++l) {
@@ -982,26 +1047,23 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     __syncthreads();
   }
   // logit + BCE (Eq. 1), dl = sigmoid(l) - y, or for regression the
-  // squared error and dl = 2 (l - y): a wavefront per row (its
-  // BR / 8 rows one after the other), lane on the columns 256 i + 4 lane
-  // .. +4; the last hidden delta dl * w (ReLU-masked) goes to LDS.  The
-  // logit layer's weight gradient sum_r dl_r h[r][c], the loss and dl
-  // accumulate per wavefront in registers and are then summed over the
-  // wavefronts in order.  The loss only reports progress: its exp and log
-  // are the hardware's.
+  // squared error and dl = 2 (l - y): a wavefront takes BR / 8 rows, lane on
+  // the columns 256 i + 4 lane .. +4; the last hidden delta dl * w
+  // (ReLU-masked) goes to LDS.  The logit layer's weight gradient
+  // sum_r dl_r h[r][c], the loss and dl accumulate per wavefront in
+  // registers and are then summed over the wavefronts in order (by the
+  // copy wavefronts, beside the next stage).  The loss only reports
+  // progress: its exp and log are the hardware's.
   {
     const LBuf Hb = j.ft[H - 1].out, Db = j.dh;
-    constexpr int KS = Ch<T>::KS, RW = BR / kNW;
+    constexpr int RW = BR / kNW;                // rows per wavefront: 2, 4, 6, 8
+    constexpr int P = RW > 4 ? 8 : RW, LP = RW > 4 ? 3 : RW / 2;   // up to a power of two, its log
     const int Hw = (Hd + KS - 1) / KS * KS;     // LDS width of h and dh
-    const int Hd4 = (Hd + 3) / 4 * 4;
-    float* wpart = yl + BR;                     // [kNW][Hd4]
-    float* wl = wpart + kNW * Hd4;              // [kNW][2]
     float g[kLogitChunks][4];
 #pragma unroll
     for (int i = 0; i < kLogitChunks; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) g[i][e] = 0.f;
-    float lsum = 0.f, dsum = 0.f;
     const bool relu_h = j.relu_h != 0;
     auto load_h = [&](int r, float (&h)[kLogitChunks][4]) {
 #pragma unroll
@@ -1015,72 +1077,59 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       }
     };
     // the logits of the wavefront's rows: partial dots first, then their
-    // wavefront reductions side by side (independent shuffle chains)
-    float dots[RW];
+    // sums over the lanes with the rows dealt out on the way (each step
+    // halves the rows a lane holds): lane l ends with the logit of row
+    // l >> (6 - LP), where a butterfly per row took six shuffles each, and
+    // the loss chain below runs once for all rows instead of once per row
+    float v[P];
 #pragma unroll
-    for (int rr = 0; rr < RW; ++rr) {
+    for (int rr = 0; rr < P; ++rr) {
+      v[rr] = 0.f;
+      if (rr >= RW) continue;
       float h[kLogitChunks][4];
       load_h(wave * RW + rr, h);
-      float dot = 0.f;
 #pragma unroll
       for (int i = 0; i < kLogitChunks; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dot += h[i][e] * lwr[i][e];
-      dots[rr] = dot;
+        for (int e = 0; e < 4; ++e) v[rr] += h[i][e] * lwr[i][e];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int rr = 0; rr < RW; ++rr) dots[rr] += __shfl_xor(dots[rr], o, 64);
-    // the loss terms and dl of every row first: their exp / reciprocal /
-    // log chains are independent, while the stage below alternates LDS
-    // reads and writes the compiler must keep in order (they may alias)
-    float dls[RW];
+    const float dot = rows_reduce<P>(v, lane);
+    // this lane's row: the loss term and dl
+    const int lr = lane >> (6 - LP), r = wave * RW + lr;
+    const bool ok = lr < RW && r < rv;
+    const float l = dot + lbias, yy = yl[min(r, BR - 1)];
+    float lt, dl;
     if (cst(j).mse) {
-      // regression: squared error (l - y)^2, dl = 2 (l - y)
-#pragma unroll
-      for (int rr = 0; rr < RW; ++rr) {
-        const int r = wave * RW + rr;
-        const bool ok = r < rv;
-        const float e = dots[rr] + lbias - yl[r];
-        const float dl = ok ? 2.f * e : 0.f;
-        if (ok) lsum += e * e;
-        dsum += dl;
-        dls[rr] = dl;
-      }
+      const float e = l - yy;
+      lt = e * e;
+      dl = 2.f * e;
     } else {
-#pragma unroll
-      for (int rr = 0; rr < RW; ++rr) {
-        const int r = wave * RW + rr;
-        const bool ok = r < rv;
-        const float l = dots[rr] + lbias;
-        const float yy = yl[r];
-        const float ex = __expf(-fabsf(l));
-        const float inv = __frcp_rn(1.f + ex);
-        const float sig = l >= 0.f ? inv : ex * inv;
-        const float dl = ok ? sig - yy : 0.f;
-        if (ok) lsum += fmaxf(l, 0.f) - yy * l + __logf(1.f + ex);
-        dsum += dl;
-        dls[rr] = dl;
-      }
+      const float ex = __expf(-fabsf(l));
+      const float inv = __frcp_rn(1.f + ex);
+      lt = fmaxf(l, 0.f) - yy * l + __logf(1.f + ex);
+      dl = (l >= 0.f ? inv : ex * inv) - yy;
     }
+    lt = ok ? lt : 0.f;
+    dl = ok ? dl : 0.f;
+    float lsum = 0.f, dsum = 0.f;
 #pragma unroll
     for (int rr = 0; rr < RW; ++rr) {
-      const int r = wave * RW + rr;
-      const float dl = dls[rr];
+      const float dr = lane_value(dl, rr << (6 - LP));
+      lsum += lane_value(lt, rr << (6 - LP));
+      dsum += dr;
       float h[kLogitChunks][4];
-      load_h(r, h);
+      load_h(wave * RW + rr, h);
 #pragma unroll
       for (int i = 0; i < kLogitChunks; ++i) {
         const int c0 = 256 * i + 4 * lane;
         float d[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          d[e] = dl * lwr[i][e];
+          d[e] = dr * lwr[i][e];
           if (relu_h && !(h[i][e] > 0.f)) d[e] = 0.f;
-          g[i][e] += dl * h[i][e];
+          g[i][e] += dr * h[i][e];
         }
-        if (c0 < Hw) st4<T>(lp(s, Db, r, c0 * (int)sizeof(T)), d);
+        if (c0 < Hw) st4<T>(lp(s, Db, wave * RW + rr, c0 * (int)sizeof(T)), d);
       }
     }
 #pragma unroll
@@ -1093,18 +1142,6 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       wl[2 * wave + 1] = dsum;
     }
     __syncthreads();
-    VFL_GLOBAL float* part = glb(j.part) + (int64_t)blockIdx.x * (Hd + 2);
-    for (int c = threadIdx.x; c < Hd + 2; c += kNT) {
-      float t = 0.f;
-      if (c < 2) {
-#pragma unroll
-        for (int w = 0; w < kNW; ++w) t += wl[2 * w + c];
-      } else {
-#pragma unroll
-        for (int w = 0; w < kNW; ++w) t += wpart[w * Hd4 + c - 2];
-      }
-      part[c] = t;
-    }
   }
   // top input-gradient chain
   for (int q = 0; q + 1 < H; ++q) {
@@ -1116,9 +1153,8 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     const int dA = j.dA, dAB = j.dA + j.dB;
     const int dApad = (dA + KS - 1) / KS * KS;
     const LBuf ob = j.dc.out, mk = j.dc.mask, msg = j.msg;
-    const bool maskA = mk.pitch > 0, gextra = j.gextra != 0;
-    VFL_GLOBAL T* ring = glb((T*)j.ring);
-    const int64_t ldr = j.ldring;
+    const bool maskA = mk.pitch > 0;
+    const int msg_end = dA + (j.dB + CE - 1) / CE * CE;   // the message's columns in whole chunks
     block_mm<T, RT>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
                     [&](int r, int n, const f32x4& a, const f32x4&) {
       const bool ok = r < rv;
@@ -1131,21 +1167,22 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
         st4<T>(lp(s, ob, r, n * (int)sizeof(T)), v);
         return;
       }
+      // the message to LDS (float32 when clip or noise follow), where the
+      // copy wavefronts take it from
+      float v[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = n + i;
-        const float x = ok ? a[i] : 0.f;
-        if (c < dApad) st1<T>((T*)lp(s, ob, r, 0) + c, 0.f);
-        if (c < dAB) {
-          if (gextra) ((float*)lp(s, msg, r, 0))[c - dA] = x;
-          else if (ok) st1<T>((T*)(ring + (int64_t)(r0 + r) * ldr + (c - dA)), x);
-        }
+      for (int i = 0; i < 4; ++i) v[i] = ok && n + i < dAB ? a[i] : 0.f;
+      if (n < dApad) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st1<T>((T*)lp(s, ob, r, 0) + n + i, 0.f);
+      }
+      if (n < msg_end) {
+        if (gextra) st4<float>(lp(s, msg, r, (n - dA) * 4), v);
+        else st4<T>(lp(s, msg, r, (n - dA) * (int)sizeof(T)), v);
       }
     });
     __syncthreads();
-    if (gextra)
-      msg_rows<T, float, BR>(s, msg, j.dB, j.m, (uint32_t)k.group, k.row0, j.ring, j.ldring, nullptr,
-                             nullptr, r0, rv);
+    if (gextra && msg_all) send_noised(0, (int)(blockDim.x >> 6));
   }
   // A's input-gradient chain
   for (int q = 0; q < nda; ++q) {
