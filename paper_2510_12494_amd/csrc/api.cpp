@@ -161,7 +161,6 @@ struct DwMeta { int tile = 64, splits = 1, rps = 0, blocks = 0, red_blocks = 0, 
 struct Plan {
   Elt e = F32;
   int s = 0, k = 1, B = 1, R = 1, Ra = 64, dA = 0, dB = 0;
-  bool dw32 = false;                  // unsplit 32 x 32 weight gradients
   Party A, P;                         // P: party B (passive)
   Top T;
   size_t cat_rc = 0;
@@ -332,8 +331,18 @@ int dw_tiles(int N, int K, int tile = 64) {
 constexpr double kDwtMinFlops = 4e9;
 
 // Groups whose RC operand columns hold at most this many bytes (rows times
-// element size) contract all their rows in one block per 32 x 32 tile.
-constexpr int kDwUnsplitBytes = 2048;
+// element size) contract all their rows in one block per 32 x 32 tile
+// (k_dw32: one launch, no partials), if the tiles' operand reads stay below
+// kDwUnsplitReads.  A block reads its 64 columns through one CU, so past
+// about 4096 bf16 rows the row chunks of k_dw + k_dw_reduce are faster, and
+// many wide tiles are bound by the L2 (us per tick, split / unsplit; bf16
+// 64-256-128 at 2048, 4096, 6144 rows: 41.3 / 34.7, 43.6 / 41.7, 51.5 /
+// 57.6; float32 at 1024, 2048, 4096 rows: 57.4 / 50.7, 60.9 / 58.8, 70.2 /
+// 86.7; 500-1024-512-128 at 2048 and 4096 rows, 285 and 570 MB of reads:
+// 110 / 101, 122.5 / 123.6).
+constexpr int kDwUnsplitBytes = 8192;
+constexpr int64_t kDwUnsplitReads = 320 << 20;   // bytes, two 32-column operands per tile
+constexpr int kDw32Steps = 16;        // MFMA row steps the RC rows are rounded up to there (k_dw32)
 
 // Chunks of at least this many rows may be cut at any 32-row stage.
 constexpr int kDwtFineRows = 1024;
@@ -505,12 +514,12 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   p.k = o->replicas;
   p.B = o->batch;
   p.R = o->batch * o->replicas;
-  // weight-gradient launch shapes (they fix the RC row count Ra): small
-  // groups take the unsplit 32 x 32 weight gradient, whose four wavefronts
-  // run two groups of four row steps per iteration over rows rounded up to
-  // 1024; larger ones row chunks of rps rows (a multiple of two load
-  // groups) over 64 x 64 tiles.  Every block contracts whole chunks: the
-  // rows past the group are zero deltas.
+  // weight-gradient launch shapes of each party (they fix the RC row count
+  // Ra): the unsplit 32 x 32 weight gradient, whose wavefronts cover the
+  // rows rounded up to 16 MFMA steps, or row chunks of rps rows (a multiple
+  // of two load groups) over 64 x 64 or 256 x 256 tiles.  Every block
+  // contracts whole steps or chunks: the rows past the group are zero
+  // deltas.
   {
     auto bottom_tiles = [&](const vfl_bottom_spec* sp, int tile) {
       int in = sp->n_cat * sp->emb_dim + sp->dense_in, n = 0;
@@ -522,35 +531,37 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
       for (int j = 0; j + 1 < t->n_layers; ++j) { n += dw_tiles(t->widths[j], in, tile); in = t->widths[j]; }
       return n;
     };
-    const int Ra128 = (p.R + 127) / 128 * 128;
-    p.dw32 = (int64_t)Ra128 * elt_size(p.e) <= kDwUnsplitBytes;
-    if (p.dw32) {
-      p.Ra = (p.R + 1023) / 1024 * 1024;
-      p.da.blocks = bottom_tiles(a, 32) + top_tiles(32);
-      p.db.blocks = bottom_tiles(b, 32);
-      for (DwMeta* m : {&p.da, &p.db}) { m->tile = 32; m->splits = 1; m->rps = p.Ra; }
-    } else {
-      // MACs per row of each party's weight gradients
-      auto bottom_macs = [&](const vfl_bottom_spec* sp) {
-        double in = sp->n_cat * sp->emb_dim + sp->dense_in, n = 0;
-        for (int l = 0; l < sp->n_layers; ++l) { n += in * sp->widths[l]; in = sp->widths[l]; }
-        return n;
-      };
-      double top_macs = 0;
-      {
-        double in = a->widths[a->n_layers - 1] + b->widths[b->n_layers - 1];
-        for (int j = 0; j + 1 < t->n_layers; ++j) { top_macs += in * t->widths[j]; in = t->widths[j]; }
-      }
-      const bool bf = dtype == VFL_BF16;
-      p.da.tile = bf && 2.0 * p.R * (bottom_macs(a) + top_macs) >= kDwtMinFlops ? 256 : 64;
-      p.db.tile = bf && 2.0 * p.R * bottom_macs(b) >= kDwtMinFlops ? 256 : 64;
-      const int ta = bottom_tiles(a, p.da.tile) + top_tiles(p.da.tile), tb = bottom_tiles(b, p.db.tile);
-      dw_split(p.R, ta, bf, p.da);
-      dw_split(p.R, tb, bf, p.db);
-      p.da.blocks = ta * p.da.splits;
-      p.db.blocks = tb * p.db.splits;
-      p.Ra = std::max(p.da.splits * p.da.rps, p.db.splits * p.db.rps);
+    // MACs per row of each party's weight gradients
+    auto bottom_macs = [&](const vfl_bottom_spec* sp) {
+      double in = sp->n_cat * sp->emb_dim + sp->dense_in, n = 0;
+      for (int l = 0; l < sp->n_layers; ++l) { n += in * sp->widths[l]; in = sp->widths[l]; }
+      return n;
+    };
+    double top_macs = 0;
+    {
+      double in = a->widths[a->n_layers - 1] + b->widths[b->n_layers - 1];
+      for (int j = 0; j + 1 < t->n_layers; ++j) { top_macs += in * t->widths[j]; in = t->widths[j]; }
     }
+    const bool bf = dtype == VFL_BF16;
+    const int es = elt_size(p.e), gran = kDw32Steps * 64 / es;
+    auto shape = [&](DwMeta& m, int tiles32, double macs, auto&& tiles_of) {
+      const int64_t col_bytes = (int64_t)p.R * es;
+      if (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads) {
+        m.tile = 32;
+        m.splits = 1;
+        m.rps = (p.R + gran - 1) / gran * gran;
+        m.blocks = tiles32;
+      } else {
+        m.tile = bf && 2.0 * p.R * macs >= kDwtMinFlops ? 256 : 64;
+        const int tiles = tiles_of(m.tile);
+        dw_split(p.R, tiles, bf, m);
+        m.blocks = tiles * m.splits;
+      }
+    };
+    shape(p.da, bottom_tiles(a, 32) + top_tiles(32), bottom_macs(a) + top_macs,
+          [&](int tile) { return bottom_tiles(a, tile) + top_tiles(tile); });
+    shape(p.db, bottom_tiles(b, 32), bottom_macs(b), [&](int tile) { return bottom_tiles(b, tile); });
+    p.Ra = std::max(p.da.splits * p.da.rps, p.db.splits * p.db.rps);
   }
   const int es = elt_size(p.e);
   const int64_t R = p.R, Ra = p.Ra;
@@ -1024,7 +1035,6 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
   for (int l = 0; l < A.L; ++l)
     add(dwa, p.da, A.drc[l], l == 0 ? A.x0rc[0] : A.arc[0][l - 1], A.out[l], A.in[l], A.W[l], A.b[l],
         A.Wq[0][l], A.kq[l], A.Wtq[0][l], A.kt[l], A.part[l], A.partb[l]);
-  dwa.rows_pad = p.Ra;
   dwa.red_blocks = p.da.red_blocks;
   dwa.lpart = at_f(T.logit_part);
   dwa.Hd = T.out[T.H - 1];
@@ -1036,7 +1046,6 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     for (int l = 0; l < P.L; ++l)
       add(J, p.db, P.drc[l], l == 0 ? P.x0rc[q] : P.arc[q][l - 1], P.out[l], P.in[l], P.W[l], P.b[l],
           P.Wq[q][l], P.kq[l], P.Wtq[q][l], P.kt[l], P.part[l], P.partb[l]);
-    J.rows_pad = p.Ra;
     J.red_blocks = p.db.red_blocks;
   }
   if (dwa.blocks != p.da.blocks || dwb[0].blocks != p.db.blocks)

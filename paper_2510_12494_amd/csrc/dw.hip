@@ -455,8 +455,8 @@ __global__ __launch_bounds__(256) void k_dwt(const DwJob* __restrict__ jp) {
 __device__ __forceinline__ void logit_reduce(const DwJob& J, int lb, int R, float scale, float* loss_out) {
   __shared__ float red[64][5];
   const int W = J.Hd + 2;
-  const int cl = threadIdx.x & 3, sl = threadIdx.x >> 2;
-  const int c = lb * 4 + cl;
+  const int cl = threadIdx.x & 3, sl = threadIdx.x >> 2;   // threads past 256 only meet the barrier
+  const int c = sl < 64 ? lb * 4 + cl : W;
   const int rows = (R + J.lrows - 1) / J.lrows;
   const VFL_GLOBAL float* lp = glb(J.lpart);
   float acc = 0.f;
@@ -469,7 +469,7 @@ __device__ __forceinline__ void logit_reduce(const DwJob& J, int lb, int R, floa
     }
     for (; b < rows; b += 64) acc += lp[(int64_t)b * W + c];
   }
-  red[sl][cl] = acc;
+  if (sl < 64) red[sl][cl] = acc;
   __syncthreads();
   if (sl == 0 && c < W) {
     float tot = 0.f;
@@ -485,19 +485,27 @@ __device__ __forceinline__ void logit_reduce(const DwJob& J, int lb, int R, floa
 }
 
 // Unsplit weight gradient over 32 x 32 output tiles, for groups small
-// enough that one block can contract all their rows: the block's four
-// wavefronts take interleaved MFMA row steps (wavefront w: steps w, w + 4,
-// ...) and accumulate the whole tile each; the four sums meet in LDS and
-// are added in wavefront order; the SGD of the tile's master weights (and
-// bias, for the tiles of the first 32 inputs) and the operand-copy refresh
-// follow in the same block, so no reduction launch is needed.  Blocks past
-// the tiles reduce the logit layer's partials.
-template <typename T>
-__global__ __launch_bounds__(256) void k_dw32(const DwJob* __restrict__ jp, int Rarg, float scale_arg,
-                                              float* loss_out, TickRef tr, float* loss_base) {
-  constexpr int RR = 16 / (int)sizeof(T);   // rows per chunk
-  constexpr int KR = 4 * RR;                // rows per MFMA step
-  constexpr int PF = 4;                     // MFMA steps per load group
+// enough that one block can contract all their rows: the block's W
+// wavefronts take interleaved MFMA row steps (wavefront w: steps w, w + W,
+// ...) and accumulate the whole tile each; the W sums meet in LDS and are
+// added in wavefront order; the SGD of the tile's master weights (and bias,
+// for the tiles of the first 32 inputs) follows in the same block, and the
+// new values go through LDS so that both packed operand copies are written
+// as whole 16-byte chunks.  No reduction launch and no partials in memory.
+// Blocks past the tiles reduce the logit layer's partials.
+// The row steps of a block are a chain of L2 reads (R * 64 columns through
+// one CU), so few tiles take 16 wavefronts, which read 16 steps at a time;
+// many tiles (more than kDwuTiles) fill the CUs with 4 each.  Against the row
+// chunks with their reduction launch: 4096 rows of 64-256-128 + 256-256,
+// 19 + 15 -> 25 us for both parties on one stream.
+constexpr int kDwuTiles = 384;
+
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W, 4) void k_dw32(const DwJob* __restrict__ jp, int Rarg, float scale_arg,
+                                                        float* loss_out, TickRef tr, float* loss_base) {
+  constexpr int CE = 16 / (int)sizeof(T);   // elements per chunk = rows per RC chunk
+  constexpr int KR = 4 * CE;                // rows per MFMA step
+  constexpr int NT = 64 * W;
   const DwJob& J = *jp;
   int R = Rarg;
   float scale = scale_arg;
@@ -519,7 +527,7 @@ __global__ __launch_bounds__(256) void k_dw32(const DwJob* __restrict__ jp, int 
   const int tiles_k = (K + 31) / 32;
   const int lb = blockIdx.x - P.first_block;
   const int n0 = (lb / tiles_k) * 32, k0 = (lb % tiles_k) * 32;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int kc = lane >> 4, lr = lane & 15;
   const bool do_bias = k0 == 0;
 
@@ -530,24 +538,18 @@ __global__ __launch_bounds__(256) void k_dw32(const DwJob* __restrict__ jp, int 
     dcol[i] = glb((const char*)P.D.p) + (int64_t)min(n0 + 16 * i + lr, N - 1) * 16;
     xcol[i] = glb((const char*)P.X.p) + (int64_t)min(k0 + 16 * i + lr, K - 1) * 16;
   }
-  const int64_t dcp = P.D.cp, xcp = P.X.cp;
-  // every wavefront takes the same number of row steps, covering all the
-  // RC rows (a multiple of 1024; the delta rows past the group are zero):
-  // an even number of load groups, no step conditional
-  const int nsw = J.rows_pad / KR / 4;                      // steps per wavefront
-  const int ngr = nsw / PF;                                 // load groups
-  // loads of group g (past the last group they repeat its last step:
-  // unconditional, never used)
-  auto load = [&](int g, u32x4 (&df)[PF][2], u32x4 (&xf)[PF][2]) {
+  const int64_t dcp = (int64_t)P.D.cp * 16, xcp = (int64_t)P.X.cp * 16;
+  // every wavefront takes the same number of row steps, covering the
+  // group's rows (the RC rows are a multiple of 16 steps, and the delta
+  // rows past the group are zero); loads past the last step repeat it
+  const int nst = ((R + KR - 1) / KR + W - 1) / W;
+  struct Step { u32x4 d[2], x[2]; };
+  auto load = [&](int i, Step& f) {
+    const int64_t rg = (int64_t)(wave + W * min(i, nst - 1)) * (KR / CE) + kc;
 #pragma unroll
-    for (int st = 0; st < PF; ++st) {
-      const int sw = min(g * PF + st, nsw - 1);
-      const int64_t rg = (int64_t)(wave + 4 * sw) * (KR / RR) + kc;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        df[st][i] = *(const VFL_GLOBAL u32x4*)(dcol[i] + rg * dcp * 16);
-        xf[st][i] = *(const VFL_GLOBAL u32x4*)(xcol[i] + rg * xcp * 16);
-      }
+    for (int h = 0; h < 2; ++h) {
+      f.d[h] = *(const VFL_GLOBAL u32x4*)(dcol[h] + rg * dcp);
+      f.x[h] = *(const VFL_GLOBAL u32x4*)(xcol[h] + rg * xcp);
     }
   };
   f32x4 acc[2][2];
@@ -556,73 +558,66 @@ __global__ __launch_bounds__(256) void k_dw32(const DwJob* __restrict__ jp, int 
 #pragma unroll
     for (int jn = 0; jn < 2; ++jn) acc[i][jn] = f32x4{0.f, 0.f, 0.f, 0.f};
   float bsum[2] = {0.f, 0.f};
-  auto group = [&](const u32x4 (&df)[PF][2], const u32x4 (&xf)[PF][2]) {
+  auto mma = [&](const Step& f) {
 #pragma unroll
-    for (int st = 0; st < PF; ++st) {
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int jn = 0; jn < 2; ++jn) {
+        if constexpr (sizeof(T) == 2) {
+          acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, f.x[i]), __builtin_bit_cast(bf16x8, f.d[jn]), acc[i][jn], 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int jn = 0; jn < 2; ++jn) {
+          for (int e = 0; e < 4; ++e)
+            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                __uint_as_float(f.x[i][e]), __uint_as_float(f.d[jn][e]), acc[i][jn], 0, 0, 0);
+        }
+      }
+    if (do_bias) {
+#pragma unroll
+      for (int jn = 0; jn < 2; ++jn)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
           if constexpr (sizeof(T) == 2) {
-            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, xf[st][i]), __builtin_bit_cast(bf16x8, df[st][jn]), acc[i][jn], 0, 0, 0);
+            bsum[jn] += __uint_as_float(f.d[jn][e] << 16) + __uint_as_float(f.d[jn][e] & 0xffff0000u);
           } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                  __uint_as_float(xf[st][i][e]), __uint_as_float(df[st][jn][e]), acc[i][jn], 0, 0, 0);
+            bsum[jn] += __uint_as_float(f.d[jn][e]);
           }
         }
-      }
-      if (do_bias) {
-#pragma unroll
-        for (int jn = 0; jn < 2; ++jn) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if constexpr (sizeof(T) == 2) {
-              bsum[jn] += __uint_as_float(df[st][jn][e] << 16) + __uint_as_float(df[st][jn][e] & 0xffff0000u);
-            } else {
-              bsum[jn] += __uint_as_float(df[st][jn][e]);
-            }
-          }
-        }
-      }
     }
   };
-  // two groups in flight at the top of every iteration (A: group g, B:
-  // group g + 1); each is refilled as soon as its MFMAs have read it
-  // (the first iteration is peeled, so that the loop is entered with the
-  // loads in flight exactly as at its back edge: the compiler's wait
-  // counts stay exact)
-  u32x4 dA[PF][2], xA[PF][2], dB[PF][2], xB[PF][2];
-  load(0, dA, xA);
-  load(1, dB, xB);
-  group(dA, xA);
-  load(2, dA, xA);
-  group(dB, xB);
-  load(3, dB, xB);
+  // two steps in flight at the top of every iteration, each refilled as
+  // soon as its products have read it; the loads are unconditional
+  Step fa, fb;
+  load(0, fa);
+  load(1, fb);
 #pragma unroll 1
-  for (int g = 2; g < ngr; g += 2) {
-    group(dA, xA);
-    load(g + 2, dA, xA);
-    group(dB, xB);
-    load(g + 3, dB, xB);
+  for (int i = 0; i + 1 < nst; i += 2) {
+    mma(fa);
+    load(i + 2, fa);
+    mma(fb);
+    load(i + 3, fb);
   }
+  if (nst & 1) mma(fa);
 
-  // the SGD operands (their loads overlap the LDS reduction): thread t
-  // updates W[n0 + t / 8][k0 + 4 (t % 8) .. +4] and, t < 32, bias[n0 + t]
-  const int tn = threadIdx.x >> 3, tk = 4 * (threadIdx.x & 7);
-  float w[4];
-  sgd_load4<T>(P, n0 + tn, k0 + tk, w);
-  const float b0 = glb(P.bias)[min(n0 + (int)(threadIdx.x & 31), N - 1)];
-  // the wavefronts' tiles, added in wavefront order (rows padded to 9
-  // float4: the 16 lanes of a column group hit distinct banks)
-  __shared__ f32x4 red[4][32][9];
-  __shared__ float rb[4][32];
+  // the SGD operands (their loads overlap the LDS reduction): thread t takes
+  // the elements i = t, t + NT, ... of the tile, W[n0 + i / 32][k0 + i % 32],
+  // and, t < 32, bias[n0 + t]
+  constexpr int EPT = 1024 / NT;
+  float w[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int i = t + e * NT;
+    w[e] = glb(P.W)[(int64_t)min(n0 + (i >> 5), N - 1) * K + min(k0 + (i & 31), K - 1)];
+  }
+  const float b0 = glb(P.bias)[min(n0 + (t & 31), N - 1)];
+  // the wavefronts' tiles, added in wavefront order (rows padded by 4 floats)
+  __shared__ __attribute__((aligned(16))) float red[W][32][36];
+  __shared__ float rb[W][32];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int jn = 0; jn < 2; ++jn) red[wave][16 * jn + lr][4 * i + kc] = acc[i][jn];
+    for (int jn = 0; jn < 2; ++jn) *(f32x4*)&red[wave][16 * jn + lr][16 * i + 4 * kc] = acc[i][jn];
   if (do_bias) {
 #pragma unroll
     for (int jn = 0; jn < 2; ++jn) {
@@ -635,12 +630,56 @@ __global__ __launch_bounds__(256) void k_dw32(const DwJob* __restrict__ jp, int 
     }
   }
   __syncthreads();
-  const f32x4 g = ((red[0][tn][tk / 4] + red[1][tn][tk / 4]) + red[2][tn][tk / 4]) + red[3][tn][tk / 4];
-  sgd_store4<T>(P, n0 + tn, k0 + tk, w, g, scale);
-  if (do_bias && threadIdx.x < 32) {
-    const int n = n0 + threadIdx.x;
-    const float gb = ((rb[0][threadIdx.x] + rb[1][threadIdx.x]) + rb[2][threadIdx.x]) + rb[3][threadIdx.x];
-    if (n < N) glb(P.bias)[n] = b0 - scale * gb;
+  float v[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int i = t + e * NT, nr = i >> 5, kk = i & 31;
+    float g = red[0][nr][kk];
+#pragma unroll
+    for (int u = 1; u < W; ++u) g += red[u][nr][kk];
+    v[e] = n0 + nr < N && k0 + kk < K ? w[e] - scale * g : 0.f;
+    if (n0 + nr < N && k0 + kk < K) glb(P.W)[(int64_t)(n0 + nr) * K + k0 + kk] = v[e];
+  }
+  if (do_bias && t < 32 && n0 + t < N) {
+    float gb = rb[0][t];
+#pragma unroll
+    for (int u = 1; u < W; ++u) gb += rb[u][t];
+    glb(P.bias)[n0 + t] = b0 - scale * gb;
+  }
+  __syncthreads();
+  // the new values (zero past N and K) in the element type, over the sums
+  constexpr int kPitch = 32 + CE;             // elements per row
+  T* tile = (T*)&red[0][0][0];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int i = t + e * NT;
+    st1<T>(&tile[(i >> 5) * kPitch + (i & 31)], v[e]);
+  }
+  __syncthreads();
+  constexpr int CPR = 32 / CE;                // chunks per row or column of the tile
+  for (int i = t; i < 2 * 32 * CPR; i += NT) {
+    const int c = CE * (i % CPR);
+    if (i < 32 * CPR) {
+      // inputs k0 + c .. of output n0 + i / CPR
+      const int nr = i / CPR;
+      if (P.Wq && n0 + nr < (N + 15) / 16 * 16 && k0 + c < P.kq * KR)
+        *(VFL_GLOBAL u32x4*)(glb((T*)P.Wq) + pk_index<T>(n0 + nr, k0 + c, P.kq)) = *(const u32x4*)&tile[nr * kPitch + c];
+    } else {
+      // outputs n0 + c .. of input k0 + kk
+      const int kk = i / CPR - 32;
+      if (P.Wtq && k0 + kk < (K + 15) / 16 * 16 && n0 + c < P.kt * KR) {
+        u32x4 x;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if constexpr (sizeof(T) == 4) {
+            x[u] = __float_as_uint(tile[(c + u) * kPitch + kk]);
+          } else {
+            x[u] = (uint32_t)tile[(c + 2 * u) * kPitch + kk] | ((uint32_t)tile[(c + 2 * u + 1) * kPitch + kk] << 16);
+          }
+        }
+        *(VFL_GLOBAL u32x4*)(glb((T*)P.Wtq) + pk_index<T>(k0 + kk, n0 + c, P.kt)) = x;
+      }
+    }
   }
 }
 
@@ -817,10 +856,14 @@ hipError_t launch_dwt(const DwJob* job, int blocks, hipStream_t st) {
 hipError_t launch_dw32(Elt e, const DwJob* job, int blocks, int R, float scale, float* loss_out,
                       TickRef tr, float* loss_base, hipStream_t st) {
   if (blocks < 1) return hipErrorInvalidValue;
-  if (e == BF16)
-    hipLaunchKernelGGL(k_dw32<uint16_t>, dim3(blocks), dim3(256), 0, st, job, R, scale, loss_out, tr, loss_base);
-  else
-    hipLaunchKernelGGL(k_dw32<float>, dim3(blocks), dim3(256), 0, st, job, R, scale, loss_out, tr, loss_base);
+#define VFL_DW32(T, W) \
+  hipLaunchKernelGGL((k_dw32<T, W>), dim3(blocks), dim3(64 * W), 0, st, job, R, scale, loss_out, tr, loss_base)
+  const bool wide = blocks <= kDwuTiles;
+  if (e == BF16 && wide) VFL_DW32(uint16_t, 16);
+  else if (e == BF16) VFL_DW32(uint16_t, 4);
+  else if (wide) VFL_DW32(float, 16);
+  else VFL_DW32(float, 4);
+#undef VFL_DW32
   return hipGetLastError();
 }
 

@@ -325,7 +325,6 @@ struct DwJob {
   // rows of Hd + 2 floats, of which the first ceil(rows / lrows) are the
   // group's)
   int32_t red_blocks = 0;
-  int32_t rows_pad = 0;               // RC rows (k_dw32: its row steps cover them all)
   float* lpart = nullptr; int32_t Hd = 0, lrows = 0;
   float* lw = nullptr; float* lb = nullptr;
 };
