@@ -6,32 +6,36 @@
 // for every touched table row, the gradient rows of all samples that looked
 // it up, and applies SGD once per touched row.
 //
-// Work split: no two workgroups ever write the same table row.  Workgroup
-// (field f, hot id h), h < H = 16, owns id h alone; workgroup (field f,
-// part p) owns the ids >= H with id mod P == p (P = 16).  With Zipf-like
-// fields the small ids carry a large share of the samples (ids 0..15 about
-// 40 % at exponent 1.1 over 100k ids, id 0 alone 13 %): alone in a
-// workgroup each, their rows are summed without a sort, and the parts
-// left to sort stay small.  A hot-id workgroup collects the rows of its id
-// per pass (block scan, order fixed by the data), sums their gradient rows
-// with 64 scanners per 4-column chunk (each over every 64th listed row, in
-// list order) and a fixed-order tree over the scanners, and updates the
-// row once.  Per pass of up to 8192 samples a part workgroup
-//   1. collects its (id / P, row) keys into LDS from the field's row of the
-//      field-major id copy (a block scan of per-thread match counts places
-//      them; the keys are unique, so their order does not matter),
-//   2. sorts them (bitonic network over 2, 8 or 32 keys per thread held in
-//      registers, so the order is deterministic: by id, then by sample),
-//   3. stages the gradient rows of the sorted keys and the table rows of
-//      their ids in LDS, 256 positions at a time (every global load of a
-//      stage issued together, while the previous stage is scanned), and forms segmented
-//      sums per id with a fixed-shape scan: 64 scanners per 4-column chunk
-//      each reduce 8 consecutive positions, an exclusive segmented scan
-//      combines the scanners (lanes in order, then wavefronts in order),
-//      and each scanner walks its positions again, storing the updated
-//      table row where its id's segment ends.
-// The summation order depends only on the sorted positions, so two runs
-// give bitwise the same tables.
+// Work split: no two wavefronts ever write the same table row.  The ids of a
+// field are dealt to kParts = 64 parts (id mod 64); a workgroup takes four
+// parts of one field, a wavefront one of them.  Per pass of up to 8192
+// samples
+//   1. the workgroup reads the field's ids (a field-major copy the gather
+//      wrote) once and places the (id / 64, row) keys of its four parts into
+//      LDS, part by part, in a fixed order (a scan of per-thread counts);
+// then each wavefront works on its part alone, without a barrier:
+//   2. a frequent id is found in a sample of 64 of the part's keys (one that
+//      holds at least kHotSample of them), taken out of the list and summed
+//      in list order, kQueue rows in flight, whatever its value is: with
+//      Zipf-like fields the first ids carry a large share of the samples
+//      (exponent 1.1 over 100k ids: 13 %, 6 %, 4 %, ..), and sorting them
+//      would cost more than reading them;
+//   3. the other keys are sorted (bitonic network in registers up to 1024
+//      keys, in LDS beyond), by id, then by sample;
+//   4. segmented sums per id over the sorted keys, 128 positions at a time:
+//      16 lane groups (4 lanes: the row's 4-column chunks) take 8
+//      consecutive positions each, their gradient and table rows loaded
+//      together, a scan over the groups combines the segments that cross
+//      them, and the updated table row is stored where its segment ends.
+// The order of every sum depends only on the ids, so two runs give bitwise
+// the same tables.
+//
+// Bound by latency (dependent id, key, gradient and table reads), so many
+// small independent wavefronts: with a workgroup per part (16 sorted parts
+// and 16 workgroups for the ids 0 .. 15) and its barriers, 8192 samples of 13
+// fields took 27 us per party, now 22 us; with the frequent ids
+// scattered over the vocabulary, which those workgroups did not see,
+// 31 and 21.5 us.
 #include <algorithm>
 
 #include "device.h"
@@ -42,24 +46,24 @@ namespace {
 using namespace dev;
 
 constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
 constexpr int kRowBits = 13;
 constexpr int kPass = 1 << kRowBits;           // samples per pass
 constexpr uint32_t kRowMask = kPass - 1;
-constexpr int kStage = 256;                    // sorted positions staged at a time (64 KB of
-                                               // LDS in all: two workgroups per CU)
-constexpr int kScanners = kThreads / 4;        // per 4-column chunk
-constexpr int kSpan = kStage / kScanners;      // positions per scanner
 constexpr int kRowsPerThread = kPass / kThreads;     // rows a thread tests per pass
-constexpr int kParts = 16;                     // id parts per field (id mod kParts)
-constexpr int kHot = 16;                       // ids 0 .. kHot-1: a workgroup each
-constexpr int kStageLoads = kStage * 4 / kThreads;   // (gradient, table) pairs per thread and stage
+constexpr int kParts = 64;                     // id parts per field (id mod kParts)
+constexpr int kBlocksPerField = kParts / kWaves;
+constexpr int kHotMin = 128;                   // keys from which frequent ids are looked for
+constexpr int kHotSample = 8;                  // of 64 sampled keys: such an id is taken out
+constexpr int kQueue = 128;                    // rows of a frequent id summed together
+constexpr int kStage = 128;                    // sorted positions per stage
+constexpr int kGroups = 16;                    // 4-lane groups per wavefront
+constexpr int kSpan = kStage / kGroups;        // positions per group
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
-// segmented-scan operator on (head seen, value): a later head restarts the sum
-__device__ __forceinline__ void seg_combine(bool& F, f32x4& V, bool f2, const f32x4& v2) {
-  V = f2 ? v2 : V + v2;
-  F = F || f2;
-}
+// keeps the LDS accesses of a wavefront's lanes in program order (the
+// hardware does; this holds the compiler to it)
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
 __device__ __forceinline__ f32x4 shfl_up4(const f32x4& v, int d) {
   f32x4 r;
@@ -67,46 +71,40 @@ __device__ __forceinline__ f32x4 shfl_up4(const f32x4& v, int d) {
   for (int e = 0; e < 4; ++e) r[e] = __shfl_up(v[e], d, 64);
   return r;
 }
+__device__ __forceinline__ f32x4 shfl4(const f32x4& v, int lane) {
+  f32x4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = __shfl(v[e], lane, 64);
+  return r;
+}
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
-// Bitonic sort of a[0, n) (n <= kThreads * KPT) into ascending order over
-// N = kThreads * KPT slots, a[n, N) padded with kNone.  Thread t holds the
-// slots [t * KPT, t * KPT + KPT) in registers: compare-exchange distances
-// below KPT stay in the thread, those below 64 * KPT go through wavefront
-// shuffles, and only the longer ones through LDS.  Ends with a[0, N)
-// written back and a barrier.
+// Ascending bitonic sort of a[0, n), n <= 64 * KPT, by one wavefront: lane l
+// holds the slots [l * KPT, l * KPT + KPT) in registers (padded with kNone).
 template <int KPT>
-__device__ __forceinline__ void bitonic(uint32_t* a, int n) {
-  constexpr int N = kThreads * KPT;
-  const int t = threadIdx.x;
+__device__ __forceinline__ void sort_regs(uint32_t* a, int n) {
+  constexpr int N = 64 * KPT;
+  const int t = threadIdx.x & 63;
   uint32_t x[KPT];
 #pragma unroll
   for (int e = 0; e < KPT; ++e) x[e] = t * KPT + e < n ? a[t * KPT + e] : kNone;
+#pragma unroll 1
   for (int k = 2; k <= N; k <<= 1) {
+#pragma unroll 1
     for (int h = k >> 1; h >= KPT; h >>= 1) {
       // bit k of a slot index lies in t * KPT (k > h >= KPT)
-      const bool asc = ((t * KPT) & k) == 0;
-      const bool lower = ((t * KPT) & h) == 0;
+      const bool asc = ((t * KPT) & k) == 0, lower = ((t * KPT) & h) == 0;
       const bool keep_min = asc == lower;
-      if (h < 64 * KPT) {
-        const int m = h / KPT;
+      const int m = h / KPT;
 #pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-          const uint32_t o = (uint32_t)__shfl_xor((int)x[e], m, 64);
-          x[e] = keep_min ? min(x[e], o) : max(x[e], o);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) a[t * KPT + e] = x[e];
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-          const uint32_t o = a[(t * KPT + e) ^ h];
-          x[e] = keep_min ? min(x[e], o) : max(x[e], o);
-        }
-        __syncthreads();
+      for (int e = 0; e < KPT; ++e) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)x[e], m, 64);
+        x[e] = keep_min ? min(x[e], o) : max(x[e], o);
       }
     }
-    // distances below KPT: inside the thread
+    // distances below KPT: inside the lane
 #pragma unroll
     for (int h = KPT / 2; h >= 1; h >>= 1) {
       if (h >= k) continue;
@@ -121,52 +119,42 @@ __device__ __forceinline__ void bitonic(uint32_t* a, int n) {
     }
   }
 #pragma unroll
-  for (int e = 0; e < KPT; ++e) a[t * KPT + e] = x[e];
-  __syncthreads();
+  for (int e = 0; e < KPT; ++e)
+    if (t * KPT + e < n) a[t * KPT + e] = x[e];
+  lds_order();
 }
 
-// Block-wide placement of this thread's flagged rows (bit i of take: row
-// i * kThreads + tid of the pass) into keys[], key(i) each, in thread order;
-// returns the number of keys.  Ends with a barrier.
-template <typename KeyOf>
-__device__ __forceinline__ int place_keys(uint32_t take, uint32_t* keys, int* wcnt, KeyOf&& key) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = __builtin_popcount(take);
-  int incl = c;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int v = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += v;
+// the same in LDS, any n (slots past n count as kNone: an exchange with
+// one never moves a key there, because the network's last half-cleaner
+// directions leave the largest at the end)
+__device__ __forceinline__ void sort_lds(uint32_t* a, int n) {
+  const int t = threadIdx.x & 63;
+  int N = 64;
+  while (N < n) N <<= 1;
+  // the bitonic network with every comparison ascending (the first step of
+  // each merge compares mirrored slots), so that slots past n stay the
+  // largest and need no storage
+  for (int k = 2; k <= N; k <<= 1) {
+    for (int h = k >> 1; h >= 1; h >>= 1) {
+      for (int p = t; p < N / 2; p += 64) {
+        const int lo = (p / h) * 2 * h + p % h;
+        const int hi = h == k >> 1 ? (lo / k) * k + k - 1 - lo % k : lo + h;
+        if (hi < n) {
+          const uint32_t x = a[lo], y = a[hi];
+          if (x > y) { a[lo] = y; a[hi] = x; }
+        }
+      }
+      lds_order();
+    }
   }
-  if (lane == 63) wcnt[wave] = incl;
-  __syncthreads();
-  int pos = incl - c, total = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
-    const int x = wcnt[w];
-    pos += w < wave ? x : 0;
-    total += x;
-  }
-#pragma unroll
-  for (int i = 0; i < kRowsPerThread; ++i)
-    if ((take >> i) & 1u) keys[pos++] = key(i);
-  __syncthreads();
-  return total;
 }
 
-__global__ __launch_bounds__(kThreads) void k_embed_sgd(ScatterJob j) {
+__global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
   __shared__ uint32_t keys[kPass];
-  __shared__ f32x4 gs[kStage][4], ts[kStage][4];
-  __shared__ f32x4 wv[kThreads / 64][4];
-  __shared__ int wf[kThreads / 64][4];
-  __shared__ int wcnt[kThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // part workgroups first (the longer work is dispatched first), then the
-  // hot ids
-  const int nparts = j.n_cat * kParts;
-  const bool hot = (int)blockIdx.x >= nparts;
-  const int b = hot ? (int)blockIdx.x - nparts : (int)blockIdx.x;
-  const int f = hot ? b / kHot : b / kParts, part = hot ? b % kHot : b % kParts;
+  __shared__ uint16_t queue[kWaves][kQueue + 64];
+  __shared__ uint32_t wcnt[kWaves][2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f = blockIdx.x / kBlocksPerField, quad = blockIdx.x % kBlocksPerField;
   int R = j.R;
   float scale = j.scale;
   if (j.tr.src) {
@@ -176,142 +164,223 @@ __global__ __launch_bounds__(kThreads) void k_embed_sgd(ScatterJob j) {
   }
   const int EC = j.E / 4;                       // 4-column chunks per table row
   const VFL_GLOBAL int32_t* ids = glb(j.idt) + (int64_t)f * j.ldi;
-  const VFL_GLOBAL f32x4* G = glb((const f32x4*)j.G);
-  const int64_t ldg4 = j.ldg / 4;
-  VFL_GLOBAL f32x4* Tf = glb((f32x4*)(j.T + (int64_t)f * j.V * j.E));
-  const int q = tid >> 2, ch = tid & 3;         // scanner, chunk
+  const int grp = lane >> 2, ch = lane & 3;     // lane group, chunk
+  const int cc = min(ch, EC - 1);               // lanes past E repeat its last chunk (never stored)
+  // a pass's gradient rows and the field's table through uniform bases with
+  // 32-bit byte offsets (8192 rows of at most 64K floats; 2^19 rows of 64
+  // bytes), so that a load needs one address register
+  const uint32_t part = (uint32_t)(kWaves * quad + wave);
+  const VFL_GLOBAL char* Gb = glb((const char*)j.G) + (int64_t)f * EC * 16;
+  VFL_GLOBAL char* Tb = glb((char*)(j.T + (int64_t)f * j.V * j.E));
+  const uint32_t ldg = (uint32_t)j.ldg * 4u, row_bytes = 16u * (uint32_t)EC, lo = 16u * (uint32_t)cc;
+  auto table_row = [&](uint32_t id_hi) {        // this lane's chunk of the part's table row
+    return (VFL_GLOBAL f32x4*)(Tb + (uint32_t)((id_hi * (uint32_t)kParts + part) * row_bytes + lo));
+  };
+  uint16_t* q = queue[wave];
 
   for (int c0 = 0; c0 < R; c0 += kPass) {
     const int n = min(kPass, R - c0);
-    // 1. the workgroup's keys: every thread tests kPass / kThreads rows
-    // (strided, so each load instruction of a wavefront is contiguous), then
-    // a block scan of the per-thread counts places them
+    // 1. every thread tests kPass / kThreads rows (strided, so each load
+    // instruction of a wavefront is contiguous) and counts those of each of
+    // the workgroup's parts, in a byte each
     uint32_t idv[kRowsPerThread];
+    auto sub_part = [&](int i) {              // the row's part here, >= kWaves: not in this workgroup
+      return (idv[i] & (kParts - 1)) - (uint32_t)(kWaves * quad);
+    };
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) idv[i] = (uint32_t)ids[c0 + min(i * kThreads + tid, n - 1)];
-    uint32_t take = 0u;
+    uint32_t count = 0u;
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) {
-      const uint32_t id = idv[i];
-      const bool mine = hot ? id == (uint32_t)part : id >= (uint32_t)kHot && (id & (kParts - 1)) == (uint32_t)part;
-      take |= (uint32_t)(i * kThreads + tid < n && mine) << i;
+      const uint32_t x = sub_part(i);
+      count += x < (uint32_t)kWaves && i * kThreads + tid < n ? 1u << (8 * x) : 0u;
     }
-    if (hot) {
-      // rows of id `part`, in thread order; scanner q sums listed rows q,
-      // q + 64, ... of its chunk in list order (eight loads in flight)
-      const int np = place_keys(take, keys, wcnt, [&](int i) { return (uint32_t)(i * kThreads + tid); });
-      if (np == 0) continue;   // uniform: no barrier skipped by part of the block
-      const int cq = min(ch, EC - 1);
-      const VFL_GLOBAL f32x4* Gc = G + (int64_t)c0 * ldg4 + f * EC + cq;
-      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-      int p = q;
-      for (; p + 7 * kScanners < np; p += 8 * kScanners) {
-        f32x4 v[8];
+    // the counts of parts 0, 1 and 2, 3 as 16-bit halves (at most kPass
+    // together): scans over the lanes, then over the wavefronts
+    uint32_t cnt[2], incl[2];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = Gc[(int64_t)keys[p + u * kScanners] * ldg4];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
-      }
-      for (; p < np; p += kScanners) sum += Gc[(int64_t)keys[p] * ldg4];
-      // the 16 scanners of a wavefront (lanes 4 apart), a fixed tree
-#pragma unroll
-      for (int d = 32; d >= 4; d >>= 1) {
-        const f32x4 o = f32x4{__shfl_down(sum[0], d, 64), __shfl_down(sum[1], d, 64),
-                              __shfl_down(sum[2], d, 64), __shfl_down(sum[3], d, 64)};
-        sum += o;
-      }
-      if (lane < 4) wv[wave][lane] = sum;
-      __syncthreads();
-      if (tid < EC) {
-        const f32x4 tot = ((wv[0][tid] + wv[1][tid]) + wv[2][tid]) + wv[3][tid];
-        VFL_GLOBAL f32x4* row = Tf + (int64_t)part * EC + tid;
-        *row = *row - scale * tot;
-      }
-      __syncthreads();
-      continue;
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t x = count >> (16 * h);
+      cnt[h] = (x & 0xffu) | (x & 0xff00u) << 8;
+      incl[h] = cnt[h];
     }
-    const int np = place_keys(take, keys, wcnt, [&](int i) {
-      return ((idv[i] / kParts) << kRowBits) | (uint32_t)(i * kThreads + tid);
-    });
-    // 2. sort keys[0, np) ascending (padding kNone sorts last)
-    if (np <= 2 * kThreads) bitonic<2>(keys, np);
-    else if (np <= 8 * kThreads) bitonic<8>(keys, np);
-    else bitonic<32>(keys, np);
-    // 3. segmented sums, kStage sorted positions at a time; the gradient and
-    // table rows of the next stage are loaded while this one is scanned
-    f32x4 carry = f32x4{0.f, 0.f, 0.f, 0.f};    // the open segment entering the stage
-    f32x4 gv[kStageLoads], tv[kStageLoads];
-    // loads clamped into range, so all are unconditional and in flight
-    // together; chunks past E repeat the last one (never stored back)
-    auto issue = [&](int s0) {
 #pragma unroll
-      for (int u = 0; u < kStageLoads; ++u) {
-        const int i = min(s0 * 4 + u * kThreads + tid, np * 4 - 1);
-        const int c = min(i & 3, EC - 1);
-        const uint32_t key = keys[i >> 2];
-        gv[u] = G[(int64_t)(c0 + (key & kRowMask)) * ldg4 + f * EC + c];
-        tv[u] = Tf[(int64_t)((key >> kRowBits) * (uint32_t)kParts + (uint32_t)part) * EC + c];
-      }
-    };
-    if (np > 0) issue(0);
-    for (int s0 = 0; s0 < np; s0 += kStage) {
-      const int ns = min(kStage, np - s0);
+    for (int d = 1; d < 64; d <<= 1)
 #pragma unroll
-      for (int u = 0; u < kStageLoads; ++u) {
-        const int i = u * kThreads + tid;
-        if (i < ns * 4) { gs[i >> 2][i & 3] = gv[u]; ts[i >> 2][i & 3] = tv[u]; }
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl[h], d, 64);
+        if (lane >= d) incl[h] += v;
       }
-      __syncthreads();
-      issue(s0 + kStage);   // past the last stage: clamped repeats, never stored
-      auto head = [&](int a) { return a == 0 || (keys[a] >> kRowBits) != (keys[a - 1] >> kRowBits); };
-      const int p0 = q * kSpan, p1 = min(p0 + kSpan, ns);
-      // (a) the scanner's aggregate
-      bool F = false;
-      f32x4 V = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int i = p0; i < p1; ++i) seg_combine(F, V, head(s0 + i), gs[i][ch]);
-      // (b) inclusive scan over the 16 scanners of the wavefront (lanes 4 apart)
-      bool Fi = F;
-      f32x4 Vi = V;
+    if (lane == 63) { wcnt[wave][0] = incl[0]; wcnt[wave][1] = incl[1]; }
+    __syncthreads();
+    uint32_t before[2] = {0u, 0u}, total[2] = {0u, 0u};
 #pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
-        const f32x4 vu = shfl_up4(Vi, 4 * d);
-        const bool fu = __shfl_up((int)Fi, 4 * d, 64) != 0;
-        if ((lane >> 2) >= d) {
-          // (fu, vu) comes first: (fu, vu) then (Fi, Vi)
-          Vi = Fi ? Vi : vu + Vi;
-          Fi = Fi || fu;
-        }
+    for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t x = wcnt[w][h];
+        before[h] += w < wave ? x : 0u;
+        total[h] += x;
       }
-      if ((lane >> 2) == 15) { wv[wave][ch] = Vi; wf[wave][ch] = Fi; }
-      // exclusive prefix within the wavefront
-      f32x4 Ve = shfl_up4(Vi, 4);
-      bool Fe = __shfl_up((int)Fi, 4, 64) != 0;
-      if ((lane >> 2) == 0) { Ve = f32x4{0.f, 0.f, 0.f, 0.f}; Fe = false; }
-      __syncthreads();
-      // carry-in: stage carry, then the earlier wavefronts in order, then
-      // the earlier scanners of this wavefront
-      bool Fc = false;
-      f32x4 Vc = carry;
-      for (int w = 0; w < wave; ++w) seg_combine(Fc, Vc, wf[w][ch] != 0, wv[w][ch]);
-      seg_combine(Fc, Vc, Fe, Ve);
-      // (c) walk again; update where a segment ends
-      f32x4 run = Vc;
-      for (int i = p0; i < p1; ++i) {
-        const int a = s0 + i;
-        const f32x4 g = gs[i][ch];
-        run = head(a) ? g : run + g;
-        const bool last = a + 1 == np || (keys[a + 1] >> kRowBits) != (keys[a] >> kRowBits);
-        if (last && ch < EC) {
-          const uint32_t id = (keys[a] >> kRowBits) * (uint32_t)kParts + (uint32_t)part;
-          Tf[(int64_t)id * EC + ch] = ts[i][ch] - scale * run;
-        }
+    int base[kWaves + 1];
+    uint32_t pos[2];                          // of the thread's next key, packed like the counts
+    base[0] = 0;
+#pragma unroll
+    for (int s = 0; s < kWaves; ++s) base[s + 1] = base[s] + (int)((total[s >> 1] >> (16 * (s & 1))) & 0xffffu);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      pos[h] = before[h] + incl[h] - cnt[h] + ((uint32_t)base[2 * h] | (uint32_t)base[2 * h + 1] << 16);
+#pragma unroll
+    for (int i = 0; i < kRowsPerThread; ++i) {
+      const uint32_t x = sub_part(i);
+      if (x < (uint32_t)kWaves && i * kThreads + tid < n) {
+        const uint32_t sh = 16 * (x & 1), p = x & 2 ? pos[1] : pos[0];
+        keys[(p >> sh) & 0xffffu] = ((idv[i] / kParts) << kRowBits) | (uint32_t)(i * kThreads + tid);
+        pos[0] += x & 2 ? 0u : 1u << sh;
+        pos[1] += x & 2 ? 1u << sh : 0u;
       }
-      // the open segment after the whole stage
-      bool Ft = false;
-      for (int w = 0; w < kThreads / 64; ++w) seg_combine(Ft, carry, wf[w][ch] != 0, wv[w][ch]);
-      __syncthreads();
     }
     __syncthreads();
+    int b0 = base[0], np = base[1] - base[0];
+#pragma unroll
+    for (int s = 1; s < kWaves; ++s)
+      if (wave == s) { b0 = base[s]; np = base[s + 1] - base[s]; }
+    b0 = __builtin_amdgcn_readfirstlane(b0);
+    np = __builtin_amdgcn_readfirstlane(np);
+    uint32_t* list = keys + b0;
+    const VFL_GLOBAL char* Gp = Gb + (int64_t)c0 * ldg;
+    auto grad_row = [&](uint32_t row) { return *(const VFL_GLOBAL f32x4*)(Gp + (uint32_t)(row * ldg + lo)); };
+
+    // 2. frequent ids (at least kHotSample keys leave the list each time)
+    while (np > kHotMin) {
+      const uint32_t sid = list[(lane * np) >> 6] >> kRowBits;
+      int same = 0;
+#pragma unroll 8
+      for (int l = 0; l < 64; ++l) same += sid == (uint32_t)__builtin_amdgcn_readlane((int)sid, l) ? 1 : 0;
+      int best = same << 6 | lane;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) best = max(best, __shfl_xor(best, d, 64));
+      best = __builtin_amdgcn_readfirstlane(best);
+      if ((best >> 6) < kHotSample) break;
+      const uint32_t hot = (uint32_t)__builtin_amdgcn_readlane((int)sid, best & 63);
+      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+      // rows q[0, m) (m <= kQueue) are loaded together, a lane group every
+      // 16th, and added, in order, once the next ones are found
+      f32x4 v[kQueue / kGroups];
+      int loaded = 0;
+      auto add_loaded = [&] {
+#pragma unroll
+        for (int u = 0; u < kQueue / kGroups; ++u)
+          if (u * kGroups + grp < loaded) sum += v[u];
+      };
+      auto load_rows = [&](int m) {
+#pragma unroll
+        for (int u = 0; u < kQueue / kGroups; ++u) v[u] = grad_row(q[min(u * kGroups + grp, m - 1)]);
+        loaded = m;
+      };
+      int rest = 0, qn = 0;
+      for (int i0 = 0; i0 < np; i0 += 64) {
+        const bool in = i0 + lane < np;
+        const uint32_t key = list[min(i0 + lane, np - 1)];
+        const bool is = in && (key >> kRowBits) == hot;
+        const uint64_t bh = __ballot(is), br = __ballot(in && !is);
+        lds_order();
+        if (is) q[qn + lanes_below(bh)] = (uint16_t)(key & kRowMask);
+        else if (in) list[rest + lanes_below(br)] = key;   // at or below i0 + lane: read already
+        rest += __builtin_popcountll(br);
+        qn += __builtin_popcountll(bh);
+        lds_order();
+        if (qn >= kQueue) {
+          add_loaded();
+          load_rows(kQueue);
+          const uint16_t left = q[kQueue + lane];
+          lds_order();
+          if (lane < qn - kQueue) q[lane] = left;
+          qn -= kQueue;
+          lds_order();
+        }
+      }
+      add_loaded();
+      if (qn > 0) {
+        load_rows(qn);
+        add_loaded();
+      }
+      np = rest;
+      // the 16 groups (lanes 4 apart), a fixed tree
+#pragma unroll
+      for (int d = 32; d >= 4; d >>= 1) {
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __shfl_down(sum[e], d, 64);
+        sum += o;
+      }
+      if (lane < EC) {
+        VFL_GLOBAL f32x4* row = table_row(hot);   // (lane = chunk here)
+        *row = *row - scale * sum;
+      }
+    }
+
+    // 3. sort
+    if (np <= 64) sort_regs<1>(list, np);
+    else if (np <= 128) sort_regs<2>(list, np);
+    else if (np <= 256) sort_regs<4>(list, np);
+    else if (np <= 1024) sort_regs<16>(list, np);
+    else sort_lds(list, np);
+
+    // 4. segmented sums
+    f32x4 carry = f32x4{0.f, 0.f, 0.f, 0.f};    // the open segment entering the stage
+    for (int s0 = 0; s0 < np; s0 += kStage) {
+      const int p0 = s0 + grp * kSpan;
+      uint32_t id[kSpan + 2];                   // of positions p0 - 1 .. p0 + kSpan (kNone outside the list)
+      f32x4 gv[kSpan], tv[kSpan];
+#pragma unroll
+      for (int u = 0; u < kSpan + 2; ++u) {
+        const int p = p0 - 1 + u;
+        const uint32_t key = list[min(max(p, 0), np - 1)];
+        id[u] = p >= 0 && p < np ? key >> kRowBits : kNone;
+        if (u >= 1 && u <= kSpan) {
+          gv[u - 1] = grad_row(key & kRowMask);
+          tv[u - 1] = *table_row(key >> kRowBits);
+        }
+      }
+      // (a) the group's aggregate: F, whether a segment starts in it
+      bool F = false;
+      f32x4 V = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 1; u <= kSpan; ++u) {
+        const f32x4 g = p0 + u - 1 < np ? gv[u - 1] : f32x4{0.f, 0.f, 0.f, 0.f};
+        const bool head = id[u] != id[u - 1];
+        V = head ? g : V + g;
+        F = F || head;
+      }
+      // (b) inclusive scan over the groups (lanes 4 apart)
+#pragma unroll
+      for (int d = 1; d < kGroups; d <<= 1) {
+        const f32x4 vu = shfl_up4(V, 4 * d);
+        const bool fu = __shfl_up((int)F, 4 * d, 64) != 0;
+        if (grp >= d) {
+          // (fu, vu) comes first
+          V = F ? V : vu + V;
+          F = F || fu;
+        }
+      }
+      // what enters the group: the stage's carry, then the earlier groups
+      const f32x4 ve = shfl_up4(V, 4);
+      const bool fe = __shfl_up((int)F, 4, 64) != 0;
+      f32x4 run = grp == 0 ? carry : (fe ? ve : carry + ve);
+      // (c) walk again; update where a segment ends
+#pragma unroll
+      for (int u = 1; u <= kSpan; ++u) {
+        run = id[u] != id[u - 1] ? gv[u - 1] : run + gv[u - 1];
+        if (p0 + u - 1 < np && id[u] != id[u + 1] && ch < EC)
+          *table_row(id[u]) = tv[u - 1] - scale * run;
+      }
+      // the open segment after the stage (a full one: all positions valid)
+      const f32x4 vl = shfl4(V, 60 + ch);
+      const bool fl = __shfl((int)F, 60 + ch, 64) != 0;
+      carry = fl ? vl : carry + vl;
+    }
+    __syncthreads();   // the next pass refills the keys
   }
 }
 
@@ -319,7 +388,7 @@ __global__ __launch_bounds__(kThreads) void k_embed_sgd(ScatterJob j) {
 
 hipError_t launch_scatter_sgd(const ScatterJob& j, hipStream_t st) {
   if (j.E > kMaxEmbDim || j.E % 4 || j.ldg % 4 || j.V > (1 << (32 - kRowBits))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_embed_sgd, dim3(j.n_cat * (kParts + kHot)), dim3(kThreads), 0, st, j);
+  hipLaunchKernelGGL(k_embed_sgd, dim3(j.n_cat * kBlocksPerField), dim3(kThreads), 0, st, j);
   return hipGetLastError();
 }
 
