@@ -40,7 +40,10 @@ using namespace vfl;
 namespace {
 
 constexpr int kMaxSlots = VFL_MAX_STALENESS + 1;
-constexpr int kGemmMinWidth = 512;    // B's first-layer width from which its input gradient is a layer product
+constexpr int kGemmMinWidth = 512;    // B's first-layer width from which its input gradient may be a layer product
+constexpr int kGemmMinRows = 2048;    // rows from which it is one where the chain has fewer than
+constexpr int kGemmChainRows = 48;    // these rows per block
+constexpr int kBwdChunk = 256;        // columns per range of B's last delta
 constexpr int kMinBlocks = 256;       // row blocks a chain launch aims at (one per CU)
 constexpr int kDwBlocks = 256;        // weight-gradient blocks a launch aims at
 constexpr double kRcStreamBytes = 32e6;  // RC copies above this size use streaming stores
@@ -150,7 +153,7 @@ struct ActBufs {
     for (int q = 0; q + 1 < LA; ++q) da[q] = next();
   }
 };
-struct BwdLds { LBuf P[2], mask[VFL_MAX_LAYERS]; int bytes = 0; };
+struct BwdLds { LBuf P[2], C, mask[VFL_MAX_LAYERS]; int bytes = 0; };   // C: every second column range
 
 struct KMeta { int rt = 1, blocks = 1, lds = 0, cw = kChainCopyWaves; };
 
@@ -181,6 +184,7 @@ struct Plan {
   size_t mbits[kMaxSlots][VFL_MAX_LAYERS]{};   // B's ReLU bits per slot and layer [Ra / 8 x ldb[l]] (0: none)
   int ldb[VFL_MAX_LAYERS]{};                  // their row pitch (bytes: the layer width rounded up to 64)
   KMeta kf, ka, kb;
+  int bchunk = 0;                     // columns per range of B's last delta (0: whole)
   FwdLds lf;
   ActLds la;
   BwdLds lb;
@@ -341,8 +345,8 @@ constexpr double kDwtMinFlops = 4e9;
 // 86.7; 500-1024-512-128 at 2048 and 4096 rows, 285 and 570 MB of reads:
 // 110 / 101, 122.5 / 123.6).
 constexpr int kDwUnsplitBytes = 8192;
+constexpr int kDwUnsplitSmall = 2048;   // up to here whatever the reads
 constexpr int64_t kDwUnsplitReads = 320 << 20;   // bytes, two 32-column operands per tile
-constexpr int kDw32Steps = 16;        // MFMA row steps the RC rows are rounded up to there (k_dw32)
 
 // Chunks of at least this many rows may be cut at any 32-row stage.
 constexpr int kDwtFineRows = 1024;
@@ -433,7 +437,8 @@ void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
   a.bytes = l.off;
 }
 
-void plan_bwd_lds(const Plan& p, int BR, BwdLds& b) {
+// chunk: columns per range of the chain's last delta (0: whole)
+void plan_bwd_lds(const Plan& p, int BR, int chunk, BwdLds& b) {
   Lds l;
   l.KS = p.e == BF16 ? 32 : 16;
   l.BR = BR;
@@ -442,11 +447,16 @@ void plan_bwd_lds(const Plan& p, int BR, BwdLds& b) {
   // those of layers 1 .. L-1
   const int lo = p.bgemm ? 1 : 0;
   // the cut delta (layer L-1's output) is in P[0], the delta of layer i's
-  // output in P[(L-1-i) % 2]; the table input gradient reads layer 0's
+  // output in P[(L-1-i) % 2]; the table input gradient reads layer 0's.  In
+  // ranges, the last delta alternates between its P and C
   int w[2] = {1, 1};
-  for (int i = lo; i < p.P.L; ++i) w[(p.P.L - 1 - i) % 2] = std::max(w[(p.P.L - 1 - i) % 2], p.P.out[i]);
+  for (int i = lo; i < p.P.L; ++i) {
+    const int wi = chunk && i == 0 ? chunk : p.P.out[i];
+    w[(p.P.L - 1 - i) % 2] = std::max(w[(p.P.L - 1 - i) % 2], wi);
+  }
   b.P[0] = l.take(w[0], es);
   b.P[1] = l.take(w[1], es);
+  if (chunk) b.C = l.take(chunk, es);
   // one mask buffer per ReLU layer the chain crosses: all are loaded up
   // front; bf16 keeps the bits B's forward recorded (a byte per 8 rows and
   // column), float32 the stashed activations
@@ -461,6 +471,46 @@ void plan_bwd_lds(const Plan& p, int BR, BwdLds& b) {
     }
   }
   b.bytes = l.off;
+}
+
+// The interface's limit on the widths: one workgroup's LDS holds 16 rows of
+// every layer's output of party A and the top model (B's embedding and the
+// message beside them), and of B's widest pairs of layers with a ReLU mask
+// per layer.  The kernels' own layouts are smaller; the limit stays where it
+// was when they kept all of that, so that what is accepted does not depend
+// on them.  Empty when the widths are within it.
+std::string width_limit(const Plan& p, bool gextra) {
+  const int es = elt_size(p.e);
+  Lds l;
+  l.KS = p.e == BF16 ? 32 : 16;
+  int w = 1;
+  for (int j = 0; j < p.T.H; ++j) w = std::max(w, p.T.out[j]);
+  for (int i = 0; i < p.A.L; ++i) w = std::max(w, p.A.out[i]);
+  for (int i = 0; i + 1 < p.A.L; ++i) l.take(p.A.out[i], es);
+  l.take(p.dA + p.dB, es);
+  for (int j = 0; j + 1 < p.T.H; ++j) l.take(p.T.out[j], es);
+  l.take(w, es);
+  LBuf x, y;
+  l.take_shared(x, p.A.din, es, y, w, es);
+  if (gextra) l.take_shared(x, p.T.out[p.T.H - 1], es, y, p.dB, 4);
+  else l.take(p.T.out[p.T.H - 1], es);
+  l.raw(4 * (l.BR + kChainWaves * ((p.T.out[p.T.H - 1] + 3) / 4 * 4) + 2 * kChainWaves));
+  l.raw(4 * p.nbias_a);
+  if (l.off > kLdsMax) return "party A's and the top model's widths exceed the LDS of one workgroup";
+  // a bf16 first layer from kGemmMinWidth on does not count in the backward
+  const int lo = p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth ? 1 : 0;
+  int v[2] = {1, 1};
+  for (int i = lo; i < p.P.L; ++i) v[(p.P.L - 1 - i) % 2] = std::max(v[(p.P.L - 1 - i) % 2], p.P.out[i]);
+  l.off = 0;
+  l.take(v[0], es);
+  l.take(v[1], es);
+  for (int i = lo; i + 1 < p.P.L; ++i) {
+    if (!p.P.relu[i]) continue;
+    if (p.e == BF16) l.raw(l.BR / 8 * ((p.P.out[i] + 63) / 64 * 64 + 16));
+    else l.take(p.P.out[i], es);
+  }
+  if (l.off > kLdsMax) return "party B's widths exceed the LDS of one workgroup";
+  return "";
 }
 
 // Rows per block: the largest of 64, 48, 32, 16 whose layout fits the LDS
@@ -479,6 +529,25 @@ bool pick_rt(int R, KMeta& m, F&& bytes_at) {
     return true;
   }
   return false;
+}
+
+// The backward chain's rows per block, with its last delta whole or in
+// ranges of kBwdChunk columns: that delta (of B's first layer) is read by no
+// further product, so it need not take LDS for its whole width where that
+// leaves room for more rows.  rt > 0: whether the LDS holds 16 * rt rows.
+bool pick_bwd(const Plan& p, int rt, KMeta& m, int& chunk) {
+  const bool ranges = !p.bgemm && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] > kBwdChunk &&
+                      p.P.L - 2 + (p.P.out[0] + kBwdChunk - 1) / kBwdChunk <= kMaxChain;
+  auto bytes = [&](int BR, int c) { BwdLds x; plan_bwd_lds(p, BR, c, x); return x.bytes; };
+  if (rt > 0) return bytes(16 * rt, 0) <= kLdsMax || (ranges && bytes(16 * rt, kBwdChunk) <= kLdsMax);
+  chunk = 0;
+  const bool whole = pick_rt(p.R, m, [&](int BR) { return bytes(BR, 0); });
+  KMeta r;
+  if (ranges && pick_rt(p.R, r, [&](int BR) { return bytes(BR, kBwdChunk); }) && (!whole || r.rt > m.rt)) {
+    m = r;
+    chunk = kBwdChunk;
+  }
+  return whole || chunk;
 }
 
 std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const vfl_top_spec* t,
@@ -515,11 +584,10 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   p.B = o->batch;
   p.R = o->batch * o->replicas;
   // weight-gradient launch shapes of each party (they fix the RC row count
-  // Ra): the unsplit 32 x 32 weight gradient, whose wavefronts cover the
-  // rows rounded up to 16 MFMA steps, or row chunks of rps rows (a multiple
-  // of two load groups) over 64 x 64 or 256 x 256 tiles.  Every block
-  // contracts whole steps or chunks: the rows past the group are zero
-  // deltas.
+  // Ra): the unsplit 32 x 32 weight gradient over the rows rounded up to
+  // 128, or row chunks of rps rows (a multiple of two load groups) over 64 x
+  // 64 or 256 x 256 tiles.  Every block contracts whole MFMA steps or chunks:
+  // the rows past the group are zero deltas.
   {
     auto bottom_tiles = [&](const vfl_bottom_spec* sp, int tile) {
       int in = sp->n_cat * sp->emb_dim + sp->dense_in, n = 0;
@@ -543,13 +611,13 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
       for (int j = 0; j + 1 < t->n_layers; ++j) { top_macs += in * t->widths[j]; in = t->widths[j]; }
     }
     const bool bf = dtype == VFL_BF16;
-    const int es = elt_size(p.e), gran = kDw32Steps * 64 / es;
+    const int es = elt_size(p.e);
     auto shape = [&](DwMeta& m, int tiles32, double macs, auto&& tiles_of) {
       const int64_t col_bytes = (int64_t)p.R * es;
-      if (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads) {
+      if (col_bytes <= kDwUnsplitSmall || (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads)) {
         m.tile = 32;
         m.splits = 1;
-        m.rps = (p.R + gran - 1) / gran * gran;
+        m.rps = (p.R + 127) / 128 * 128;
         m.blocks = tiles32;
       } else {
         m.tile = bf && 2.0 * p.R * macs >= kDwtMinFlops ? 256 : 64;
@@ -622,17 +690,30 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   party(p.P, b, p.s + 1, true);
   p.dA = p.A.out[p.A.L - 1];
   p.dB = p.P.out[p.P.L - 1];
-  // B's first layer at least kGemmMinWidth wide (its deltas would crowd the
-  // chain's LDS), no tables, bf16: layer 1's input gradient is a layer
-  // product over the whole group
-  p.bgemm = p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth;
+  for (int l = 0; l + 1 < p.P.L; ++l) p.ldb[l] = (p.P.out[l] + 63) / 64 * 64;
+  // Layer 1's input gradient of B as a layer product over the whole group
+  // (bf16, no tables) where B's backward chain would have fewer than
+  // kGemmChainRows rows per block, so that each block streams the wide
+  // weights for few rows, and the group gives the product's 256 x 256 tiles
+  // enough work, or where the chain's LDS does not hold the layers at all.
+  // Everywhere else the chain is faster: it saves the launch and the
+  // row-major delta's way through HBM, and small groups do not fill the
+  // CUs with large tiles (us per tick, product / chain; 500-1024-512-128 at
+  // 512, 8192 and 32768 rows: 89 / 72, 152 / 143, 381 / 370;
+  // 500-2048-512-128 at 32768 rows: 753 / 737; 500-2048-1024-128 at 2048
+  // and 32768 rows, 32 rows per block: 183 / 182, 1090 / 1159).
+  if (p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth) {
+    KMeta m;
+    int chunk = 0;
+    p.bgemm = !pick_bwd(p, 1, m, chunk) ||
+              (p.R >= kGemmMinRows && !pick_bwd(p, kGemmChainRows / 16, m, chunk));
+  }
   if (p.bgemm) p.d1rm = ly.take((size_t)es * R * ld_of(p.P.out[1]));
   // bf16: B's forward records one bit per activation of every ReLU layer
   // below the cut layer, which B's delayed backward (and the wide layer's
   // input-gradient product) read as the ReLU derivative instead of the
   // stashed activations
   if (p.e == BF16) {
-    for (int l = 0; l + 1 < p.P.L; ++l) p.ldb[l] = (p.P.out[l] + 63) / 64 * 64;
     for (int q = 0; q <= p.s; ++q)
       for (int l = 0; l + 1 < p.P.L; ++l)
         if (p.P.relu[l]) p.mbits[q][l] = ly.take((size_t)(Ra / 8) * p.ldb[l]);
@@ -674,13 +755,14 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   for (int l = 0; l < p.P.L; ++l) p.P.b[l] = p.bias_b + sizeof(float) * p.P.bo[l];
   p.cat_rc = ly.take(rc_bytes(p.dA + p.dB));
 
+  why = width_limit(p, gextra);
+  if (!why.empty()) return why;
   // chain kernels: rows per block and LDS layouts
   if (!pick_rt(p.R, p.kf, [&](int BR) { FwdLds f; plan_fwd_lds(p, BR, f); return f.bytes; }))
     return "party B's widths exceed the LDS of one workgroup";
   if (!pick_rt(p.R, p.ka, [&](int BR) { ActLds x; plan_act_lds(p, BR, gextra, x); return x.bytes; }))
     return "party A's and the top model's widths exceed the LDS of one workgroup";
-  if (!pick_rt(p.R, p.kb, [&](int BR) { BwdLds x; plan_bwd_lds(p, BR, x); return x.bytes; }))
-    return "party B's widths exceed the LDS of one workgroup";
+  if (!pick_bwd(p, 0, p.kb, p.bchunk)) return "party B's widths exceed the LDS of one workgroup";
   {
     // B's backward starts every block with its loads (ReLU masks, gradient
     // message, stashed output): 32-row blocks when two of them fit one CU's
@@ -697,8 +779,8 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     double macs_a = macs(p.A);
     for (int j = 0; j < T.H; ++j) macs_a += (double)T.in[j] * T.out[j];
     BwdLds two, cur;
-    plan_bwd_lds(p, 32, two);
-    plan_bwd_lds(p, 16 * p.kb.rt, cur);
+    plan_bwd_lds(p, 32, p.bchunk, two);
+    plan_bwd_lds(p, 16 * p.kb.rt, p.bchunk, cur);
     if (p.kb.rt > 2 && 2 * two.bytes <= kLdsMax && 2 * cur.bytes > kLdsMax && macs(p.P) > 2 * macs_a) {
       p.kb.rt = 2;
       p.kb.blocks = (p.R + 31) / 32;
@@ -707,7 +789,7 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   }
   plan_fwd_lds(p, 16 * p.kf.rt, p.lf);
   plan_act_lds(p, 16 * p.ka.rt, gextra, p.la);
-  plan_bwd_lds(p, 16 * p.kb.rt, p.lb);
+  plan_bwd_lds(p, 16 * p.kb.rt, p.bchunk, p.lb);
   T.logit_part = ly.take(sizeof(float) * (size_t)p.ka.blocks * (T.out[T.H - 1] + 2));
 
   // messages and control
@@ -778,25 +860,22 @@ bool layer_fits(const Plan& p, const ChainLayer& L, int BR, int lds, bool lds_ou
   const int es = elt_size(p.e), KS = p.e == BF16 ? 32 : 16;
   auto inside = [&](const LBuf& b, int cols) {
     const int need = (cols + KS - 1) / KS * KS * es;
-    return b.pitch >= need && b.off >= 0 && b.off + b.pitch * BR <= lds && b.off % 16 == 0 && b.pitch % 16 == 0;
+    return b.pitch >= need && b.off >= 0 && b.off + b.pitch * (BR - 1) + need <= lds && b.off % 16 == 0 && b.pitch % 16 == 0;
   };
   if (!L.W || L.N < 1 || L.K < 1 || L.kst != (L.K + KS - 1) / KS) return false;
   if (L.bl >= 0 && (L.bl % 16 || L.bl + 4 * ((L.N + 31) / 32 * 32) > lds)) return false;
   if (!inside(L.in, L.K)) return false;
   if (lds_out && !inside(L.out, out_cols < 0 ? L.N : out_cols)) return false;
   // byte masks: a byte per 16 / es rows and column, read four columns at a
-  // time up to the MFMA depth; those loaded from the stash are copied 16
-  // columns at a time
+  // time up to the MFMA depth
   auto bytes_inside = [&](const LBuf& m, int cols) {
     return m.off >= 0 && m.off % 16 == 0 && m.pitch % 16 == 0 && m.pitch >= (cols + KS - 1) / KS * KS &&
-           m.off + m.pitch * (BR * es / 16) <= lds;
+           m.off + m.pitch * (BR * es / 16 - 1) + (cols + KS - 1) / KS * KS <= lds;
   };
   const int mcols = out_cols < 0 ? L.N : out_cols;
   if (L.mask_out.pitch && !bytes_inside(L.mask_out, L.N)) return false;
   if (L.mask.pitch && L.mask_bits) {
-    const int nb = (L.N + 15) / 16 * 16;
     if (!bytes_inside(L.mask, mcols)) return false;
-    if (L.mask_src.p && (!L.mask_src.bits || L.mask_src.ldb < nb || L.mask_src.ldb % 16)) return false;
   } else if (L.mask.pitch && !inside(L.mask, L.N)) {
     return false;
   }
@@ -975,23 +1054,39 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     b.hdr_chk = hdrp(1, q); b.err = (int32_t*)(ws + p.hdr) + 2 * kMaxSlots * 4;
     b.warm.p[0] = c->ws + P.Wtq[q][0];
     b.warm.lines[0] = (int32_t)((P.wtq_end[q] - P.Wtq[q][0]) / 128);
-    b.nd = P.L - 1 - (p.bgemm ? 1 : 0);
-    for (int qq = 0; qq < b.nd; ++qq) {
+    const int nd = P.L - 1 - (p.bgemm ? 1 : 0);
+    for (int qq = 0; qq < nd; ++qq) {
       const int l = P.L - 1 - qq;
-      ChainLayer& L = b.dx[qq];
-      L = layer(c->ws + P.Wtq[q][l], P.kt[l], -1, P.in[l], P.out[l], false, lb.P[qq % 2], lb.P[(qq + 1) % 2]);
+      LBuf mask;
       if (P.relu[l - 1]) {
-        L.mask = lb.mask[l - 1];
-        L.mask_src = rcm(c, P.arc[q][l - 1], P.out[l - 1]);
+        mask = lb.mask[l - 1];
+        MaskLoad& ml = b.ml[b.nmask++];
+        ml.b = mask;
+        ml.m = rcm(c, P.arc[q][l - 1], P.out[l - 1]);
+        ml.cols = P.out[l - 1];
         if (p.mbits[q][l - 1]) {
-          L.mask_src.bits = (uint8_t*)(ws + p.mbits[q][l - 1]);
-          L.mask_src.ldb = p.ldb[l - 1];
-          L.mask_bits = 1;
+          ml.m.bits = (uint8_t*)(ws + p.mbits[q][l - 1]);
+          ml.m.ldb = p.ldb[l - 1];
         }
-        // bf16 backward kernels read masks only in the byte form
-        if ((p.e == BF16) != (L.mask_bits != 0)) return "party B's backward: bf16 masks without ReLU bits";
+        // bf16 masks are the stashed bits, copied 16 columns at a time
+        if ((p.e == BF16) != (ml.m.bits != nullptr)) return "party B's backward: bf16 masks without ReLU bits";
+        if (p.e == BF16 && (ml.m.ldb % 16 || ml.m.ldb < (ml.cols + 15) / 16 * 16 || mask.pitch < (ml.cols + 15) / 16 * 16))
+          return "internal: party B's backward masks do not cover a layer";
       }
-      L.rc = rcm(c, P.drc[l - 1], P.out[l - 1]);
+      const int step = p.bchunk && l == 1 ? p.bchunk : P.in[l];
+      for (int n0 = 0; n0 < P.in[l]; n0 += step) {
+        // columns n0 .. n0 + N of the delta (n0 a multiple of 256: whole
+        // 16-column tiles of the packed operand)
+        ChainLayer& L = b.dx[b.nd++];
+        const LBuf out = (n0 / step) % 2 ? lb.C : lb.P[(qq + 1) % 2];
+        L = layer(c->ws + P.Wtq[q][l] + (size_t)(n0 / 16) * P.kt[l] * 1024, P.kt[l], -1, std::min(step, P.in[l] - n0),
+                  P.out[l], false, lb.P[qq % 2], out);
+        L.mask = mask;
+        L.mask.off += n0 * (p.e == BF16 ? 1 : elt_size(p.e));
+        L.mask_bits = p.e == BF16;
+        L.rc = rcm(c, P.drc[l - 1], P.out[l - 1]);
+        L.rc.p = (char*)L.rc.p + (size_t)n0 * 16;
+      }
     }
     b.has_gx = P.spec.n_cat > 0;
     if (b.has_gx) {
@@ -1417,7 +1512,7 @@ struct StateHead {
       slot_published[kMaxSlots];
 };
 constexpr char kStateMagic[8] = {'V', 'F', 'L', 'S', 'T', 'A', 'T', 'E'};
-constexpr uint32_t kStateFormat = 2;
+constexpr uint32_t kStateFormat = 3;   // 3: workspace layout of the chain kernels with copy wavefronts
 
 // FNV-1a over everything that fixes the workspace layout: element type,
 // batch, staleness, replicas and both bottom specs and the top spec.

@@ -489,140 +489,56 @@ __device__ __forceinline__ void zero_rc(const RCMat& m, int cols, int r0) {
   }
 }
 
-// RC global matrix -> LDS rows (columns below cols; zeros up to the MFMA
-// depth): one lane per chunk (RR rows of one column), one 16-byte load (or
-// a byte of the matrix's ReLU bits when it has them) and RR element writes.
-// Past one chunk per lane, the loads of NB units per lane are issued
-// before their first use (one round trip to HBM per NB units, not per
-// unit), and bits go a lane per 4 chunks (one 4-byte load, an 8-byte write
-// per row).  Blocks with at most one chunk per lane keep the one-chunk
-// loop (narrow masks: there the batched form was slower beside the other
-// party's kernels).
 // The ReLU bits of a block's BR rows as they are (a byte per 8 rows and
 // column) into b: BR / 8 rows of b.pitch bytes, 16 bytes per lane and load,
-// columns up to cols rounded to 16 (within m.ldb).  Row groups past m.rows
+// columns up to cols rounded to 16 (within m.ldb), by the copy
+// threads.  Row groups past m.rows
 // repeat its last (their rows are past the tick's and never kept).
 template <int BR>
 __device__ __forceinline__ void bits_to_lds(char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
   const int nc = (cols + 15) / 16;
   const int rg_last = m.rows > 0 ? max(m.rows / 8 - 1, 0) : (1 << 30);
   const VFL_GLOBAL uint8_t* bits = glb((const uint8_t*)m.bits);
-  for (int u = threadIdx.x; u < (BR / 8) * nc; u += kNT) {
+  for (int u = (int)threadIdx.x - kNT; u < (BR / 8) * nc; u += (int)blockDim.x - kNT) {
     const int rg = u / nc, c = 16 * (u - rg * nc);
     const u32x4 v = __builtin_nontemporal_load((const VFL_GLOBAL u32x4*)(bits + (int64_t)min(r0 / 8 + rg, rg_last) * m.ldb + c));
     *(u32x4*)(s + b.off + rg * b.pitch + c) = v;
   }
 }
 
+// RC global matrix -> LDS rows (columns below cols; zeros up to the MFMA
+// depth), by the copy threads: one 16-byte load per chunk (RR rows of one
+// column) and RR element writes, the loads of NB chunks per lane issued
+// before their first use (one round trip to HBM per NB chunks).
 template <typename T, int BR>
 __device__ __forceinline__ void rc_to_lds(char* s, const LBuf& b, int cols, const RCMat& m, int r0) {
   constexpr int RR = Ch<T>::CE, KS = Ch<T>::KS;
-  constexpr int NB = 4;                       // units whose loads are in flight together
+  constexpr int NB = 4;
+  static_assert(RR == 4, "bf16 masks are bits");
+  const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
   const int cw = (cols + KS - 1) / KS * KS;   // columns up to the MFMA depth
   const VFL_GLOBAL char* g = glb((const char*)m.p);
   const int64_t cp = m.cp;
-  const VFL_GLOBAL uint8_t* bits = glb((const uint8_t*)m.bits);
   const int rg_last = m.rows > 0 ? max(m.rows / RR - 1, 0) : (1 << 30);
-  const int units = (BR / RR) * cw;
-  if constexpr (RR == 8) {
-    if (bits && units > kNT) {
-      // the ReLU bits: a lane takes 4 columns of a row group (one 4-byte
-      // load, byte j = column c + j, bit i = row i), written as bf16 ones
-      // (which the mask test reads as positive), 8 bytes per LDS row
-      const int nc4 = cw / 4, nu = (BR / RR) * nc4;
-      for (int u0 = threadIdx.x; u0 < nu; u0 += NB * kNT) {
-        uint32_t wv[NB];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int u = min(u0 + i * kNT, nu - 1);
-          const int rg = u / nc4, c = 4 * (u - rg * nc4);
-          wv[i] = *(const VFL_GLOBAL uint32_t*)(bits + (int64_t)min(r0 / RR + rg, rg_last) * m.ldb + c);
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int u = u0 + i * kNT;
-          if (u >= nu) continue;
-          const int rg = u / nc4, c = 4 * (u - rg * nc4);
-          const bool in_m = m.rows == 0 || r0 + rg * RR < m.rows;
-          uint32_t w = in_m ? wv[i] : 0u;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (c + j >= cols) w &= ~(0xffu << (8 * j));
-          char* dst = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            uint2 q;
-            q.x = ((w >> r) & 1u ? 0x3f80u : 0u) | ((w >> (8 + r)) & 1u ? 0x3f800000u : 0u);
-            q.y = ((w >> (16 + r)) & 1u ? 0x3f80u : 0u) | ((w >> (24 + r)) & 1u ? 0x3f800000u : 0u);
-            *(uint2*)(dst + r * b.pitch) = q;
-          }
-        }
-      }
-      return;
-    }
-  }
-  if (units <= kNT) {
-    // at most one chunk per lane: a chunk of RC data or of bits each
-    const int u = threadIdx.x;
-    if (u < units) {
-      const int rg = u / cw, c = u - rg * cw;
-      u32x4 v = u32x4{0u, 0u, 0u, 0u};
-      if (c < cols && (m.rows == 0 || r0 + rg * RR < m.rows)) {
-        if constexpr (RR == 8) {
-          if (bits) {
-            const uint32_t byte = bits[(int64_t)(r0 / RR + rg) * m.ldb + c];
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-              v[w] = ((byte >> (2 * w)) & 1u ? 0x3f80u : 0u) | ((byte >> (2 * w + 1)) & 1u ? 0x3f800000u : 0u);
-          } else {
-            v = *(const VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
-          }
-        } else {
-          v = *(const VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
-        }
-      }
-      char* dst = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
-      if constexpr (RR == 8) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          *(uint16_t*)(dst + (2 * w) * b.pitch) = (uint16_t)(v[w] & 0xffffu);
-          *(uint16_t*)(dst + (2 * w + 1) * b.pitch) = (uint16_t)(v[w] >> 16);
-        }
-      } else {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) *(uint32_t*)(dst + w * b.pitch) = v[w];
-      }
-    }
-    return;
-  }
-  // the RC chunks, several per lane: batches of NB 16-byte loads
-  const int nu = units;
-  for (int u0 = threadIdx.x; u0 < nu; u0 += NB * kNT) {
+  const int nu = (BR / RR) * cw;
+  for (int u0 = tid; u0 < nu; u0 += NB * nt) {
     u32x4 v[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      const int u = min(u0 + i * kNT, nu - 1);
+      const int u = min(u0 + i * nt, nu - 1);
       const int rg = u / cw, c = min(u - rg * cw, cols - 1);
       v[i] = *(const VFL_GLOBAL u32x4*)(g + ((int64_t)min(r0 / RR + rg, rg_last) * cp + c) * 16);
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      const int u = u0 + i * kNT;
+      const int u = u0 + i * nt;
       if (u >= nu) continue;
       const int rg = u / cw, c = u - rg * cw;
       const bool ok = c < cols && (m.rows == 0 || r0 + rg * RR < m.rows);
       const u32x4 x = ok ? v[i] : u32x4{0u, 0u, 0u, 0u};
       char* dst = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
-      if constexpr (RR == 8) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          *(uint16_t*)(dst + (2 * w) * b.pitch) = (uint16_t)(x[w] & 0xffffu);
-          *(uint16_t*)(dst + (2 * w + 1) * b.pitch) = (uint16_t)(x[w] >> 16);
-        }
-      } else {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) *(uint32_t*)(dst + w * b.pitch) = x[w];
-      }
+      for (int w = 0; w < 4; ++w) *(uint32_t*)(dst + w * b.pitch) = x[w];
     }
   }
 }
@@ -1213,6 +1129,13 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_bwd(const BwdJob* __r
   }
   const int rv = min(BR, k.rows - r0);
   if (threadIdx.x >= kNT) {
+    // the ReLU masks of every layer of the chain, each in an LDS buffer of
+    // its own (bf16: the ReLU bits of this group's forward as bytes; float32:
+    // its stashed activations), beside the cut layer
+    for (int q = 0; q < j.nmask; ++q) {
+      if constexpr (sizeof(T) == 2) bits_to_lds<BR>(s, j.ml[q].b, j.ml[q].cols, j.ml[q].m, r0);
+      else rc_to_lds<T, BR>(s, j.ml[q].b, j.ml[q].cols, j.ml[q].m, r0);
+    }
     __syncthreads();
     lds_to_rc<T, BR, true>(s, j.d, j.D, j.d_rc, r0);
     for (int q = 0; q < nd; ++q) {
@@ -1224,14 +1147,6 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_bwd(const BwdJob* __r
   Pipe pp;
   if (nd > 0 || has_gx) prefetch<T>(nd > 0 ? &j.dx[0] : &j.gx, pp);
   const uint32_t wx = warm_l2(j.warm, jp);
-  // the ReLU masks of every layer of the chain, each in an LDS buffer of
-  // its own (bf16: the ReLU bits of this group's forward as bytes; float32:
-  // its stashed activations)
-  for (int q = 0; q < nd; ++q)
-    if (j.dx[q].mask_src.p) {
-      if constexpr (sizeof(T) == 2) bits_to_lds<BR>(s, j.dx[q].mask, j.dx[q].N, j.dx[q].mask_src, r0);
-      else rc_to_lds<T, BR>(s, j.dx[q].mask, j.dx[q].N, j.dx[q].mask_src, r0);
-    }
   // cut-layer backward: through the clip when the row was clipped
   // (d(c v)/dv = c (I - u u^T) with u = v / ||v||), then the ReLU of B's
   // last layer; 16 lanes per row, 4 rows per wavefront at a time

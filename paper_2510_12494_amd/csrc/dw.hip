@@ -539,13 +539,14 @@ __global__ __launch_bounds__(64 * W, 4) void k_dw32(const DwJob* __restrict__ jp
     xcol[i] = glb((const char*)P.X.p) + (int64_t)min(k0 + 16 * i + lr, K - 1) * 16;
   }
   const int64_t dcp = (int64_t)P.D.cp * 16, xcp = (int64_t)P.X.cp * 16;
-  // every wavefront takes the same number of row steps, covering the
-  // group's rows (the RC rows are a multiple of 16 steps, and the delta
-  // rows past the group are zero); loads past the last step repeat it
-  const int nst = ((R + KR - 1) / KR + W - 1) / W;
+  // the group's row steps (the RC rows past the group, up to a multiple of
+  // 128, hold zero deltas) and how many this wavefront takes; loads past
+  // its last step repeat the group's last
+  const int steps = (R + KR - 1) / KR;
+  const int nst = steps > wave ? (steps - wave + W - 1) / W : 0;
   struct Step { u32x4 d[2], x[2]; };
   auto load = [&](int i, Step& f) {
-    const int64_t rg = (int64_t)(wave + W * min(i, nst - 1)) * (KR / CE) + kc;
+    const int64_t rg = (int64_t)min(wave + W * i, steps - 1) * (KR / CE) + kc;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       f.d[h] = *(const VFL_GLOBAL u32x4*)(dcol[h] + rg * dcp);

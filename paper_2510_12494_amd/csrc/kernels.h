@@ -126,7 +126,6 @@ struct RCMat {
 //   input gradient:  * (mask[r][n] > 0) when mask.pitch > 0.
 // Columns of `out` from N up to the next multiple of the MFMA depth are
 // written as zeros, as are rows beyond the group.  rc: RC copy of out.
-// mask_src (k_bwd): the mask is first loaded into `mask` from this matrix.
 // bl: byte offset of the layer's bias row in the kernel's LDS bias table
 // (-1: no bias).  nopad: columns from N on are left as they are (another
 // tensor shares the LDS rows there).
@@ -142,7 +141,7 @@ struct ChainLayer {
   // output leaves such bytes.
   int32_t mask_bits = 0;
   LBuf in, out, mask, mask_out;
-  RCMat rc, mask_src;
+  RCMat rc;
 };
 
 // The biases a chain kernel adds: one contiguous float32 array in global
@@ -265,8 +264,10 @@ struct ActiveJob {
 // (row-major) at the stashed output z (clip backward with norm/cfac when
 // clip), then the chain dx (l = L-1 .. 1, or down to 2 when layer 1's input
 // gradient is a layer product: then the last delta also goes row-major to
-// drm), masks loaded from the stashed ReLU bits (bf16) or RC activations;
-// with tables, gx as in ActiveJob.
+// drm), masks ml loaded from the stashed ReLU bits (bf16) or RC activations;
+// with tables, gx as in ActiveJob.  The last delta of a chain may be several
+// entries of dx, each a range of its columns.
+struct MaskLoad { LBuf b; RCMat m; int32_t cols = 0; };
 struct BwdJob {
   BiasTab bt;
   WarmSet warm;
@@ -277,6 +278,8 @@ struct BwdJob {
   float C = 0.f;
   LBuf d; RCMat d_rc;
   const int32_t* hdr_chk = nullptr; int32_t* err = nullptr;
+  int32_t nmask = 0;
+  MaskLoad ml[kMaxChain];
   int32_t nd = 0;
   ChainLayer dx[kMaxChain];
   int32_t has_gx = 0;

@@ -364,6 +364,45 @@ def test_wide_first_layer_product(widths, s, k, clip):
     _full_check(run, w)
 
 
+@pytest.mark.parametrize("widths,batch,clip", [([1288, 1032, 40], 2056, True), ([2056, 1024], 2048, False)])
+def test_wide_first_layer_large_product(widths, batch, clip):
+    """Layers so wide that B's backward chain would hold fewer than 48 rows
+    per block, at 2048 rows per tick and more: layer 1's input gradient is a
+    product over the group in 256 x 256 tiles (partial tiles of outputs and
+    rows, with two layers fed by the cut-layer delta).  Integers, losses and
+    messages of five groups, whose embeddings show B's updates (lr 0.5)."""
+    w = Workload(name="widelarge", n_rows=4 * batch + 905, dtype="bf16",
+                 A=PartySpec(dense=24, widths=[32, 16]), B=PartySpec(dense=40, widths=widths),
+                 top=TopSpec(widths=[20, 1]), batch=batch, staleness=1, replicas=1, lr=0.5,
+                 clip=1.0 if clip else 0.0, sigma=0.0, clip_emb=clip, clip_grad=clip,
+                 labels="teacher", data_seed=75, init_seed=76, noise_seed=77)
+    run = H.Run(w, w.n_rows, 5)
+    o, recs = run.oracle(_prec(w))
+    _check_ints(run, o, recs)
+    _check_losses(run, recs, w)
+    _check_messages(run, recs, w)
+
+
+@pytest.mark.parametrize("widths,batch,dtype", [([1300, 40], 16400, "bf16"), ([1000, 512, 24], 16500, "bf16"),
+                                                ([700, 96], 8210, "f32")])
+def test_backward_last_delta_in_ranges(widths, batch, dtype):
+    """B's backward with a first layer so wide that its delta is computed and
+    copied out in ranges of 256 columns (six, four and three ranges, the last
+    of 20, 232 and 188 columns), which leaves room for 64 instead of 48 rows
+    per block, or 32 instead of 16 (float32); a ragged last group.  Integers,
+    losses and messages of four groups, whose embeddings show B's updates
+    (lr 0.5)."""
+    w = Workload(name="ranges", n_rows=3 * batch + 77, dtype=dtype,
+                 A=PartySpec(dense=24, widths=[32, 16]), B=PartySpec(dense=33, widths=widths),
+                 top=TopSpec(widths=[20, 1]), batch=batch, staleness=1, replicas=1, lr=0.5,
+                 labels="teacher", data_seed=78, init_seed=79, noise_seed=80)
+    run = H.Run(w, w.n_rows, 4)
+    o, recs = run.oracle(_prec(w))
+    _check_ints(run, o, recs)
+    _check_losses(run, recs, w)
+    _check_messages(run, recs, w)
+
+
 def _wide_three(din, widths, s, k, clip, lr=0.5):
     return Workload(name="widethree", n_rows=1401, dtype="bf16",
                     A=PartySpec(dense=24, widths=[32, 16]), B=PartySpec(dense=din, widths=widths),
