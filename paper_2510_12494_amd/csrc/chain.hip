@@ -397,60 +397,90 @@ __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float
 // inside.  Run by the copy threads.
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// (row, column) of the units u, u + step, ... of a grid of n columns, without
+// a division per unit (about 40 instructions for a divisor known at run
+// time: more than the copy of a unit)
+struct GridWalk {
+  int r, c, n, dr, dc;
+  __device__ __forceinline__ GridWalk(int u, int n_, int step) : r(u / n_), c(u - r * n_), n(n_), dr(step / n_), dc(step - dr * n_) {}
+  __device__ __forceinline__ void next() {
+    r += dr;
+    c += dc;
+    const bool wrap = c >= n;
+    r += wrap;
+    c -= wrap ? n : 0;
+  }
+};
+
+// bits 0 and 1: whether the low and the high bf16 of x is positive (sign bit
+// clear and not zero; a ReLU output is never NaN)
+__device__ __forceinline__ uint32_t positive2(uint32_t x) {
+  const uint32_t p = ((x & 0x7fff7fffu) + 0x7fff7fffu) & ~x;   // bits 15 and 31
+  return ((p >> 15) & 1u) | ((p >> 30) & 2u);
+}
+
 template <typename T, int BR, bool NT>
 __device__ __forceinline__ void lds_to_rc_(char* s, const LBuf& b, int cols, const RCMat& m, int r0,
                                            const LBuf& mask, int mcols) {
   constexpr int RR = Ch<T>::CE;
   const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
   const int cw = (cols + RR - 1) / RR * RR;
-  VFL_GLOBAL char* g = glb((char*)m.p);
   const int64_t cp = m.cp;
+  VFL_GLOBAL char* g = glb((char*)m.p) + (int64_t)(r0 / RR) * cp * 16;   // the block's first row group
   const int nrg = m.rows > 0 ? min(BR / RR, (m.rows - r0) / RR) : BR / RR;   // row groups inside m
   const bool lds_mask = mask.pitch > 0;
+  auto store = [&](int rg, int c, const u32x4& v) {
+    VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + (uint32_t)((rg * (int)cp + c) * 16));
+    if constexpr (NT) __builtin_nontemporal_store(v, dst);
+    else *dst = v;
+  };
   if constexpr (RR == 8) {
+    constexpr int NB = BR > 16 ? 4 : 2;         // units whose LDS reads are in flight together
     const int nc16 = (cw + 15) / 16;
     const int i16 = tid & 15;
-    const int lofs = (i16 >> 2) * b.pitch + (i16 & 3) * 8;   // the lane's source in a 4 x 16 tile
-    // u: 8 x 16 unit, the same for the 16 lanes
-    for (int u = tid >> 4; u < nrg * nc16; u += nt >> 4) {
-      const int rg = u / nc16, c = 16 * (u - rg * nc16) + i16;
-      const char* src = s + b.off + rg * 8 * b.pitch + (c - i16) * 2 + lofs;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)src);
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(src + 4 * b.pitch));
-      const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-      const u32x4 v = u32x4{l2[0], l2[1], h2[0], h2[1]};
-      if (c >= cw) continue;
-      VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
-      if constexpr (NT) __builtin_nontemporal_store(v, dst);
-      else *dst = v;
-      if ((m.bits || lds_mask) && c < mcols) {
-        // the chunk's positive rows, one bit each (ReLU outputs: a row is
-        // positive when its sign bit is clear and it is not zero)
-        uint32_t byte = 0;
+    const char* src = s + b.off + (i16 >> 2) * b.pitch + (i16 & 3) * 8;   // the lane's source in unit (0, 0)
+    VFL_GLOBAL uint8_t* bits = glb(m.bits) + (int64_t)(r0 / RR) * m.ldb;
+    // w: 8 x 16 unit, the same for the 16 lanes
+    for (GridWalk w(tid >> 4, nc16, nt >> 4); w.r < nrg;) {
+      int rg[NB], c[NB];
+      u32x4 v[NB];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t x = v[w] & 0xffffu, y = v[w] >> 16;
-          byte |= (uint32_t)(x != 0 && !(x & 0x8000u)) << (2 * w);
-          byte |= (uint32_t)(y != 0 && !(y & 0x8000u)) << (2 * w + 1);
+      for (int i = 0; i < NB; ++i) {
+        rg[i] = w.r;
+        c[i] = 16 * w.c + i16;
+        w.next();
+        const char* p = src + min(rg[i], nrg - 1) * 8 * b.pitch + (c[i] - i16) * 2;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * b.pitch));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        v[i] = u32x4{l2[0], l2[1], h2[0], h2[1]};
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (rg[i] >= nrg || c[i] >= cw) continue;
+        store(rg[i], c[i], v[i]);
+        if ((m.bits || lds_mask) && c[i] < mcols) {
+          // the chunk's positive rows, one bit each
+          const uint32_t byte = positive2(v[i][0]) | positive2(v[i][1]) << 2 | positive2(v[i][2]) << 4 |
+                                positive2(v[i][3]) << 6;
+          if (m.bits) bits[rg[i] * m.ldb + c[i]] = (uint8_t)byte;
+          if (lds_mask) s[mask.off + rg[i] * mask.pitch + c[i]] = (char)byte;
         }
-        if (m.bits) glb(m.bits)[(int64_t)(r0 / RR + rg) * m.ldb + c] = (uint8_t)byte;
-        if (lds_mask) s[mask.off + rg * mask.pitch + c] = (char)byte;
       }
     }
   } else {
-    for (int u = tid; u < nrg * cw; u += nt) {
-      const int rg = u / cw, c = u - rg * cw;
+    for (GridWalk w(tid, cw, nt); w.r < nrg; w.next()) {
+      const int rg = w.r, c = w.c;
       const char* src = s + b.off + rg * RR * b.pitch + c * (int)sizeof(T);
       u32x4 v;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) v[w] = *(const uint32_t*)(src + w * b.pitch);
-      VFL_GLOBAL u32x4* dst = (VFL_GLOBAL u32x4*)(g + ((int64_t)(r0 / RR + rg) * cp + c) * 16);
-      if constexpr (NT) __builtin_nontemporal_store(v, dst);
-      else *dst = v;
+      for (int e = 0; e < 4; ++e) v[e] = *(const uint32_t*)(src + e * b.pitch);
+      store(rg, c, v);
       if (lds_mask && c < mcols) {
         uint32_t byte = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) byte |= (uint32_t)(__uint_as_float(v[w]) > 0.f) << w;
+        for (int e = 0; e < 4; ++e) byte |= (uint32_t)(__uint_as_float(v[e]) > 0.f) << e;
         s[mask.off + rg * mask.pitch + c] = (char)byte;
       }
     }
@@ -499,8 +529,8 @@ __device__ __forceinline__ void bits_to_lds(char* s, const LBuf& b, int cols, co
   const int nc = (cols + 15) / 16;
   const int rg_last = m.rows > 0 ? max(m.rows / 8 - 1, 0) : (1 << 30);
   const VFL_GLOBAL uint8_t* bits = glb((const uint8_t*)m.bits);
-  for (int u = (int)threadIdx.x - kNT; u < (BR / 8) * nc; u += (int)blockDim.x - kNT) {
-    const int rg = u / nc, c = 16 * (u - rg * nc);
+  for (GridWalk w((int)threadIdx.x - kNT, nc, (int)blockDim.x - kNT); w.r < BR / 8; w.next()) {
+    const int rg = w.r, c = 16 * w.c;
     const u32x4 v = __builtin_nontemporal_load((const VFL_GLOBAL u32x4*)(bits + (int64_t)min(r0 / 8 + rg, rg_last) * m.ldb + c));
     *(u32x4*)(s + b.off + rg * b.pitch + c) = v;
   }
@@ -552,11 +582,9 @@ __device__ __forceinline__ void lds_to_rows(const char* s, const LBuf& b, int co
   constexpr int CE = Ch<T>::CE;
   const int nch = (cols + CE - 1) / CE;
   VFL_GLOBAL char* d = glb((char*)dst);
-  for (int u = tid; u < rv * nch; u += COPY ? (int)blockDim.x - kNT : kNT) {
-    const int r = u / nch, ch = u % nch;
-    *(VFL_GLOBAL u32x4*)(d + ((int64_t)(r0 + r) * ld + ch * CE) * sizeof(T)) =
-        *(const u32x4*)(s + b.off + r * b.pitch + ch * 16);
-  }
+  for (GridWalk w(tid, nch, COPY ? (int)blockDim.x - kNT : kNT); w.r < rv; w.next())
+    *(VFL_GLOBAL u32x4*)(d + ((int64_t)(r0 + w.r) * ld + w.c * CE) * sizeof(T)) =
+        *(const u32x4*)(s + b.off + w.r * b.pitch + w.c * 16);
 }
 
 // an embedding id clamped into [0, V)
@@ -717,8 +745,8 @@ __device__ __forceinline__ float rows_reduce(const float (&v)[P], int lane) {
 // factor.  16 lanes per row (4 rows per wavefront at a time), each lane on
 // the 4-column groups cg, cg + 16, ...; the noise is keyed by the row's
 // sample id, two groups' Philox blocks at a time (independent instruction
-// streams, so one lane keeps the VALU busy).  Run by nwaves wavefronts, this
-// one the wave-th of them.
+// streams, so one lane keeps the VALU busy).  Block rows lo .. hi - 1, by
+// nwaves wavefronts, this one the wave-th of them.
 template <typename V>
 __device__ __forceinline__ void msg_ld4(const char* row, int g, int D, float (&x)[4]) {
   ld4<V>(row + 4 * g * (int)sizeof(V), x);
@@ -738,13 +766,14 @@ __device__ __forceinline__ void msg_st4(VFL_GLOBAL T* o, int g, int D, const flo
 template <typename T, typename V, int BR>
 __device__ __forceinline__ void msg_rows(const char* s, const LBuf& src, int D, const MsgOp& m,
                                          uint32_t step, int64_t sample0, void* out, int64_t ldo,
-                                         float* norm, float* cfac, int r0, int rv, int wave, int nwaves) {
+                                         float* norm, float* cfac, int r0, int rv, int wave, int nwaves,
+                                         int lo = 0, int hi = BR) {
   const int lane = threadIdx.x & 63;
   const int sub = lane >> 4, cg = lane & 15;
   const int ngrp = (D + 3) >> 2;
-  for (int rb = 0; rb < BR; rb += 4 * nwaves) {
+  for (int rb = lo; rb < hi; rb += 4 * nwaves) {
     const int r = rb + wave * 4 + sub;
-    if (r >= rv) continue;   // uniform within the row's 16 lanes
+    if (r >= min(rv, hi)) continue;   // uniform within the row's 16 lanes
     const char* row = s + src.off + r * src.pitch;
     float ss = 0.f;
     for (int g = cg; g < ngrp; g += 16) {
@@ -866,12 +895,16 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   float* wpart = yl + BR;                     // logit weight gradient [kNW][Hd4]
   float* wl = wpart + kNW * Hd4;              // {loss, dl} [kNW][2]
   const bool gextra = j.gextra != 0;
-  // the message with clip or noise: by the copy wavefronts beside A's
-  // input-gradient chain, or by all of them where there is none
+  // the message with clip or noise: its first rows by the copy wavefronts
+  // beside A's input-gradient chain, the others by the product wavefronts
+  // after it (64 rows of 128 columns with Philox noise: the copy wavefronts
+  // alone took 4.7 us longer than the chain); by all of them together where
+  // there is no chain
   const bool msg_all = nda == 0 && !has_gx;
-  auto send_noised = [&](int w0, int nw) {
+  constexpr int kCopyRows = 16 * (RT > 1 ? RT / 2 : 1);
+  auto send_noised = [&](int w0, int nw, int lo, int hi) {
     msg_rows<T, float, BR>(s, j.msg, j.dB, j.m, (uint32_t)k.group, k.row0, j.ring, j.ldring, nullptr, nullptr,
-                           r0, rv, wave - w0, nw);
+                           r0, rv, wave - w0, nw, lo, hi);
   };
   if (threadIdx.x >= kNT) {
     const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
@@ -884,8 +917,8 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       const VFL_GLOBAL T* zb = glb((const T*)j.zb);
       const VFL_GLOBAL float* y = glb(cc.labels) + k.in_off + r0;
       const float py = y[min(tid, rv - 1)];
-      for (int u = tid; u < BR * nch; u += nt) {
-        const int r = u / nch, ch = u % nch, c = ch * CE;
+      for (GridWalk w(tid, nch, nt); w.r < BR; w.next()) {
+        const int r = w.r, c = w.c * CE;
         u32x4 v = u32x4{0u, 0u, 0u, 0u};
         if (r < rv && c < dB) v = mask_tail<T>(*(const VFL_GLOBAL u32x4*)(zb + (int64_t)(r0 + r) * j.ldzb + c), dB - c);
         *(u32x4*)(s + j.cat.off + r * j.cat.pitch + (dA + c) * (int)sizeof(T)) = v;
@@ -921,7 +954,8 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     }
     __syncthreads();
     lds_to_rc<T, BR>(s, j.dc.out, j.dA, j.dc.rc, r0);
-    if (gextra) send_noised(msg_all ? 0 : kNW, (int)(blockDim.x >> 6) - (msg_all ? 0 : kNW));
+    if (gextra && msg_all) send_noised(0, (int)(blockDim.x >> 6), 0, BR);
+    else if (gextra) send_noised(kNW, (int)(blockDim.x >> 6) - kNW, 0, kCopyRows);
     else lds_to_rows<T, BR, true>(s, j.msg, j.dB, j.ring, j.ldring, r0, rv);
     for (int q = 0; q < nda; ++q) {
       __syncthreads();
@@ -1098,7 +1132,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
       }
     });
     __syncthreads();
-    if (gextra && msg_all) send_noised(0, (int)(blockDim.x >> 6));
+    if (gextra && msg_all) send_noised(0, (int)(blockDim.x >> 6), 0, BR);
   }
   // A's input-gradient chain
   for (int q = 0; q < nda; ++q) {
@@ -1106,6 +1140,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     __syncthreads();
   }
   if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
+  if (gextra && !msg_all && kCopyRows < BR) send_noised(0, kNW, kCopyRows, BR);
 }
 
 template <typename T, int RT>
