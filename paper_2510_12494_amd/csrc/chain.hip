@@ -163,21 +163,20 @@ __device__ __forceinline__ int tiles_of(int N) {
   return (N + KS - 1) / KS * (KS / 16);
 }
 
-// the loads of group g of a pass (tiles tile[]) of an operand W with kst
-// K steps and ntl tiles into d: one contiguous 1 KB fragment per tile and
-// step of the packed operand.  Loads are unconditional: tiles past the
-// operand's last are clamped to it, steps past K to its last step (never
-// used; re-reading lines already fetched keeps them off the L2, and a
-// conditional load would make the compiler wait for it on the spot).
-__device__ __forceinline__ void wgroup(const void* Wp, int kst, int ntl, const int (&tile)[kNTW], int g,
-                                       u32x4 (&d)[PF][kNTW]) {
+// The loads of two MFMA steps of a pass's tiles at p[] into d: one contiguous
+// 1 KB fragment per tile and step of the packed operand, each a load with a
+// uniform base, the lane's 32-bit offset and an immediate.  Loads are
+// unconditional (a conditional load would make the compiler wait for it on
+// the spot): tiles past the operand's last are clamped to it, and steps past
+// K read what follows the tile (the next tile, or the slack behind the
+// operand), never used.
+template <int OFS>
+__device__ __forceinline__ void wgroup(const VFL_GLOBAL char* const (&p)[kNTW], u32x4 (&d)[PF][kNTW]) {
   const uint32_t lo = (threadIdx.x & 63) * 16;
 #pragma unroll
-  for (int j = 0; j < kNTW; ++j) {
-    const VFL_GLOBAL char* base = glb((const char*)Wp) + (int64_t)min(tile[j], ntl - 1) * kst * 1024 + lo;
+  for (int j = 0; j < kNTW; ++j)
 #pragma unroll
-    for (int q = 0; q < PF; ++q) d[q][j] = *(const VFL_GLOBAL u32x4*)(base + (int64_t)min(g * PF + q, kst - 1) * 1024);
-  }
+    for (int q = 0; q < PF; ++q) d[q][j] = *(const VFL_GLOBAL u32x4*)((p[j] + (OFS + q) * 1024) + lo);
 }
 
 // the tiles of a wavefront's pass: wave + kNW * (kNTW * pass + j)
@@ -187,16 +186,23 @@ __device__ __forceinline__ void pass_tiles(int pass, int (&tile)[kNTW]) {
   for (int j = 0; j < kNTW; ++j) tile[j] = wave + kNW * (kNTW * pass + j);
 }
 
+// where the fragments of a pass's tiles start in the packed operand W
+__device__ __forceinline__ void pass_bases(const void* W, int kst, int ntl, int pass, const VFL_GLOBAL char* (&p)[kNTW]) {
+  int tile[kNTW];
+  pass_tiles(pass, tile);
+#pragma unroll
+  for (int j = 0; j < kNTW; ++j)
+    p[j] = glb((const char*)uniform_ptr((const char*)W + (uint64_t)(uint32_t)(min(tile[j], ntl - 1) * kst) * 1024));
+}
+
 // start the loads of groups 0 and 1 of L's first pass
 template <typename T>
 __device__ __forceinline__ void prefetch(const ChainLayer* L, Pipe& p) {
-  int tile[kNTW];
-  pass_tiles(0, tile);
   const VFL_CONST ChainLayer& C = cst(*(const ChainLayer*)uniform_ptr(L));
-  const void* W = uniform_ptr(C.W);
-  const int kst = uniform(C.kst), ntl = uniform(tiles_of<T>(C.N));
-  wgroup(W, kst, ntl, tile, 0, p.wa);
-  wgroup(W, kst, ntl, tile, 1, p.wb);
+  const VFL_GLOBAL char* base[kNTW];
+  pass_bases(uniform_ptr(C.W), uniform(C.kst), uniform(tiles_of<T>(C.N)), 0, base);
+  wgroup<0>(base, p.wa);
+  wgroup<PF>(base, p.wb);
 }
 
 // Copy of a chain kernel's bias table into LDS (see BiasTab).
@@ -235,7 +241,18 @@ __device__ __forceinline__ uint32_t warm_l2(const WarmSet& w, const void* dummy)
 // bias or past N), for every row of the block and every column below N
 // rounded up to the MFMA depth.  On entry p holds groups 0 and 1 of L's
 // first pass; on return, groups 0 and 1 of `next`'s (nullable).
-template <typename T, int RT, typename Epi>
+// Weight addresses are one uniform pointer per tile of the pass, advanced by
+// the groups of an iteration, instead of a step and a tile clamped per load:
+// about 45 scalar instructions less per refill.  500-1024-512-128 at 48 rows
+// per block: k_fwd 136 -> 125 us, k_bwd 87 -> 84; ten 256-wide layers at 32
+// rows: k_active 72 -> 70.6.
+// FAST: load groups with both tiles and all steps run without a branch between
+// their products (the same k_fwd 125 -> 120), which takes about 30 registers
+// more.  For kernels at 48 rows per block alone: at 16 and 32 rows the
+// registers are what lets two workgroups, or another kernel's, share the CU
+// (k_active with it at 32 rows: 70.6 -> 68 us by itself, but the two-party
+// tick with 65536-row tables 152 -> 156), and at 64 rows it spills.
+template <typename T, int RT, bool FAST, typename Epi>
 __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pipe& p,
                                          const ChainLayer* next, Epi&& epi) {
   constexpr int NTW = kNTW;
@@ -258,62 +275,77 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
   const VFL_CONST ChainLayer& CN = cst(next ? *next : L);
   const void* nW = uniform_ptr(CN.W);
   const int nkst = uniform(CN.kst), nntl = uniform(tiles_of<T>(CN.N));
+  const char* xbase = s + in.off + lr * in.pitch + kc * 16;
 #pragma unroll 1
   for (int pass = 0; pass < npass; ++pass) {
-    int tile[NTW], ntile[NTW];
+    int tile[NTW];
     pass_tiles(pass, tile);
-    // where the loads go once this pass's groups are all issued: the next
-    // pass, or the next product's first
+    // this pass's fragments (groups 0 and 1 are in p), and where the loads
+    // go once its groups are all issued: the next pass, or the next
+    // product's first
     const bool more = pass + 1 < npass;
-    pass_tiles(more ? pass + 1 : 0, ntile);
-    const void* rW = more ? W : nW;
-    const int rkst = more ? nks : nkst, rntl = more ? ntl : nntl;
+    const VFL_GLOBAL char* wp[NTW];
+    const VFL_GLOBAL char* np[NTW];
+    pass_bases(W, nks, ntl, pass, wp);
+    pass_bases(more ? W : nW, more ? nks : nkst, more ? ntl : nntl, more ? pass + 1 : 0, np);
     f32x4 acc[NTW][RT];
 #pragma unroll
     for (int j = 0; j < NTW; ++j)
 #pragma unroll
       for (int t = 0; t < RT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto step = [&](int ks, const u32x4 (&w)[NTW]) {
-      if (ks >= nks) return;
-      u32x4 xf[RT];
+    auto xread = [&](int ks, u32x4 (&x)[RT]) {
 #pragma unroll
-      for (int t = 0; t < RT; ++t)
-        xf[t] = *(const u32x4*)(s + in.off + (t * 16 + lr) * in.pitch + (ks * 4 + kc) * 16);
+      for (int t = 0; t < RT; ++t) x[t] = *(const u32x4*)(xbase + t * 16 * in.pitch + ks * 64);
+    };
+    auto mma = [&](int j, const u32x4& w, const u32x4 (&x)[RT]) {
 #pragma unroll
-      for (int j = 0; j < NTW; ++j) {
-        if (tile[j] >= ntl) continue;
+      for (int t = 0; t < RT; ++t) {
+        if constexpr (sizeof(T) == 2) {
+          acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x[t]), acc[j][t], 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) {
-          if constexpr (sizeof(T) == 2) {
-            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, w[j]), __builtin_bit_cast(bf16x8, xf[t]), acc[j][t], 0, 0, 0);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                  __uint_as_float(w[j][e]), __uint_as_float(xf[t][e]), acc[j][t], 0, 0, 0);
-          }
+          for (int e = 0; e < 4; ++e)
+            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                __uint_as_float(w[e]), __uint_as_float(x[t][e]), acc[j][t], 0, 0, 0);
         }
       }
     };
-    auto group = [&](int g, const u32x4 (&w)[PF][NTW]) {
+    // two groups of an iteration, each refilled as soon as its products
+    // have read it; the iteration's last loads are the next pass's when
+    // this one has no further group
+    const bool two = tile[NTW - 1] < ntl;
+    auto group = [&](int k0, const u32x4 (&w)[PF][NTW]) {
+      if constexpr (FAST) {
+        if (two && k0 + PF <= nks) {
 #pragma unroll
-      for (int q = 0; q < PF; ++q) step(g * PF + q, w[q]);
-    };
-    // group g of this pass into w, or group g - ng of the next pass/product
-    auto refill = [&](int g, u32x4 (&w)[PF][NTW]) {
-      const bool cur = g < ng;
-      int tt[NTW];
+          for (int q = 0; q < PF; ++q) {
+            u32x4 x[RT];
+            xread(k0 + q, x);
 #pragma unroll
-      for (int j = 0; j < NTW; ++j) tt[j] = cur ? tile[j] : ntile[j];
-      wgroup(cur ? W : rW, cur ? nks : rkst, cur ? ntl : rntl, tt, cur ? g : g - ng, w);
+            for (int j = 0; j < NTW; ++j) mma(j, w[q][j], x);
+          }
+          return;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < PF; ++q) {
+        if (k0 + q >= nks || tile[0] >= ntl) continue;
+        u32x4 x[RT];
+        xread(k0 + q, x);
+        mma(0, w[q][0], x);
+        if (two) mma(1, w[q][1], x);
+      }
     };
 #pragma unroll 1
-    for (int g = 0; g < ng; g += 2) {
-      group(g, p.wa);
-      refill(g + 2, p.wa);
-      group(g + 1, p.wb);
-      refill(g + 3, p.wb);
+    for (int ks = 0; ks < ng * PF; ks += 2 * PF) {
+      const bool last = ks + 2 * PF >= ng * PF;
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) wp[j] = last ? np[j] : wp[j] + 2 * PF * 1024;
+      group(ks, p.wa);
+      wgroup<0>(wp, p.wa);
+      group(ks + PF, p.wb);
+      wgroup<PF>(wp, p.wb);
     }
 #pragma unroll
     for (int j = 0; j < NTW; ++j) {
@@ -329,7 +361,7 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
 // Forward or input-gradient layer into LDS (see ChainLayer).
 // MB: the mask (when there is one) holds a byte per RR rows and column
 // instead of elements
-template <typename T, int RT, bool MB = false>
+template <typename T, int RT, bool FAST, bool MB = false>
 __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, Pipe& p,
                                           const ChainLayer* next) {
   const int N = L.N;
@@ -361,17 +393,17 @@ __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, 
     // below N or all past it
     if (!nopad || n < N) st4<T>(lp(s, out, r, n * (int)sizeof(T)), v);
   };
-  block_mm<T, RT>(s, L, p, next, epi);
+  block_mm<T, RT, FAST>(s, L, p, next, epi);
 }
 
 // Input gradient of the embedding columns of a bottom input: float32 rows
 // of gx (block rows below rv).
-template <typename T, int RT>
+template <typename T, int RT, bool FAST>
 __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float* gx, int64_t ldgx,
                                        int r0, int rv, Pipe& p) {
   const int N = L.N;
   VFL_GLOBAL float* gxg = glb(gx);
-  block_mm<T, RT>(s, L, p, nullptr, [&](int r, int n, const f32x4& a, const f32x4&) {
+  block_mm<T, RT, FAST>(s, L, p, nullptr, [&](int r, int n, const f32x4& a, const f32x4&) {
     if (r >= rv) return;
     VFL_GLOBAL float* dst = gxg + (int64_t)(r0 + r) * ldgx + n;
     if (n + 4 <= N) {
@@ -849,7 +881,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_fwd(const FwdJob* __r
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
   for (int l = 0; l < nL; ++l) {
-    run_layer<T, RT>(s, j.l[l], rv, pp, l + 1 < nL ? &j.l[l + 1] : nullptr);
+    run_layer<T, RT, RT == 3>(s, j.l[l], rv, pp, l + 1 < nL ? &j.l[l + 1] : nullptr);
     __syncthreads();
   }
   if (j.publish)
@@ -862,6 +894,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
                                                 TickRef tr) {
   constexpr int BR = 16 * RT;
   constexpr int CE = Ch<T>::CE, KS = Ch<T>::KS;
+  constexpr bool FAST = RT == 3;
   extern __shared__ __attribute__((aligned(16))) char s[];
   const ActiveJob& j = *jp;
   const int LA = cst(j).LA;
@@ -988,12 +1021,12 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   __syncthreads();
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
   for (int l = 0; l < LA; ++l) {
-    run_layer<T, RT>(s, j.fa[l], rv, pp, l + 1 < LA ? &j.fa[l + 1] : &j.ft[0]);
+    run_layer<T, RT, FAST>(s, j.fa[l], rv, pp, l + 1 < LA ? &j.fa[l + 1] : &j.ft[0]);
     __syncthreads();
   }
   // top hidden layers
   for (int q = 0; q < H; ++q) {
-    run_layer<T, RT>(s, j.ft[q], rv, pp, q + 1 < H ? &j.ft[q + 1] : (H > 1 ? &j.dt[0] : &j.dc));
+    run_layer<T, RT, FAST>(s, j.ft[q], rv, pp, q + 1 < H ? &j.ft[q + 1] : (H > 1 ? &j.dt[0] : &j.dc));
     __syncthreads();
   }
   // logit + BCE (Eq. 1), dl = sigmoid(l) - y, or for regression the
@@ -1095,7 +1128,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   }
   // top input-gradient chain
   for (int q = 0; q + 1 < H; ++q) {
-    run_layer<T, RT, true>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc);
+    run_layer<T, RT, FAST, true>(s, j.dt[q], rv, pp, q + 2 < H ? &j.dt[q + 1] : &j.dc);
     __syncthreads();
   }
   // concat product: A's cut delta and the gradient message for B
@@ -1105,7 +1138,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     const LBuf ob = j.dc.out, mk = j.dc.mask, msg = j.msg;
     const bool maskA = mk.pitch > 0;
     const int msg_end = dA + (j.dB + CE - 1) / CE * CE;   // the message's columns in whole chunks
-    block_mm<T, RT>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
+    block_mm<T, RT, FAST>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
                     [&](int r, int n, const f32x4& a, const f32x4&) {
       const bool ok = r < rv;
       if (n < dA) {   // dA is a multiple of 8: all four columns are A's
@@ -1136,10 +1169,10 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
   }
   // A's input-gradient chain
   for (int q = 0; q < nda; ++q) {
-    run_layer<T, RT, true>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr));
+    run_layer<T, RT, FAST, true>(s, j.da[q], rv, pp, q + 1 < nda ? &j.da[q + 1] : (has_gx ? &j.gx : nullptr));
     __syncthreads();
   }
-  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
+  if (has_gx) run_gx<T, RT, FAST>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
   if (gextra && !msg_all && kCopyRows < BR) send_noised(0, kNW, kCopyRows, BR);
 }
 
@@ -1233,10 +1266,10 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 2)) void k_bwd(const BwdJob* __r
   asm volatile("" ::"v"(wx));   // the L2 fetches have landed with the inputs
   for (int q = 0; q < nd; ++q) {
     const ChainLayer& L = j.dx[q];
-    run_layer<T, RT, sizeof(T) == 2>(s, L, rv, pp, q + 1 < nd ? &j.dx[q + 1] : (has_gx ? &j.gx : nullptr));
+    run_layer<T, RT, RT == 3, sizeof(T) == 2>(s, L, rv, pp, q + 1 < nd ? &j.dx[q + 1] : (has_gx ? &j.gx : nullptr));
     __syncthreads();
   }
-  if (has_gx) run_gx<T, RT>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
+  if (has_gx) run_gx<T, RT, RT == 3>(s, j.gx, j.gxp, j.ldgx, r0, rv, pp);
   if (j.drm) {
     // the last delta of the chain, row-major, for the layer product below it
     const LBuf last = nd > 0 ? j.dx[nd - 1].out : j.d;
