@@ -236,7 +236,7 @@ __device__ __forceinline__ uint32_t warm_l2(const WarmSet& w, const void* dummy)
 }
 
 // out[r][n] = epi(r, n, sum_k in[r][k] W[n][k], bias) for the block's rows:
-// epi(r, n, acc, bias) receives block row r, output columns n .. n+3 (n a
+// epi(lr, n, acc, bias) receives block rows lr + 16 t, output columns n .. n+3 (n a
 // multiple of 4; bias[i] = bias[n + i] from the LDS table, zero without a
 // bias or past N), for every row of the block and every column below N
 // rounded up to the MFMA depth.  On entry p holds groups 0 and 1 of L's
@@ -352,8 +352,7 @@ __device__ __forceinline__ void block_mm(const char* s, const ChainLayer& L, Pip
       if (tile[j] >= ntl) continue;
       const int n = tile[j] * 16 + 4 * kc;
       const f32x4 bv = bl >= 0 ? *(const f32x4*)(s + bl + 4 * n) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < RT; ++t) epi(t * 16 + lr, n, acc[j][t], bv);
+      epi(lr, n, acc[j], bv);
     }
   }
 }
@@ -367,31 +366,80 @@ __device__ __forceinline__ void run_layer(char* s, const ChainLayer& L, int rv, 
   const int N = L.N;
   const bool relu = L.relu != 0, msk = L.mask.pitch > 0, nopad = L.nopad != 0;
   const LBuf out = L.out, mk = L.mask;
-  // branch-free: every condition is a select (a short-circuit test here
-  // compiles to one exec-mask branch per element)
-  auto epi = [&](int r, int n, const f32x4& a, const f32x4& b) {
-    float m[4] = {1.f, 1.f, 1.f, 1.f}, v[4];
-    if constexpr (MB) {
-      if (msk) {
-        // the 4 columns' bytes of r's row group in one word
-        const uint32_t w = *(const uint32_t*)(s + mk.off + (r / Ch<T>::CE) * mk.pitch + n);
+  // Full blocks and widths of whole MFMA depths need no test per element:
+  // an add, the max or the mask, the conversion and one store.  The epilogue
+  // is vector work that the two product wavefronts of a SIMD mostly do at the
+  // same time, so its instructions count beside the MFMAs' cycles (500-1024-512-128
+  // at 48 rows per block: k_fwd 121 -> 115 us, k_bwd 83 -> 81; ten 256-wide layers:
+  // k_active 70 -> 66, the tick 3 % shorter).  Not at 16 rows per block, where
+  // it spilled in k_active and gained nothing elsewhere (20.3 -> 22.0 us).
+  const bool whole = RT > 1 && rv == 16 * RT && N % Ch<T>::KS == 0;
+  auto epi = [&](int lr, int n, const f32x4 (&a)[RT], const f32x4& b) {
+    char* o = lp(s, out, lr, n * (int)sizeof(T));
+    const int opitch = 16 * out.pitch;
+    if (whole && (MB || !msk)) {
+      if (MB && msk) {
+        // the 4 columns' bytes of the row's row group in one word, the row's
+        // bit of each stretched over the element (the masked value is +0)
+        const char* mp = s + mk.off + (lr / Ch<T>::CE) * mk.pitch + n;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = (w >> (8 * i + r % Ch<T>::CE)) & 1u ? 1.f : 0.f;
+        for (int t = 0; t < RT; ++t) {
+          const uint32_t w = *(const uint32_t*)(mp + t * (16 / Ch<T>::CE) * mk.pitch) >> (lr % Ch<T>::CE);
+          float v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float x0 = a[t][i] + b[i];
+            const float x = relu ? fmaxf(x0, 0.f) : x0;
+            v[i] = __uint_as_float(__float_as_uint(x) & (uint32_t)((int32_t)(w << (31 - 8 * i)) >> 31));
+          }
+          st4<T>(o + t * opitch, v);
+        }
+      } else if (relu) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          float v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = fmaxf(a[t][i] + b[i], 0.f);
+          st4<T>(o + t * opitch, v);
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          float v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = a[t][i] + b[i];
+          st4<T>(o + t * opitch, v);
+        }
       }
-    } else {
-      if (msk) ld4<T>(lp(s, mk, r, n * (int)sizeof(T)), m);
+      return;
     }
-    const bool rok = r < rv;
+    // branch-free: every condition is a select (a short-circuit test here
+    // compiles to one exec-mask branch per element)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x0 = a[i] + b[i];
-      const float x = relu ? fmaxf(x0, 0.f) : x0;
-      const bool keep = rok & (n + i < N) & (m[i] > 0.f);
-      v[i] = keep ? x : 0.f;
+    for (int t = 0; t < RT; ++t) {
+      const int r = t * 16 + lr;
+      float m[4] = {1.f, 1.f, 1.f, 1.f}, v[4];
+      if constexpr (MB) {
+        if (msk) {
+          const uint32_t w = *(const uint32_t*)(s + mk.off + (r / Ch<T>::CE) * mk.pitch + n);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) m[i] = (w >> (8 * i + r % Ch<T>::CE)) & 1u ? 1.f : 0.f;
+        }
+      } else {
+        if (msk) ld4<T>(lp(s, mk, r, n * (int)sizeof(T)), m);
+      }
+      const bool rok = r < rv;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float x0 = a[t][i] + b[i];
+        const float x = relu ? fmaxf(x0, 0.f) : x0;
+        const bool keep = rok & (n + i < N) & (m[i] > 0.f);
+        v[i] = keep ? x : 0.f;
+      }
+      // n is a multiple of 4 and a nopad N of 8: the four columns are all
+      // below N or all past it
+      if (!nopad || n < N) st4<T>(o + t * opitch, v);
     }
-    // n is a multiple of 4 and a nopad N of 8: the four columns are all
-    // below N or all past it
-    if (!nopad || n < N) st4<T>(lp(s, out, r, n * (int)sizeof(T)), v);
   };
   block_mm<T, RT, FAST>(s, L, p, next, epi);
 }
@@ -403,15 +451,20 @@ __device__ __forceinline__ void run_gx(const char* s, const ChainLayer& L, float
                                        int r0, int rv, Pipe& p) {
   const int N = L.N;
   VFL_GLOBAL float* gxg = glb(gx);
-  block_mm<T, RT, FAST>(s, L, p, nullptr, [&](int r, int n, const f32x4& a, const f32x4&) {
-    if (r >= rv) return;
-    VFL_GLOBAL float* dst = gxg + (int64_t)(r0 + r) * ldgx + n;
-    if (n + 4 <= N) {
-      *(VFL_GLOBAL f32x4*)dst = a;
-    } else {
+  block_mm<T, RT, FAST>(s, L, p, nullptr, [&](int lr, int n, const f32x4 (&acc)[RT], const f32x4&) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (n + i < N) dst[i] = a[i];
+    for (int t = 0; t < RT; ++t) {
+      const int r = t * 16 + lr;
+      const f32x4& a = acc[t];
+      if (r >= rv) continue;
+      VFL_GLOBAL float* dst = gxg + (int64_t)(r0 + r) * ldgx + n;
+      if (n + 4 <= N) {
+        *(VFL_GLOBAL f32x4*)dst = a;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < N) dst[i] = a[i];
+      }
     }
   });
 }
@@ -1139,7 +1192,11 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
     const bool maskA = mk.pitch > 0;
     const int msg_end = dA + (j.dB + CE - 1) / CE * CE;   // the message's columns in whole chunks
     block_mm<T, RT, FAST>(s, j.dc, pp, nda > 0 ? &j.da[0] : (has_gx ? &j.gx : nullptr),
-                    [&](int r, int n, const f32x4& a, const f32x4&) {
+                    [&](int lr, int n, const f32x4 (&acc)[RT], const f32x4&) {
+#pragma unroll
+     for (int t = 0; t < RT; ++t) {
+      const int r = t * 16 + lr;
+      const f32x4& a = acc[t];
       const bool ok = r < rv;
       if (n < dA) {   // dA is a multiple of 8: all four columns are A's
         uint32_t w = ~0u;
@@ -1148,7 +1205,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = (ok && ((w >> (8 * i + r % CE)) & 1u)) ? a[i] : 0.f;
         st4<T>(lp(s, ob, r, n * (int)sizeof(T)), v);
-        return;
+        continue;
       }
       // the message to LDS (float32 when clip or noise follow), where the
       // copy wavefronts take it from
@@ -1163,6 +1220,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
         if (gextra) st4<float>(lp(s, msg, r, (n - dA) * 4), v);
         else st4<T>(lp(s, msg, r, (n - dA) * (int)sizeof(T)), v);
       }
+     }
     });
     __syncthreads();
     if (gextra && msg_all) send_noised(0, (int)(blockDim.x >> 6), 0, BR);
