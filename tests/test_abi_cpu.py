@@ -114,6 +114,32 @@ def test_create_failures_report_their_reason(V):
     assert V.vfl_last_error(None) == ""
 
 
+@pytest.mark.parametrize("dtype,A,B,last", [
+    ("bf16", [None, 16], [16, 16], 1536), ("bf16", [16, 16], [None, 16], 4448),
+    ("bf16", [16, 16], [512, None, 16], 3968), ("bf16", [16, 16], [16, None], 4448),
+    ("f32", [None, 16], [16, 16], 800), ("f32", [16, 16], [None, 16], 1248),
+    ("f32", [16, 16], [512, None, 16], 736), ("f32", [16, 16], [16, None], 2352)])
+def test_widest_accepted_layers(V, dtype, A, B, last):
+    """The widest bottom layers a configuration may have do not depend on how
+    the kernels lay out LDS: the limits of the first release stay (8 columns
+    more are refused), whatever smaller buffers a kernel would manage with."""
+    from vfl_synth.workloads import Workload, PartySpec, TopSpec
+    from paper_2510_12494_amd.session import bottom_spec, top_spec, opts
+
+    def accepted(n):
+        fill = lambda ws: [n if x is None else x for x in ws]
+        w = Workload(name="limit", n_rows=64, dtype=dtype, A=PartySpec(dense=24, widths=fill(A)),
+                     B=PartySpec(dense=40, widths=fill(B)), top=TopSpec(widths=[20, 1]), batch=64,
+                     staleness=1, replicas=1, lr=0.1)
+        try:
+            return V.vfl_workspace_size(bottom_spec(w.A), bottom_spec(w.B), top_spec(w.top), opts(w)) > 0
+        except V.VflError as e:
+            assert e.status == V.VFL_E_INVALID
+            return False
+
+    assert accepted(last) and not accepted(last + 8)
+
+
 def _random_shape(rng, dtype):
     from vfl_synth.workloads import Workload, PartySpec, TopSpec
     def widths(n, last_mult):

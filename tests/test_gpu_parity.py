@@ -313,6 +313,73 @@ def test_table_sgd_segments(zipf_a, vocab, shift, stride):
     _check_params(run, recs, w, per_tick=True)
 
 
+@pytest.mark.parametrize("vocab,stride,batch,emb", [(6400, 64, 4500, 4), (6400, 64, 4500, 16),
+                                                    (640, 64, 700, 8), (130, 1, 33, 4), (70000, 9, 1500, 12)])
+def test_table_sgd_parts(vocab, stride, batch, emb):
+    """The id parts of the table SGD (id mod 64): every id in one part (stride
+    64), with over 1024 keys left after its frequent ids (two passes of 9000
+    samples) or between 128 and 1024, parts of a few keys, and parts with
+    repeated and single ids; rows of 1 to 4 chunks.  The layers are linear:
+    with ReLUs, the 9000 x 60 pre-activations of a group include some within
+    float32 rounding of zero (3.5e-8 beside values near 1, the float64 run
+    shows), whose sign decides a sample's share of a gradient (about
+    lr / 9000 * |x| |delta|, 3e-7, above the bound of one rounding)."""
+    w = Workload(name="parts", n_rows=2 * 2 * batch, dtype="f32",
+                 A=PartySpec(dense=7, n_cat=1, vocab=vocab, emb_dim=emb, widths=[24, 16], relu=[False] * 2),
+                 B=PartySpec(dense=0, n_cat=2, vocab=vocab, emb_dim=emb, widths=[20, 8], relu=[False] * 2),
+                 top=TopSpec(widths=[12, 1], relu=[False]), batch=batch, staleness=1, replicas=2, lr=0.5,
+                 labels="bernoulli", label_p=0.4, zipf_a=1.1, id_stride=stride, data_seed=84,
+                 init_seed=85, noise_seed=86)
+    run = H.Run(w, w.n_rows, 2)
+    o, recs = run.oracle("f64")
+    _check_ints(run, o, recs)
+    _check_losses(run, recs, w)
+    _check_params(run, recs, w, per_tick=True)
+
+
+@pytest.mark.parametrize("dtype,din,widths,batch", [
+    ("bf16", 40, [33, 17], 33), ("bf16", 40, [33, 17], 4096), ("bf16", 40, [33, 17], 4104),
+    ("f32", 40, [33, 17], 2048), ("f32", 40, [33, 17], 2056),
+    ("bf16", 700, [648, 40], 33), ("bf16", 700, [648, 40], 1000), ("f32", 700, [648, 40], 505)])
+def test_weight_gradients_without_a_split(dtype, din, widths, batch):
+    """Weight gradients of groups small enough for one block per 32 x 32 tile
+    (up to 4096 bf16 or 2048 float32 rows, and 8 rows past it, where the row
+    chunks take over): few tiles (16 wavefronts each) and more than 384 of
+    them (4 wavefronts), fewer row steps than wavefronts, partial tiles of
+    inputs and outputs, and a last group of one row.  The float32 layers are
+    linear, as for the tables above."""
+    lin = (lambda ws: [False] * len(ws)) if dtype == "f32" else (lambda ws: None)
+    w = Workload(name="unsplit", n_rows=2 * batch + 1, dtype=dtype,
+                 A=PartySpec(dense=13, widths=[40, 24], relu=lin([40, 24])),
+                 B=PartySpec(dense=din, widths=widths, relu=lin(widths)),
+                 top=TopSpec(widths=[19, 1], relu=lin([19])), batch=batch, staleness=1, replicas=1, lr=0.5,
+                 labels="bernoulli", label_p=0.4, data_seed=87, init_seed=88, noise_seed=89)
+    _full_check(H.Run(w, w.n_rows, 3), w)
+
+
+@pytest.mark.parametrize("dtype,rows,widths", [("bf16", 8192, [64, 32]), ("bf16", 8192 + 31, [64, 48]),
+                                               ("bf16", 12288 + 47, [128, 96, 32]), ("f32", 4096 + 17, [48, 32])])
+def test_layer_outputs_of_whole_and_partial_blocks(dtype, rows, widths):
+    """Blocks of more than 16 rows: whole ones with widths of whole MFMA
+    depths (written without a test per element) beside a last partial block
+    and widths that are not such a multiple.  Losses and messages of three
+    groups, the later ones of updated parameters (lr 0.5).  The parameters
+    themselves have no tight bound here: a hidden value that rounds across
+    zero moves one row's delta, and with messages clipped to about 1e-2 and a
+    mean over 8192 rows (updates of 4e-5) one row is 4e-7 of lr / rows * |x|
+    |delta|, where the bound of the named workloads is 3.8e-7."""
+    w = Workload(name="blocks", n_rows=3 * rows, dtype=dtype,
+                 A=PartySpec(dense=24, widths=[96, 64, 32]), B=PartySpec(dense=40, widths=widths),
+                 top=TopSpec(widths=[64, 32, 1]), batch=rows, staleness=1, replicas=1, lr=0.5,
+                 clip=1.0, clip_emb=True, clip_grad=True, labels="bernoulli", label_p=0.4,
+                 data_seed=90, init_seed=91, noise_seed=92)
+    run = H.Run(w, w.n_rows, 3)
+    o, recs = run.oracle(_prec(w))
+    _check_ints(run, o, recs)
+    _check_losses(run, recs, w)
+    _check_messages(run, recs, w)
+
+
 def test_out_of_range_ids_are_clamped_and_counted():
     """Categorical ids outside [0, vocab) (negative and past the vocabulary,
     on both parties) are read as the nearest valid id and counted: the run
