@@ -495,7 +495,10 @@ __device__ __forceinline__ void logit_reduce(const DwJob& J, int lb, int R, floa
 // Blocks past the tiles reduce the logit layer's partials.
 // The row steps of a block are a chain of L2 reads (R * 64 columns through
 // one CU), so few tiles take 16 wavefronts, which read 16 steps at a time;
-// many tiles (more than kDwuTiles) fill the CUs with 4 each.  Against the row
+// many tiles (more than kDwuTiles) fill the CUs with 4 each (both parties on
+// one stream, 16 / 4 wavefronts: 64-256-128 + 256-256 at 4096 rows, 160
+// tiles, 25.5 / 37.6 us; 500-1024-512-128 at 512 rows, 1088 tiles, 25.1 /
+// 21.5 us and the tick 76.6 / 68.5).  Against the row
 // chunks with their reduction launch: 4096 rows of 64-256-128 + 256-256,
 // 19 + 15 -> 25 us for both parties on one stream.
 constexpr int kDwuTiles = 384;
