@@ -132,7 +132,7 @@ struct Lds {
 
 struct FwdLds { LBuf buf[2], bias; int bytes = 0; };
 struct ActLds {
-  LBuf X[2], cat, msg, red, bias;
+  LBuf in, X[2], cat, msg, red, bias;             // in: shares X[1]
   LBuf mfa[VFL_MAX_LAYERS], mft[VFL_MAX_LAYERS];   // ReLU masks of A's layers, the top's hidden layers
   int bytes = 0;
 };
@@ -185,6 +185,7 @@ struct Plan {
   int ldb[VFL_MAX_LAYERS]{};                  // their row pitch (bytes: the layer width rounded up to 64)
   KMeta kf, ka, kb;
   int bchunk = 0;                     // columns per range of B's last delta (0: whole)
+  bool act_tight = false;             // plan_act_lds' layout of k_active
   FwdLds lf;
   ActLds la;
   BwdLds lb;
@@ -394,7 +395,12 @@ void plan_fwd_lds(const Plan& p, int BR, FwdLds& f) {
   f.bytes = l.off;
 }
 
-void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
+// tight: the ReLU mask of A's last layer lies behind the rows that X[1] holds
+// after A's input, in the input's place (the mask is written beside the top
+// model's first layer, when the input has been read and copied, and read by
+// the concat product).  Only wide inputs of widths that fit no other way need
+// it (A 1160-1160 with a 64-wide top in bf16).
+void plan_act_lds(const Plan& p, int BR, bool gextra, bool tight, ActLds& a) {
   Lds l;
   l.KS = p.e == BF16 ? 32 : 16;
   l.BR = BR;
@@ -402,15 +408,32 @@ void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
   const ActBufs x(p.A.L, p.T.H);
   int w[2] = {1, 1};
   auto holds = [&](int i, int width) { w[i] = std::max(w[i], width); };
-  holds(x.in, p.A.din);
+  if (!tight) holds(x.in, p.A.din);
   for (int i = 0; i + 1 < p.A.L; ++i) holds(x.fa[i], p.A.out[i]);
   for (int j = 0; j < p.T.H; ++j) holds(x.ft[j], p.T.out[j]);
   holds(x.dh, p.T.out[p.T.H - 1]);
   for (int q = 0; q + 1 < p.T.H; ++q) holds(x.dt[q], p.T.in[p.T.H - 1 - q]);
   holds(x.dc, p.dA);
   for (int q = 0; q + 1 < p.A.L; ++q) holds(x.da[q], p.A.in[p.A.L - 1 - q]);
+  auto mask = [&](bool relu, int width) {
+    LBuf m;
+    if (!relu) return m;
+    const int pitch = (width + 31) / 32 * 32 + 16;
+    m = l.raw(BR * es / 16 * pitch);
+    m.pitch = pitch;
+    return m;
+  };
   a.X[0] = l.take(w[0], es);
+  const int x1 = l.off;
   a.X[1] = l.take(w[1], es);
+  a.in = a.X[1];
+  if (tight) {
+    a.mfa[p.A.L - 1] = mask(p.A.relu[p.A.L - 1], p.A.out[p.A.L - 1]);
+    const int end = l.off;
+    l.off = x1;
+    a.in = l.take(p.A.din, es);
+    l.off = std::max(l.off, end);
+  }
   // the gradient message's staging (written by the concat product; float32
   // where clip or noise follow) takes the place of cat (last read by the
   // top's first layer)
@@ -420,15 +443,7 @@ void plan_act_lds(const Plan& p, int BR, bool gextra, ActLds& a) {
   // layers left room for 16 rows per block instead of 32 (8192 rows: k_active
   // 109 -> 75 us), 64-256-128 with a 256-wide top for 48 instead of 64
   // (32768 rows: 82 -> 73 us)
-  auto mask = [&](bool relu, int width) {
-    LBuf m;
-    if (!relu) return m;
-    const int pitch = (width + 31) / 32 * 32 + 16;
-    m = l.raw(BR * es / 16 * pitch);
-    m.pitch = pitch;
-    return m;
-  };
-  for (int i = 0; i < p.A.L; ++i) a.mfa[i] = mask(p.A.relu[i], p.A.out[i]);
+  for (int i = 0; i + (tight ? 1 : 0) < p.A.L; ++i) a.mfa[i] = mask(p.A.relu[i], p.A.out[i]);
   for (int j = 0; j + 1 < p.T.H; ++j) a.mft[j] = mask(p.T.relu[j], p.T.out[j]);
   // the block's labels, per-wavefront partials of the logit layer's
   // weight gradient [kChainWaves][Hd rounded to 4] and of {loss, dl}
@@ -476,9 +491,9 @@ void plan_bwd_lds(const Plan& p, int BR, int chunk, BwdLds& b) {
 // The interface's limit on the widths: one workgroup's LDS holds 16 rows of
 // every layer's output of party A and the top model (B's embedding and the
 // message beside them), and of B's widest pairs of layers with a ReLU mask
-// per layer.  The kernels' own layouts are smaller; the limit stays where it
-// was when they kept all of that, so that what is accepted does not depend
-// on them.  Empty when the widths are within it.
+// per layer.  The kernels' own layouts fit wherever this one does; the limit
+// stays where it was when they kept all of that, so that what is accepted
+// does not depend on them.  Empty when the widths are within it.
 std::string width_limit(const Plan& p, bool gextra) {
   const int es = elt_size(p.e);
   Lds l;
@@ -760,8 +775,11 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   // chain kernels: rows per block and LDS layouts
   if (!pick_rt(p.R, p.kf, [&](int BR) { FwdLds f; plan_fwd_lds(p, BR, f); return f.bytes; }))
     return "party B's widths exceed the LDS of one workgroup";
-  if (!pick_rt(p.R, p.ka, [&](int BR) { ActLds x; plan_act_lds(p, BR, gextra, x); return x.bytes; }))
-    return "party A's and the top model's widths exceed the LDS of one workgroup";
+  auto act_bytes = [&](int BR) { ActLds x; plan_act_lds(p, BR, gextra, p.act_tight, x); return x.bytes; };
+  if (!pick_rt(p.R, p.ka, act_bytes)) {
+    p.act_tight = true;
+    if (!pick_rt(p.R, p.ka, act_bytes)) return "party A's and the top model's widths exceed the LDS of one workgroup";
+  }
   if (!pick_bwd(p, 0, p.kb, p.bchunk)) return "party B's widths exceed the LDS of one workgroup";
   {
     // B's backward starts every block with its loads (ReLU masks, gradient
@@ -788,7 +806,7 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     }
   }
   plan_fwd_lds(p, 16 * p.kf.rt, p.lf);
-  plan_act_lds(p, 16 * p.ka.rt, gextra, p.la);
+  plan_act_lds(p, 16 * p.ka.rt, gextra, p.act_tight, p.la);
   plan_bwd_lds(p, 16 * p.kb.rt, p.bchunk, p.lb);
   T.logit_part = ly.take(sizeof(float) * (size_t)p.ka.blocks * (T.out[T.H - 1] + 2));
 
@@ -968,7 +986,7 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.in.idt = A.spec.n_cat ? (int32_t*)(ws + A.idt[0]) : nullptr; a.in.ldi = p.R;
     a.in.bad_ids = (int32_t*)(ws + p.hdr) + 2 * kMaxSlots * 4 + 1;
     const ActBufs x(A.L, T.H);
-    a.in.buf = la.X[x.in];
+    a.in.buf = la.in;
     a.in.rc = rcm(c, A.x0rc[0], A.din);
     a.bt.src = at_f(p.bias_a); a.bt.off = la.bias.off; a.bt.n4 = p.nbias_a / 4;
     a.warm.p[0] = c->ws + A.Wq[0][0];
@@ -977,7 +995,7 @@ std::string build_jobs(const Plan& p, const vfl_opts& o, char* ws, Jobs& J) {
     a.warm.lines[1] = (int32_t)((T.packed_end - T.Wq[0]) / 128);
     a.LA = A.L;
     for (int l = 0; l < A.L; ++l) {
-      const LBuf src = la.X[l == 0 ? x.in : x.fa[l - 1]];
+      const LBuf src = l == 0 ? la.in : la.X[x.fa[l - 1]];
       const LBuf dst = l + 1 < A.L ? la.X[x.fa[l]] : la.cat;
       a.fa[l] = layer(c->ws + A.Wq[0][l], A.kq[l], la.bias.off + 4 * A.bo[l], A.out[l], A.in[l], A.relu[l],
                       src, dst);

@@ -140,6 +140,31 @@ def test_widest_accepted_layers(V, dtype, A, B, last):
     assert accepted(last) and not accepted(last + 8)
 
 
+@pytest.mark.parametrize("dtype,extra,B,top,clip,last", [
+    ("bf16", 0, [1160], 64, False, 1184), ("bf16", 0, [100], 64, False, 1536), ("bf16", 0, [8], 8, False, 1592),
+    ("bf16", 0, [8], 8, True, 1592), ("bf16", 300, [1827, 20], 20, False, 1472), ("f32", 64, [584], 8, False, 600)])
+def test_widest_one_layer_party_with_a_wide_input(V, dtype, extra, B, top, clip, last):
+    """Party A of one layer with an input as wide as its cut layer: the ReLU
+    mask of that layer finds its place in the kernel's LDS up to the same
+    limits (checked for the 16 widths below each: the layouts' padding makes
+    some of them the tightest)."""
+    from vfl_synth.workloads import Workload, PartySpec, TopSpec
+    from paper_2510_12494_amd.session import bottom_spec, top_spec, opts
+
+    def accepted(n):
+        w = Workload(name="limit", n_rows=64, dtype=dtype, A=PartySpec(dense=n + extra, widths=[n]),
+                     B=PartySpec(dense=40, widths=B), top=TopSpec(widths=[top, 1]), batch=64, staleness=1,
+                     replicas=1, lr=0.1, clip=1.0 if clip else 0.0, clip_grad=clip)
+        try:
+            return V.vfl_workspace_size(bottom_spec(w.A), bottom_spec(w.B), top_spec(w.top), opts(w)) > 0
+        except V.VflError as e:
+            assert e.status == V.VFL_E_INVALID
+            return False
+
+    assert [n for n in range(last - 120, last + 1, 8) if not accepted(n)] == []
+    assert not accepted(last + 8)
+
+
 def _random_shape(rng, dtype):
     from vfl_synth.workloads import Workload, PartySpec, TopSpec
     def widths(n, last_mult):

@@ -109,6 +109,20 @@ def _check_params(run, recs, w, per_tick, f64_recs=None, stated=False):
                              np.max(np.abs((v - p0) - (v64 - p0))) / d64, float("inf"), f"{k} t{t}")
 
 
+def _gradient_probe(w):
+    """One update per party; w.lr = 1, so that every parameter change is -grad."""
+    run = H.Run(w, w.rows_per_tick, 1)
+    o, recs = run.oracle(_prec(w))
+    _check_ints(run, o, recs)
+    dtol = _dtol(w)
+    for key, v in o.p.items():
+        ok, err, bound = H.delta_ok(run.final[key], v, run.p0[key].astype(np.float64), dtol, 1)
+        d_ref = np.max(np.abs(v - run.p0[key]))
+        if d_ref > 0:
+            H.record("grad rel (lr 1)", err / d_ref, dtol, f"{key} max|grad| {d_ref:.2e}")
+        assert ok, (key, err, bound)
+
+
 def _full_check(run, w, per_tick=True, f64=True):
     """Integers, losses, messages and parameters of a run against the
     oracle at the workload's precision (and, for bf16, theta against the
@@ -523,17 +537,21 @@ def test_wide_three_layer_gradient_probe(din, widths, s, k, clip):
     zero, and the GPU and the emulation take that ReLU decision
     differently, which moves B.W1's gradient by 2 % of its largest entry;
     both stay equally close to the float64 oracle.)"""
-    w = _wide_three(din, widths, s, k, clip, lr=1.0)
-    run = H.Run(w, w.rows_per_tick, 1)
-    o, recs = run.oracle(_prec(w))
-    _check_ints(run, o, recs)
-    dtol = _dtol(w)
-    for key, v in o.p.items():
-        ok, err, bound = H.delta_ok(run.final[key], v, run.p0[key].astype(np.float64), dtol, 1)
-        d_ref = np.max(np.abs(v - run.p0[key]))
-        if d_ref > 0:
-            H.record("grad rel (lr 1)", err / d_ref, dtol, f"{key} max|grad| {d_ref:.2e}")
-        assert ok, (key, err, bound)
+    _gradient_probe(_wide_three(din, widths, s, k, clip, lr=1.0))
+
+
+@pytest.mark.parametrize("dtype,din,cut,B,top,clip", [
+    ("bf16", 1184, 1184, 1160, 64, False), ("bf16", 1592, 1592, 8, 8, True), ("f32", 664, 600, 584, 8, False)])
+def test_widest_one_layer_party_gradient_probe(dtype, din, cut, B, top, clip):
+    """Party A of one layer at the LDS limit, its input as wide as its cut:
+    the ReLU mask of that layer then lies in the input's place behind the
+    top model's deltas.  One update at lr 1 (every change is -grad), with
+    a last block of 12 rows; A's gradient goes through the mask."""
+    w = Workload(name="widest", n_rows=300, dtype=dtype, A=PartySpec(dense=din, widths=[cut]),
+                 B=PartySpec(dense=40, widths=[B]), top=TopSpec(widths=[top, 1]), batch=300, staleness=0,
+                 replicas=1, lr=1.0, clip=1.0 if clip else 0.0, clip_grad=clip, labels="teacher",
+                 data_seed=94, init_seed=95, noise_seed=96)
+    _gradient_probe(w)
 
 
 @pytest.mark.parametrize("din", [500, 129])
