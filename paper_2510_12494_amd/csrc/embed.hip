@@ -7,19 +7,22 @@
 // it up, and applies SGD once per touched row.
 //
 // Work split: no two wavefronts ever write the same table row.  The ids of a
-// field are dealt to kParts = 64 parts (id mod 64); a workgroup takes four
-// parts of one field, a wavefront one of them.  Per pass of up to 8192
-// samples
+// field are dealt to kParts = 64 parts by a mix of their bits (mix_id: a
+// permutation of the 19-bit ids; its upper 6 bits are the part); a workgroup
+// takes four parts of one field, a wavefront one of them.  Per pass of up to
+// 8192 samples
 //   1. the workgroup reads the field's ids (a field-major copy the gather
-//      wrote) once and places the (id / 64, row) keys of its four parts into
-//      LDS, part by part, in a fixed order (a scan of per-thread counts);
-// then each wavefront works on its part alone, without a barrier:
+//      wrote) once and places the (rest of the mixed id, row) keys of its
+//      four parts into LDS, part by part, in a fixed order (a scan of
+//      per-thread counts);
 //   2. a frequent id is found in a sample of 64 of the part's keys (one that
 //      holds at least kHotSample of them), taken out of the list and summed
-//      in list order, kQueue rows in flight, whatever its value is: with
-//      Zipf-like fields the first ids carry a large share of the samples
-//      (exponent 1.1 over 100k ids: 13 %, 6 %, 4 %, ..), and sorting them
-//      would cost more than reading them;
+//      in list order, kQueue rows per wavefront in flight, whatever its value
+//      is: with Zipf-like fields the first ids carry a large share of the
+//      samples (exponent 1.1 over 100k ids: 13 %, 6 %, 4 %, ..), and sorting
+//      them would cost more than reading them.  Lists of more than kShareMin
+//      keys are gone through by all four wavefronts, a quarter each;
+// then each wavefront works on its part alone, without a barrier:
 //   3. the other keys are sorted (bitonic network in registers up to 1024
 //      keys, in LDS beyond), by id, then by sample;
 //   4. segmented sums per id over the sorted keys, 128 positions at a time:
@@ -31,11 +34,13 @@
 // the same tables.
 //
 // Bound by latency (dependent id, key, gradient and table reads), so many
-// small independent wavefronts: with a workgroup per part (16 sorted parts
-// and 16 workgroups for the ids 0 .. 15) and its barriers, 8192 samples of 13
-// fields took 27 us per party, now 22 us; with the frequent ids
-// scattered over the vocabulary, which those workgroups did not see,
-// 31 and 21.5 us.
+// small independent wavefronts, and no long work for one of them.  us per
+// tick of 13 fields per party, 8192 samples, one stream: a workgroup per part
+// of 16 and per id 0 .. 15 with its barriers / a wavefront per part of id mod
+// 64 and per frequent id / this one: 100,000 ids 36 / 28 / 27; one id 39 / 65 /
+// 33; two 26 / 44 / 22; ten 34 / 37 / 27; multiples of 64 147 / 1059 / 27 (all
+// in one part, where one wavefront sorted 8192 keys in LDS); 30,000 samples
+// of 6 fields, 8-wide rows: 1000 ids 64 / 79 / 62, two ids 51 / 148 / 73.
 #include <algorithm>
 
 #include "device.h"
@@ -51,8 +56,9 @@ constexpr int kRowBits = 13;
 constexpr int kPass = 1 << kRowBits;           // samples per pass
 constexpr uint32_t kRowMask = kPass - 1;
 constexpr int kRowsPerThread = kPass / kThreads;     // rows a thread tests per pass
-constexpr int kParts = 64;                     // id parts per field (id mod kParts)
+constexpr int kParts = 64;                     // id parts per field
 constexpr int kBlocksPerField = kParts / kWaves;
+constexpr int kShareMin = 512;                 // keys above which the workgroup goes through a list together
 constexpr int kHotMin = 128;                   // keys from which frequent ids are looked for
 constexpr int kHotSample = 8;                  // of 64 sampled keys: such an id is taken out
 constexpr int kQueue = 128;                    // rows of a frequent id summed together
@@ -60,6 +66,28 @@ constexpr int kStage = 128;                    // sorted positions per stage
 constexpr int kGroups = 16;                    // 4-lane groups per wavefront
 constexpr int kSpan = kStage / kGroups;        // positions per group
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+// The part of an id, and what tells it from the part's other ids: a
+// permutation of the 19-bit ids, by an exclusive or with their upper bits
+// and a multiplication with 2^19 over the golden ratio (odd), which deals
+// out consecutive ids, multiples of a power of two (id mod 64 put all of them
+// in one part) and of other strides evenly.
+constexpr int kIdBits = 19, kSubBits = kIdBits - 6;
+constexpr uint32_t kIdMask = (1u << kIdBits) - 1, kSubMask = (1u << kSubBits) - 1;
+constexpr uint32_t kMul = 324027u;
+constexpr uint32_t inverse(uint32_t m) {
+  uint32_t x = m;                              // correct to 3 bits; each step doubles them
+  for (int i = 0; i < 4; ++i) x *= 2u - m * x;
+  return x & kIdMask;
+}
+constexpr uint32_t kMulInv = inverse(kMul);
+static_assert(((kMul * kMulInv) & kIdMask) == 1u && kParts == 1 << 6 && kSubBits + kRowBits <= 32 && 2 * 10 >= kIdBits,
+              "the mix is not a permutation");
+__device__ __forceinline__ uint32_t mix_id(uint32_t id) { return __umul24(id ^ (id >> 10), kMul) & kIdMask; }
+__device__ __forceinline__ uint32_t unmix_id(uint32_t h) {
+  const uint32_t y = __umul24(h, kMulInv) & kIdMask;
+  return y ^ (y >> 10);
+}
 
 // keeps the LDS accesses of a wavefront's lanes in program order (the
 // hardware does; this holds the compiler to it)
@@ -153,6 +181,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
   __shared__ uint32_t keys[kPass];
   __shared__ uint16_t queue[kWaves][kQueue + 64];
   __shared__ uint32_t wcnt[kWaves][2];
+  __shared__ f32x4 psum[2][kWaves][4];          // a shared list's wavefront sums (two iterations)
+  __shared__ int plen[kWaves];                  // and how many keys each has left in its quarter
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int f = blockIdx.x / kBlocksPerField, quad = blockIdx.x % kBlocksPerField;
   int R = j.R;
@@ -173,9 +203,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
   const VFL_GLOBAL char* Gb = glb((const char*)j.G) + (int64_t)f * EC * 16;
   VFL_GLOBAL char* Tb = glb((char*)(j.T + (int64_t)f * j.V * j.E));
   const uint32_t ldg = (uint32_t)j.ldg * 4u, row_bytes = 16u * (uint32_t)EC, lo = 16u * (uint32_t)cc;
-  auto table_row = [&](uint32_t id_hi) {        // this lane's chunk of the part's table row
-    return (VFL_GLOBAL f32x4*)(Tb + (uint32_t)((id_hi * (uint32_t)kParts + part) * row_bytes + lo));
+  auto row_at = [&](uint32_t p, uint32_t sub) { // this lane's chunk of the table row of part p's id
+    return (VFL_GLOBAL f32x4*)(Tb + (uint32_t)(unmix_id(p << kSubBits | sub) * row_bytes + lo));
   };
+  auto table_row = [&](uint32_t sub) { return row_at(part, sub); };
   uint16_t* q = queue[wave];
 
   for (int c0 = 0; c0 < R; c0 += kPass) {
@@ -183,12 +214,14 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
     // 1. every thread tests kPass / kThreads rows (strided, so each load
     // instruction of a wavefront is contiguous) and counts those of each of
     // the workgroup's parts, in a byte each
-    uint32_t idv[kRowsPerThread];
+    uint32_t idv[kRowsPerThread];             // mixed
     auto sub_part = [&](int i) {              // the row's part here, >= kWaves: not in this workgroup
-      return (idv[i] & (kParts - 1)) - (uint32_t)(kWaves * quad);
+      return (idv[i] >> kSubBits) - (uint32_t)(kWaves * quad);
     };
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) idv[i] = (uint32_t)ids[c0 + min(i * kThreads + tid, n - 1)];
+#pragma unroll
+    for (int i = 0; i < kRowsPerThread; ++i) idv[i] = mix_id(idv[i]);
     uint32_t count = 0u;
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) {
@@ -235,25 +268,18 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
       const uint32_t x = sub_part(i);
       if (x < (uint32_t)kWaves && i * kThreads + tid < n) {
         const uint32_t sh = 16 * (x & 1), p = x & 2 ? pos[1] : pos[0];
-        keys[(p >> sh) & 0xffffu] = ((idv[i] / kParts) << kRowBits) | (uint32_t)(i * kThreads + tid);
+        keys[(p >> sh) & 0xffffu] = ((idv[i] & kSubMask) << kRowBits) | (uint32_t)(i * kThreads + tid);
         pos[0] += x & 2 ? 0u : 1u << sh;
         pos[1] += x & 2 ? 1u << sh : 0u;
       }
     }
     __syncthreads();
-    int b0 = base[0], np = base[1] - base[0];
-#pragma unroll
-    for (int s = 1; s < kWaves; ++s)
-      if (wave == s) { b0 = base[s]; np = base[s + 1] - base[s]; }
-    b0 = __builtin_amdgcn_readfirstlane(b0);
-    np = __builtin_amdgcn_readfirstlane(np);
-    uint32_t* list = keys + b0;
     const VFL_GLOBAL char* Gp = Gb + (int64_t)c0 * ldg;
     auto grad_row = [&](uint32_t row) { return *(const VFL_GLOBAL f32x4*)(Gp + (uint32_t)(row * ldg + lo)); };
 
-    // 2. frequent ids (at least kHotSample keys leave the list each time)
-    while (np > kHotMin) {
-      const uint32_t sid = list[(lane * np) >> 6] >> kRowBits;
+    // 2. frequent ids.  The one most of the 64 lanes hold (sid) and how many
+    // do (at least 8 leave a list each time, so the loops below end).
+    auto frequent = [&](uint32_t sid, uint32_t& id) {
       int same = 0;
 #pragma unroll 8
       for (int l = 0; l < 64; ++l) same += sid == (uint32_t)__builtin_amdgcn_readlane((int)sid, l) ? 1 : 0;
@@ -261,9 +287,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) best = max(best, __shfl_xor(best, d, 64));
       best = __builtin_amdgcn_readfirstlane(best);
-      if ((best >> 6) < kHotSample) break;
-      const uint32_t hot = (uint32_t)__builtin_amdgcn_readlane((int)sid, best & 63);
-      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+      id = (uint32_t)__builtin_amdgcn_readlane((int)sid, best & 63);
+      return best >> 6;
+    };
+    // takes the keys of id `hot` out of list[0, n), n > 0, and sums their
+    // gradient rows; returns the keys left, sum in the lanes of group 0
+    auto take_out = [&](uint32_t* list, int n, uint32_t hot, f32x4& sum) {
+      sum = f32x4{0.f, 0.f, 0.f, 0.f};
       // rows q[0, m) (m <= kQueue) are loaded together, a lane group every
       // 16th, and added, in order, once the next ones are found
       f32x4 v[kQueue / kGroups];
@@ -279,9 +309,9 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
         loaded = m;
       };
       int rest = 0, qn = 0;
-      for (int i0 = 0; i0 < np; i0 += 64) {
-        const bool in = i0 + lane < np;
-        const uint32_t key = list[min(i0 + lane, np - 1)];
+      for (int i0 = 0; i0 < n; i0 += 64) {
+        const bool in = i0 + lane < n;
+        const uint32_t key = list[min(i0 + lane, n - 1)];
         const bool is = in && (key >> kRowBits) == hot;
         const uint64_t bh = __ballot(is), br = __ballot(in && !is);
         lds_order();
@@ -305,7 +335,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
         load_rows(qn);
         add_loaded();
       }
-      np = rest;
       // the 16 groups (lanes 4 apart), a fixed tree
 #pragma unroll
       for (int d = 32; d >= 4; d >>= 1) {
@@ -314,6 +343,98 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
         for (int e = 0; e < 4; ++e) o[e] = __shfl_down(sum[e], d, 64);
         sum += o;
       }
+      return rest;
+    };
+
+    int b0 = base[0], np = base[1] - base[0];
+#pragma unroll
+    for (int s = 1; s < kWaves; ++s)
+      if (wave == s) { b0 = base[s]; np = base[s + 1] - base[s]; }
+    b0 = __builtin_amdgcn_readfirstlane(b0);
+    np = __builtin_amdgcn_readfirstlane(np);
+    uint32_t* list = keys + b0;
+
+    // long lists together, one after the other: wavefront w goes through the
+    // w-th quarter; the owner adds the four sums in wavefront order.  Every
+    // wavefront takes the same turns (the counts and samples are the same
+    // for all, and no list changes between a sample and the barrier after it)
+#pragma unroll 1
+    for (int s = 0; s < kWaves; ++s) {
+      int sb = base[0], sn = base[1] - base[0];
+#pragma unroll
+      for (int u = 1; u < kWaves; ++u)
+        if (s == u) { sb = base[u]; sn = base[u + 1] - base[u]; }
+      sb = __builtin_amdgcn_readfirstlane(sb);
+      sn = __builtin_amdgcn_readfirstlane(sn);
+      if (sn <= kShareMin) continue;
+      int at[kWaves], len[kWaves];              // the quarters
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        at[w] = sb + sn * w / kWaves;
+        len[w] = sb + sn * (w + 1) / kWaves - at[w];
+      }
+#pragma unroll 1
+      for (int it = 0; sn > kShareMin; it ^= 1) {
+        const int x = (lane * sn) >> 6;
+        int pos = at[0] + x, end = len[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) {
+          if (x >= end) pos = at[w] + x - end;
+          end += len[w];
+        }
+        uint32_t hot;
+        const int share = frequent(keys[pos] >> kRowBits, hot);
+        __syncthreads();
+        if (share < kHotSample) break;
+        int a = at[0], m = len[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w)
+          if (wave == w) { a = at[w]; m = len[w]; }
+        f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (m > 0) m = take_out(keys + a, m, hot, sum);
+        if (lane < 4) psum[it][wave][lane] = sum;
+        if (lane == 0) plen[wave] = m;
+        __syncthreads();
+        sn = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+          len[w] = __builtin_amdgcn_readfirstlane(plen[w]);
+          sn += len[w];
+        }
+        if (wave == s && lane < EC) {
+          f32x4 t = psum[it][0][lane];
+#pragma unroll
+          for (int w = 1; w < kWaves; ++w) t += psum[it][w][lane];
+          VFL_GLOBAL f32x4* row = row_at(part, hot);   // (lane = chunk here)
+          *row = *row - scale * t;
+        }
+      }
+      if (wave == s) {
+        // what is left of the quarters, end to end (never above its place)
+        int to = at[0] + len[0];
+#pragma unroll 1
+        for (int w = 1; w < kWaves; ++w) {
+          int from = at[1], m = len[1];
+#pragma unroll
+          for (int u = 2; u < kWaves; ++u)
+            if (w == u) { from = at[u]; m = len[u]; }
+          for (int i0 = 0; i0 < m; i0 += 64) {
+            const uint32_t key = keys[from + min(i0 + lane, m - 1)];
+            lds_order();
+            if (i0 + lane < m) keys[to + i0 + lane] = key;
+            lds_order();
+          }
+          to += m;
+        }
+        np = to - b0;
+      }
+    }
+
+    while (np > kHotMin) {
+      uint32_t hot;
+      if (frequent(list[(lane * np) >> 6] >> kRowBits, hot) < kHotSample) break;
+      f32x4 sum;
+      np = take_out(list, np, hot, sum);
       if (lane < EC) {
         VFL_GLOBAL f32x4* row = table_row(hot);   // (lane = chunk here)
         *row = *row - scale * sum;

@@ -308,12 +308,9 @@ def test_odd_shapes(dtype, s, k, clip):
 def test_table_sgd_segments(zipf_a, vocab, shift, stride):
     """Sparse table SGD at its extremes: 10,000 rows per tick (two passes of
     the per-field key collection), and either (zipf_a = 30) every sample of
-    a field on one id, below 16 (a hot-id workgroup's sum over all rows) or
-    at 17 (one id part: the 32-keys-per-thread sort and a segment spanning
-    every staged block of both passes, while most parts stay empty), or a
-    spread of ids with repeats across parts and hot ids, also with the Zipf
-    ranks scattered over the ids (stride 1009, as hashed ids would be: the
-    frequent ids are no longer the low ones the hot-id workgroups take).""" 
+    a field on one id, or a spread of ids with repeats across parts and
+    frequent ids, also with the Zipf ranks scattered over the ids (stride
+    1009, as hashed ids would be)."""
     w = Workload(name="tables", n_rows=20000, dtype="f32",
                  A=PartySpec(dense=7, n_cat=2, vocab=vocab, emb_dim=16, widths=[24, 16]),
                  B=PartySpec(dense=0, n_cat=3, vocab=vocab, emb_dim=8, widths=[20, 8]),
@@ -330,10 +327,9 @@ def test_table_sgd_segments(zipf_a, vocab, shift, stride):
 @pytest.mark.parametrize("vocab,stride,batch,emb", [(6400, 64, 4500, 4), (6400, 64, 4500, 16),
                                                     (640, 64, 700, 8), (130, 1, 33, 4), (70000, 9, 1500, 12)])
 def test_table_sgd_parts(vocab, stride, batch, emb):
-    """The id parts of the table SGD (id mod 64): every id in one part (stride
-    64), with over 1024 keys left after its frequent ids (two passes of 9000
-    samples) or between 128 and 1024, parts of a few keys, and parts with
-    repeated and single ids; rows of 1 to 4 chunks.  The layers are linear:
+    """The id parts of the table SGD: ids of a stride of 64 over two passes of
+    9000 samples, parts of a few keys, and parts with repeated and single ids;
+    rows of 1 to 4 chunks.  The layers are linear:
     with ReLUs, the 9000 x 60 pre-activations of a group include some within
     float32 rounding of zero (3.5e-8 beside values near 1, the float64 run
     shows), whose sign decides a sample's share of a gradient (about
@@ -345,6 +341,43 @@ def test_table_sgd_parts(vocab, stride, batch, emb):
                  labels="bernoulli", label_p=0.4, zipf_a=1.1, id_stride=stride, data_seed=84,
                  init_seed=85, noise_seed=86)
     run = H.Run(w, w.n_rows, 2)
+    o, recs = run.oracle("f64")
+    _check_ints(run, o, recs)
+    _check_losses(run, recs, w)
+    _check_params(run, recs, w, per_tick=True)
+
+
+def _ids_of_part(part, vocab):
+    """The ids below vocab that the table SGD deals to one part: the upper 6
+    of 19 bits of (id ^ id >> 10) * 324027."""
+    ids = np.arange(vocab, dtype=np.int64)
+    return ids[(((ids ^ (ids >> 10)) * 324027) & 0x7FFFF) >> 13 == part]
+
+
+@pytest.mark.parametrize("n_ids,zipf_a,batch,emb", [
+    (1, 0.0, 256, 16), (1, 0.0, 257, 16), (1, 0.0, 4500, 16), (2, 0.0, 4500, 8), (6, 0.0, 700, 4),
+    (300, 1.1, 4500, 16), (900, 0.0, 4500, 12)])
+def test_table_sgd_long_lists(n_ids, zipf_a, batch, emb):
+    """Every id of a field in one part, so that its list is as long as the
+    pass: 512 keys (one wavefront's) and 514 (all four's), one, two and six
+    ids (the list empties, or shrinks below 512 after some turns), 300 ids of
+    which the frequent ones leave (the quarters are put together, more than
+    1024 keys are sorted), 900 equally likely ones (none is frequent); two
+    passes of 9000 samples.  B's second field has another part of the same
+    workgroup, its last one.  Linear layers, as above."""
+    w = Workload(name="lists", n_rows=2 * 2 * batch, dtype="f32",
+                 A=PartySpec(dense=7, n_cat=1, vocab=60000, emb_dim=emb, widths=[24, 16], relu=[False] * 2),
+                 B=PartySpec(dense=0, n_cat=2, vocab=60000, emb_dim=emb, widths=[20, 8], relu=[False] * 2),
+                 top=TopSpec(widths=[12, 1], relu=[False]), batch=batch, staleness=1, replicas=2, lr=0.5,
+                 labels="bernoulli", label_p=0.4, data_seed=97, init_seed=98, noise_seed=99)
+    d = dict(S.generate(w))
+    rng = np.random.default_rng(17)
+    for key, parts in (("ida", (21,)), ("idb", (40, 43))):
+        p = np.arange(1, n_ids + 1) ** -zipf_a
+        cols = [rng.choice(_ids_of_part(q, 60000)[:n_ids], w.n_rows, p=p / p.sum()) for q in parts]
+        d[key] = np.ascontiguousarray(np.stack(cols, 1), dtype=np.int32)
+        assert d[key].shape[1] == len(parts) and len(np.unique(d[key][:, 0])) == n_ids
+    run = H.Run(w, w.n_rows, 2, data=d)
     o, recs = run.oracle("f64")
     _check_ints(run, o, recs)
     _check_losses(run, recs, w)
