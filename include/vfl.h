@@ -329,8 +329,9 @@ vfl_status vfl_replica_average(vfl_ctx* const* ctxs, int32_t n, uint32_t parties
  * groups in flight), the versions and next groups of both parties, and the
  * integer schedule trace.  The image is a host buffer of vfl_state_size()
  * bytes (the size grows with the trace: ask again right before
- * vfl_get_state).  vfl_get_state synchronises both streams and copies the
- * whole workspace to the image; VFL_E_STATE while party A is inside a
+ * vfl_get_state).  vfl_get_state synchronises both streams and copies these
+ * tensors to the image, which does not depend on how the workspace is laid
+ * out; VFL_E_STATE while party A is inside a
  * group's step (after vfl_bottom_forward(A) and before its
  * vfl_bottom_backward), VFL_E_INVALID if bytes is too small.
  * vfl_set_state synchronises both streams, restores the image into this
@@ -338,7 +339,9 @@ vfl_status vfl_replica_average(vfl_ctx* const* ctxs, int32_t n, uint32_t parties
  * dtype, batch, staleness and replicas on any workspace; the hyper-
  * parameters lr, clip, sigma, seed and flags are this context's), and
  * leaves every channel event complete; VFL_E_INVALID for a foreign,
- * truncated or mismatched image (the context is then unchanged).  A
+ * truncated or mismatched image (the context is then unchanged).  Images
+ * written by earlier versions of the library (copies of their workspace)
+ * are read too.  A
  * restored run continues exactly as the original from the tick after the
  * image: its results are bitwise those of the uninterrupted run.  Batch
  * pointers of the slots are not part of the image (only the forward that

@@ -488,16 +488,14 @@ void plan_bwd_lds(const Plan& p, int BR, int chunk, BwdLds& b) {
   b.bytes = l.off;
 }
 
-// The interface's limit on the widths: one workgroup's LDS holds 16 rows of
-// every layer's output of party A and the top model (B's embedding and the
-// message beside them), and of B's widest pairs of layers with a ReLU mask
-// per layer.  The kernels' own layouts fit wherever this one does; the limit
-// stays where it was when they kept all of that, so that what is accepted
-// does not depend on them.  Empty when the widths are within it.
-std::string width_limit(const Plan& p, bool gextra) {
+// LDS bytes of k_active's first layout at BR rows per block, which kept every
+// layer's output: the interface's limit on the widths, and the rows per block
+// that state images of format 2 were laid out for.
+int first_act_bytes(const Plan& p, int BR, bool gextra) {
   const int es = elt_size(p.e);
   Lds l;
   l.KS = p.e == BF16 ? 32 : 16;
+  l.BR = BR;
   int w = 1;
   for (int j = 0; j < p.T.H; ++j) w = std::max(w, p.T.out[j]);
   for (int i = 0; i < p.A.L; ++i) w = std::max(w, p.A.out[i]);
@@ -509,9 +507,23 @@ std::string width_limit(const Plan& p, bool gextra) {
   l.take_shared(x, p.A.din, es, y, w, es);
   if (gextra) l.take_shared(x, p.T.out[p.T.H - 1], es, y, p.dB, 4);
   else l.take(p.T.out[p.T.H - 1], es);
-  l.raw(4 * (l.BR + kChainWaves * ((p.T.out[p.T.H - 1] + 3) / 4 * 4) + 2 * kChainWaves));
+  l.raw(4 * (BR + kChainWaves * ((p.T.out[p.T.H - 1] + 3) / 4 * 4) + 2 * kChainWaves));
   l.raw(4 * p.nbias_a);
-  if (l.off > kLdsMax) return "party A's and the top model's widths exceed the LDS of one workgroup";
+  return l.off;
+}
+
+// The interface's limit on the widths: one workgroup's LDS holds 16 rows of
+// every layer's output of party A and the top model (B's embedding and the
+// message beside them), and of B's widest pairs of layers with a ReLU mask
+// per layer.  The kernels' own layouts fit wherever this one does; the limit
+// stays where it was when they kept all of that, so that what is accepted
+// does not depend on them.  Empty when the widths are within it.
+std::string width_limit(const Plan& p, bool gextra) {
+  const int es = elt_size(p.e);
+  Lds l;
+  l.KS = p.e == BF16 ? 32 : 16;
+  if (first_act_bytes(p, 16, gextra) > kLdsMax)
+    return "party A's and the top model's widths exceed the LDS of one workgroup";
   // a bf16 first layer from kGemmMinWidth on does not count in the backward
   const int lo = p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth ? 1 : 0;
   int v[2] = {1, 1};
@@ -565,8 +577,14 @@ bool pick_bwd(const Plan& p, int rt, KMeta& m, int& chunk) {
   return whole || chunk;
 }
 
+// State images: format 4 holds the tensors of state_regions one after the
+// other, formats 2 and 3 the raw workspace of the library that wrote them.
+constexpr uint32_t kStateFormat = 4;
+
+// format: the present workspace layout, or that of a library which wrote
+// state images of format 2 or 3 (to read them)
 std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const vfl_top_spec* t,
-                       const vfl_opts* o, Plan& p) {
+                       const vfl_opts* o, Plan& p, uint32_t format = kStateFormat) {
   std::string why;
   if (!o) return "null opts";
   // the caller's dtype as the integer it is (a C caller may pass any value;
@@ -629,10 +647,17 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     const int es = elt_size(p.e);
     auto shape = [&](DwMeta& m, int tiles32, double macs, auto&& tiles_of) {
       const int64_t col_bytes = (int64_t)p.R * es;
-      if (col_bytes <= kDwUnsplitSmall || (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads)) {
+      bool unsplit = col_bytes <= kDwUnsplitSmall ||
+                     (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads);
+      int pad = 128;
+      if (format == 2) {
+        unsplit = ((int64_t)p.R + 127) / 128 * 128 * es <= 2048;
+        pad = 1024;
+      }
+      if (unsplit) {
         m.tile = 32;
         m.splits = 1;
-        m.rps = (p.R + 127) / 128 * 128;
+        m.rps = (p.R + pad - 1) / pad * pad;
         m.blocks = tiles32;
       } else {
         m.tile = bf && 2.0 * p.R * macs >= kDwtMinFlops ? 256 : 64;
@@ -720,7 +745,7 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   if (p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth) {
     KMeta m;
     int chunk = 0;
-    p.bgemm = !pick_bwd(p, 1, m, chunk) ||
+    p.bgemm = format == 2 || !pick_bwd(p, 1, m, chunk) ||
               (p.R >= kGemmMinRows && !pick_bwd(p, kGemmChainRows / 16, m, chunk));
   }
   if (p.bgemm) p.d1rm = ly.take((size_t)es * R * ld_of(p.P.out[1]));
@@ -780,6 +805,7 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     p.act_tight = true;
     if (!pick_rt(p.R, p.ka, act_bytes)) return "party A's and the top model's widths exceed the LDS of one workgroup";
   }
+  if (format == 2) pick_rt(p.R, p.ka, [&](int BR) { return first_act_bytes(p, BR, gextra); });
   if (!pick_bwd(p, 0, p.kb, p.bchunk)) return "party B's widths exceed the LDS of one workgroup";
   {
     // B's backward starts every block with its loads (ReLU masks, gradient
@@ -830,13 +856,17 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   p.da.logit_blocks = (T.out[T.H - 1] + 2 + 3) / 4;
 
   // device job descriptors
-  p.job_fwd = ly.take(sizeof(FwdJob) * (p.s + 1));
-  p.job_act = ly.take(sizeof(ActiveJob) * (p.s + 1));
-  p.job_bwd = ly.take(sizeof(BwdJob) * (p.s + 1));
-  p.job_dwa = ly.take(sizeof(DwJob));
-  p.job_dwb = ly.take(sizeof(DwJob) * (p.s + 1));
+  struct { size_t fwd, act, bwd, dw, lin; } jb = {sizeof(FwdJob), sizeof(ActiveJob), sizeof(BwdJob), sizeof(DwJob),
+                                                  sizeof(LinJob)};
+  if (format == 2) jb = {2280, 8864, 2384, 2352, 96};
+  if (format == 3) jb = {1896, 7280, 2752, 2352, 96};
+  p.job_fwd = ly.take(jb.fwd * (p.s + 1));
+  p.job_act = ly.take(jb.act * (p.s + 1));
+  p.job_bwd = ly.take(jb.bwd * (p.s + 1));
+  p.job_dwa = ly.take(jb.dw);
+  p.job_dwb = ly.take(jb.dw * (p.s + 1));
   if (p.bgemm) {
-    p.job_lin = ly.take(sizeof(LinJob) * (p.s + 1));
+    p.job_lin = ly.take(jb.lin * (p.s + 1));
     // row tiles up to the tick's rows only: the padded rows past them are
     // zero from the workspace's creation and no launch writes them, and a
     // 256-row tile more per XCD (Ra = 34048 at hetero) cost a third round
@@ -1514,15 +1544,70 @@ bool dropped(const vfl_ctx* c, int64_t g) {
   return false;
 }
 
-// ---- checkpoint / resume: host channel state + the whole workspace
+// ---- checkpoint / resume: host channel state + what the workspace carries
+// from one tick to the next
 
-// Fixed header of a state image, followed by the workspace bytes and the
+// The tensors that a later tick reads and this one or an earlier wrote, in
+// the order of a state image: masters, packed copies (a slot's are those of
+// its forward's version), what B's forward left for the delayed backward, the
+// channel.  Offsets are the plan's, sizes depend on the configuration alone,
+// so that an image does not depend on the kernels' workspace layout.
+// Everything else is written before it is read within a tick, or zero.
+struct Region { size_t off, bytes; };
+std::vector<Region> state_regions(const Plan& p) {
+  std::vector<Region> v;
+  const size_t es = elt_size(p.e), R = p.R, rg = (R * es + 15) / 16;   // RC row groups
+  auto add = [&](size_t off, size_t bytes) { v.push_back(Region{off, bytes}); };
+  auto rows = [&](size_t off, int cols) { add(off, es * R * ld_of(cols)); };
+  auto rc = [&](size_t off, int cols) { add(off, rg * ld_of(cols) * 16); };
+  auto packed = [&](size_t off, int n, int ksteps) {
+    const int KS = p.e == BF16 ? 32 : 16;
+    add(off, (size_t)((n + KS - 1) / KS * KS) * ksteps * 64);
+  };
+  for (const Party* P : {&p.A, &p.P}) {
+    const bool passive = P == &p.P;
+    for (int l = 0; l < P->L; ++l) add(P->W[l], sizeof(float) * (size_t)P->out[l] * P->in[l]);
+    if (P->spec.n_cat) add(P->T, sizeof(float) * (size_t)P->spec.n_cat * P->spec.vocab * P->spec.emb_dim);
+    for (int q = 0; q < P->nslots; ++q) {
+      for (int l = 0; l < P->L; ++l) packed(P->Wq[q][l], P->out[l], P->kq[l]);
+      for (int l = 0; l < P->L; ++l) packed(P->Wtq[q][l], P->in[l], P->kt[l]);
+      if (!passive) continue;
+      for (int l = 0; l + 1 < P->L; ++l) rc(P->arc[q][l], P->out[l]);
+      rc(P->x0rc[q], P->din);
+      rows(P->z[q], P->out[P->L - 1]);
+      if (P->zhat[q] != P->z[q]) rows(P->zhat[q], P->out[P->L - 1]);
+      if (P->norm[q]) {
+        add(P->norm[q], sizeof(float) * R);
+        add(P->cfac[q], sizeof(float) * R);
+      }
+      if (P->spec.n_cat) add(P->idt[q], sizeof(int32_t) * R * P->spec.n_cat);
+      for (int l = 0; l + 1 < P->L; ++l)
+        if (p.mbits[q][l]) add(p.mbits[q][l], (R + 7) / 8 * p.ldb[l]);
+      rows(p.ring_g[q], p.dB);
+    }
+  }
+  for (int j = 0; j <= p.T.H; ++j) add(p.T.W[j], sizeof(float) * (size_t)p.T.out[j] * p.T.in[j]);
+  for (int j = 0; j < p.T.H; ++j) packed(p.T.Wq[j], p.T.out[j], p.T.kq[j]);
+  for (int j = 0; j < p.T.H; ++j) packed(p.T.Wtq[j], p.T.in[j], p.T.kt[j]);
+  add(p.bias_a, sizeof(float) * (size_t)p.nbias_a);
+  add(p.T.b[p.T.H], sizeof(float));
+  add(p.bias_b, sizeof(float) * (size_t)p.nbias_b);
+  add(p.hdr, sizeof(int32_t) * (2 * kMaxSlots * 4 + 4));
+  return v;
+}
+size_t region_bytes(const std::vector<Region>& v) {
+  size_t n = 0;
+  for (const Region& r : v) n += r.bytes;
+  return n;
+}
+
+// Fixed header of a state image, followed by its tensors (body_bytes) and the
 // schedule trace (int64).  Slot inputs are not kept: a slot's batch
 // pointers are read only by the forward that filled it.
 struct StateHead {
   char magic[8];
   uint32_t format, n_slots;
-  uint64_t layout, ws_bytes, trace_len;
+  uint64_t layout, body_bytes, trace_len;
   int64_t b_next_fwd, b_next_bwd, b_version, b_pub_next, a_next, a_version, a_copy_version;
   int64_t a_rows_avg, b_rows_avg;
   int64_t b_copy_version[kMaxSlots], grad_group[kMaxSlots], grad_rows[kMaxSlots];
@@ -1530,11 +1615,11 @@ struct StateHead {
       slot_published[kMaxSlots];
 };
 constexpr char kStateMagic[8] = {'V', 'F', 'L', 'S', 'T', 'A', 'T', 'E'};
-constexpr uint32_t kStateFormat = 3;   // 3: workspace layout of the chain kernels with copy wavefronts
 
-// FNV-1a over everything that fixes the workspace layout: element type,
-// batch, staleness, replicas and both bottom specs and the top spec.
-uint64_t layout_signature(const vfl_ctx* c) {
+// FNV-1a over element type, batch, staleness, replicas, both bottom specs and
+// the top spec, and the bytes of what they lay out: the workspace, or a state
+// image's tensors.
+uint64_t layout_signature(const Plan& p, size_t bytes) {
   uint64_t h = 1469598103934665603ull;
   auto mix = [&](int64_t v) {
     for (int i = 0; i < 8; ++i) {
@@ -1542,8 +1627,7 @@ uint64_t layout_signature(const vfl_ctx* c) {
       h *= 1099511628211ull;
     }
   };
-  const Plan& p = c->p;
-  mix(p.e); mix(p.B); mix(p.s); mix(p.k); mix((int64_t)p.total);
+  mix(p.e); mix(p.B); mix(p.s); mix(p.k); mix((int64_t)bytes);
   for (const vfl_bottom_spec* b : {&p.A.spec, &p.P.spec}) {
     mix(b->dense_in); mix(b->n_cat); mix(b->vocab); mix(b->emb_dim); mix(b->n_layers); mix(b->relu_mask);
     for (int l = 0; l < b->n_layers; ++l) mix(b->widths[l]);
@@ -1554,7 +1638,7 @@ uint64_t layout_signature(const vfl_ctx* c) {
 }
 
 size_t state_bytes(const vfl_ctx* c) {
-  return sizeof(StateHead) + c->p.total + sizeof(int64_t) * c->trace.size();
+  return sizeof(StateHead) + region_bytes(state_regions(c->p)) + sizeof(int64_t) * c->trace.size();
 }
 
 vfl_status param_loc(vfl_ctx* c, vfl_party party, int layer, int kind, size_t& off, size_t& bytes) {
@@ -2169,7 +2253,7 @@ vfl_status vfl_replica_average(vfl_ctx* const* ctxs, int32_t n, uint32_t parties
     if (!c) return fail(c0, VFL_E_INVALID, "null context");
     for (int j = 0; j < i; ++j)
       if (ctxs[j] == c) return fail(c0, VFL_E_INVALID, "a context appears twice");
-    if (layout_signature(c) != layout_signature(c0))
+    if (layout_signature(c->p, c->p.total) != layout_signature(c0->p, c0->p.total))
       return fail(c0, VFL_E_INVALID, "contexts of different configurations");
     if (c->capture_phase >= 0) return fail(c0, VFL_E_STATE, "graph capture in progress");
     if ((parties & 1u) && c->a_phase != 0)
@@ -2389,8 +2473,9 @@ vfl_status vfl_get_state(vfl_ctx* c, void* host_buf, size_t bytes) {
   std::memcpy(h.magic, kStateMagic, sizeof(h.magic));
   h.format = kStateFormat;
   h.n_slots = (uint32_t)(p.s + 1);
-  h.layout = layout_signature(c);
-  h.ws_bytes = p.total;
+  const std::vector<Region> regions = state_regions(p);
+  h.body_bytes = region_bytes(regions);
+  h.layout = layout_signature(p, h.body_bytes);
   h.trace_len = c->trace.size();
   h.b_next_fwd = c->b_next_fwd; h.b_next_bwd = c->b_next_bwd; h.b_version = c->b_version;
   h.b_pub_next = c->b_pub_next; h.a_next = c->a_next; h.a_version = c->a_version;
@@ -2408,9 +2493,12 @@ vfl_status vfl_get_state(vfl_ctx* c, void* host_buf, size_t bytes) {
   HIPCHK(hipStreamSynchronize(c->sa));
   HIPCHK(hipStreamSynchronize(c->sb));
   std::memcpy(out, &h, sizeof(h));
-  HIPCHK(hipMemcpy(out + sizeof(h), c->ws, p.total, hipMemcpyDeviceToHost));
-  if (!c->trace.empty())
-    std::memcpy(out + sizeof(h) + p.total, c->trace.data(), sizeof(int64_t) * c->trace.size());
+  size_t at = sizeof(h);
+  for (const Region& r : regions) {
+    HIPCHK(hipMemcpy(out + at, c->ws + r.off, r.bytes, hipMemcpyDeviceToHost));
+    at += r.bytes;
+  }
+  if (!c->trace.empty()) std::memcpy(out + at, c->trace.data(), sizeof(int64_t) * c->trace.size());
   return VFL_OK;
 }
 
@@ -2421,17 +2509,36 @@ vfl_status vfl_set_state(vfl_ctx* c, const void* host_buf, size_t bytes) {
   StateHead h;
   if (bytes < sizeof(h)) return fail(c, VFL_E_INVALID, "state image too short");
   std::memcpy(&h, host_buf, sizeof(h));
-  if (std::memcmp(h.magic, kStateMagic, sizeof(h.magic)) || h.format != kStateFormat)
+  if (std::memcmp(h.magic, kStateMagic, sizeof(h.magic)) || h.format < 2 || h.format > kStateFormat)
     return fail(c, VFL_E_INVALID, "not a state image of this library");
-  if (h.layout != layout_signature(c) || h.ws_bytes != p.total || h.n_slots != (uint32_t)(p.s + 1))
+  // where the image's tensors lie: one after the other, or (formats 2, 3) at
+  // the offsets of the workspace it is a copy of
+  const std::vector<Region> regions = state_regions(p);
+  std::vector<Region> src = regions;
+  size_t body = 0;
+  if (h.format == kStateFormat) {
+    for (Region& r : src) { r.off = body; body += r.bytes; }
+  } else {
+    Plan old;
+    if (!build_plan(&p.A.spec, &p.P.spec, &p.T.spec, &c->o, old, h.format).empty())
+      return fail(c, VFL_E_INVALID, "state image of another configuration");
+    src = state_regions(old);
+    body = old.total;
+  }
+  if (h.layout != layout_signature(p, body) || h.body_bytes != body || h.n_slots != (uint32_t)(p.s + 1) ||
+      region_bytes(src) != region_bytes(regions))
     return fail(c, VFL_E_INVALID, "state image of another configuration");
-  if (h.trace_len % 7 || bytes < sizeof(h) + h.ws_bytes + sizeof(int64_t) * h.trace_len)
+  if (h.trace_len % 7 || bytes < sizeof(h) + body || h.trace_len > (bytes - sizeof(h) - body) / sizeof(int64_t))
     return fail(c, VFL_E_INVALID, "state image truncated");
-  const char* in = (const char*)host_buf;
+  const char* in = (const char*)host_buf + sizeof(h);
   HIPCHK(hipStreamSynchronize(c->sa));
   HIPCHK(hipStreamSynchronize(c->sb));
-  HIPCHK(hipMemcpy(c->ws, in + sizeof(h), p.total, hipMemcpyHostToDevice));
-  // the image's job descriptors point into the workspace it was taken from
+  // the rest of the workspace as after creation (rows past a group must not
+  // hold what a diverged run left there)
+  HIPCHK(hipMemsetAsync(c->ws, 0, p.total, c->sa));
+  HIPCHK(hipStreamSynchronize(c->sa));
+  for (size_t i = 0; i < regions.size(); ++i)
+    HIPCHK(hipMemcpy(c->ws + regions[i].off, in + src[i].off, regions[i].bytes, hipMemcpyHostToDevice));
   const vfl_status js = write_jobs(c);
   if (js != VFL_OK) return js;
   c->b_next_fwd = h.b_next_fwd; c->b_next_bwd = h.b_next_bwd; c->b_version = h.b_version;
@@ -2451,8 +2558,8 @@ vfl_status vfl_set_state(vfl_ctx* c, const void* host_buf, size_t bytes) {
     st.rows = (int)h.slot_rows[q]; st.published = h.slot_published[q] != 0;
     c->bslot[q] = st;
   }
-  c->trace.assign((const int64_t*)(in + sizeof(h) + h.ws_bytes),
-                  (const int64_t*)(in + sizeof(h) + h.ws_bytes) + h.trace_len);
+  c->trace.resize(h.trace_len);
+  if (h.trace_len) std::memcpy(c->trace.data(), in + body, sizeof(int64_t) * h.trace_len);
   // the channel events: everything they guarded is in place
   for (int q = 0; q <= p.s; ++q) {
     HIPCHK(hipEventRecord(c->ev_emb[q], c->sb));

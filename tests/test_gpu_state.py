@@ -5,11 +5,18 @@ uninterrupted run: parameters, losses, channel messages and the schedule
 trace, on the per-call path and under graph replay.  Images of another
 configuration, truncated or foreign images, and images asked for while A is
 inside a group's step are refused, and a refused image leaves the context
-as it was."""
+as it was.  Images that earlier versions of the library wrote are still
+read."""
+import os
+
 import numpy as np
 import pytest
 
 import vfl_synth as S
+from vfl_synth.workloads import Workload, PartySpec, TopSpec
+from oracle import PubSubOracle
+import gpu_harness as H
+from conftest import GOLDEN
 
 pytestmark = pytest.mark.gpu
 
@@ -40,7 +47,7 @@ def _same(sa, sb, shapes, groups, trace=True):
 @pytest.mark.parametrize("name", ["ctr", "private", "tiny_sync", "hetero"])
 def test_restore_continues_bitwise(name):
     """Tables (ctr), clip + noise with two replicas (private), s = 0 float32
-    (tiny_sync), s = 4 with four replicas and B's wide-layer product
+    (tiny_sync), s = 4 with four replicas and B's wide first layer
     (hetero); the image is taken with s groups in flight and a short last
     group ahead."""
     from paper_2510_12494_amd import vfl as V
@@ -211,3 +218,94 @@ def test_refused_images_leave_the_context_unchanged():
         ref.close()
         run.close()
         other.close()
+
+
+def test_restore_into_a_diverged_context():
+    """A context whose parameters, activations and deltas have become NaN
+    goes on bitwise as the original once the image is in it, also through a
+    short group, whose last row steps reach rows that the group does not have."""
+    from paper_2510_12494_amd import vfl as V
+    w = _IMAGES["wide"][0]
+    R, s = w.rows_per_tick, w.staleness
+    epoch = -(-w.n_rows // R)
+    assert w.n_rows % R
+    d, p = S.generate(w), S.init_params(w)
+    shapes = {k: v.shape for k, v in p.items()}
+    p_nan = {k: np.full_like(v, np.nan) for k, v in p.items()}
+    ref, run = _session(w, d, p, w.n_rows), _session(w, d, p_nan, w.n_rows)
+    try:
+        t1, t2 = epoch - 1, 2 * epoch + s
+        for t in range(epoch + 1):
+            run.step(t, epoch=epoch)
+        assert np.isnan(run.losses(range(1))).all()
+        for t in range(t2):
+            if t == t1:
+                V.vfl_set_state(run.ctx, V.vfl_get_state(ref.ctx))
+            ref.step(t, epoch=epoch)
+            if t >= t1:
+                run.step(t, epoch=epoch)
+        _same(ref, run, shapes, range(t1 - s, t2 - s))
+    finally:
+        ref.close()
+        run.close()
+
+
+_IMAGES = {
+    # a wide first layer of B (its input gradient was a layer product when
+    # format 2 was written), a table, clip and noise, two replicas
+    "wide": (Workload(name="wide", n_rows=217, dtype="bf16",
+                      A=PartySpec(dense=11, n_cat=2, vocab=30, emb_dim=4, widths=[24, 16]),
+                      B=PartySpec(dense=5, widths=[512, 8]), top=TopSpec(widths=[20, 1]), batch=20, staleness=1,
+                      replicas=2, lr=0.5, clip=1.0, sigma=0.5, clip_emb=True, clip_grad=True, noise_emb=True,
+                      noise_grad=True, labels="bernoulli", label_p=0.4, data_seed=111, init_seed=112,
+                      noise_seed=113), 7),
+    "tables": (Workload(name="tables", n_rows=333, dtype="f32",
+                        A=PartySpec(dense=5, n_cat=2, vocab=40, emb_dim=8, widths=[24, 16]),
+                        B=PartySpec(dense=0, n_cat=3, vocab=30, emb_dim=4, widths=[20, 8]),
+                        top=TopSpec(widths=[12, 1]), batch=70, staleness=1, replicas=1, lr=0.5,
+                        labels="bernoulli", label_p=0.4, data_seed=114, init_seed=115, noise_seed=116), 5)}
+
+
+@pytest.mark.parametrize("fmt,name", [(2, "wide"), (3, "wide"), (2, "tables")])
+def test_images_of_earlier_formats(fmt, name):
+    """State images written by the library when it stored its workspace as it
+    was (formats 2 and 3; tests/golden, taken after t1 ticks): restored into a
+    context, the run goes on as the oracle does that ran from the start, and
+    the context's own image of that state restores the same again."""
+    from paper_2510_12494_amd import vfl as V
+    w, t1 = _IMAGES[name]
+    with np.load(os.path.join(GOLDEN, f"state_format{fmt}_{name}.npz"), allow_pickle=False) as z:
+        img = z["image"]
+    assert int(img[8:12].view(np.uint32)[0]) == fmt
+    R, s = w.rows_per_tick, w.staleness
+    epoch, t2 = -(-w.n_rows // R), t1 + 5
+    d, p = S.generate(w), S.init_params(w)
+    shapes = {k: v.shape for k, v in p.items()}
+    p_other = {k: (v * 0.5).astype(v.dtype) for k, v in p.items()}
+    old, own = _session(w, d, p_other, w.n_rows), _session(w, d, p_other, w.n_rows)
+    try:
+        V.vfl_set_state(old.ctx, img)
+        V.vfl_set_state(own.ctx, V.vfl_get_state(old.ctx))
+        for t in range(t1, t2):
+            old.step(t, epoch=epoch)
+            own.step(t, epoch=epoch)
+        groups = range(t1 - s, t2 - s)
+        _same(old, own, shapes, groups)
+        got, losses = old.params(shapes), old.losses(groups)
+        trace = V.vfl_get_trace(old.ctx)
+    finally:
+        old.close()
+        own.close()
+    o = PubSubOracle(w, p, "bf16" if w.dtype == "bf16" else "f64")
+    recs = o.run(d, t2, lambda g: S.group_rows(w, g % epoch, w.n_rows), snapshot=lambda t: t == t2 - 1,
+                 keep_messages=False)
+    assert trace == [tuple(r) for r in o.trace[:t2]]
+    ref = np.array([r["loss"] for r in recs if "loss" in r])[t1 - s:t2 - s]
+    np.testing.assert_allclose(losses, ref, rtol=1e-4)
+    tol, dtol = (H.BF16_THETA_EMU, H.BF16_DELTA_TOL) if w.dtype == "bf16" else (H.F32_TOL, H.F32_TOL)
+    for k, v in recs[t2 - 1]["params"].items():
+        e = H.rel_inf(got[k], v)
+        H.record("theta rel", e, tol, k)
+        assert e <= tol, (k, e)
+        ok, err, bound = H.delta_ok(got[k], v, p[k].astype(np.float64), dtol, t2 - s)
+        assert ok, (k, err, bound)
