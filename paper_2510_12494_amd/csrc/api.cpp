@@ -348,6 +348,15 @@ constexpr double kDwtMinFlops = 4e9;
 constexpr int kDwUnsplitBytes = 8192;
 constexpr int kDwUnsplitSmall = 2048;   // up to here whatever the reads
 constexpr int64_t kDwUnsplitReads = 320 << 20;   // bytes, two 32-column operands per tile
+// Few float32 tiles leave most CUs idle while each takes the whole group on
+// one, where a float32 step costs eight times a bf16 one: past these rows,
+// row chunks, unless a party has this many tiles (us per tick, split /
+// unsplit; 64-64 and its top of 64 at 2048 rows, 12 and 4 tiles: 35.5 / 38.4;
+// 16-16 with 16, 2 and 1: 31.7 / 34.6, at 1536 rows 31.8 / 31.9; 96-64 with
+// 64, 20 and 12: 42.1 / 44.8; 133-40, 77-33-21 with 90-17, 29 and 14: 49.9 /
+// 45.3; 192-64 with 96, 36 and 24: 49.6 / 46.9).
+constexpr int kDwFewRowsF32 = 1920;
+constexpr int kDwFewTilesF32 = 24;
 
 // Chunks of at least this many rows may be cut at any 32-row stage.
 constexpr int kDwtFineRows = 1024;
@@ -645,10 +654,13 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     }
     const bool bf = dtype == VFL_BF16;
     const int es = elt_size(p.e);
+    const int tiles_a = bottom_tiles(a, 32) + top_tiles(32), tiles_b = bottom_tiles(b, 32);
+    const bool few = format >= 4 && !bf && p.R > kDwFewRowsF32 && std::max(tiles_a, tiles_b) < kDwFewTilesF32;
     auto shape = [&](DwMeta& m, int tiles32, double macs, auto&& tiles_of) {
       const int64_t col_bytes = (int64_t)p.R * es;
       bool unsplit = col_bytes <= kDwUnsplitSmall ||
                      (col_bytes <= kDwUnsplitBytes && tiles32 * col_bytes * 64 <= kDwUnsplitReads);
+      if (few) unsplit = false;
       int pad = 128;
       if (format == 2) {
         unsplit = ((int64_t)p.R + 127) / 128 * 128 * es <= 2048;
@@ -666,9 +678,9 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
         m.blocks = tiles * m.splits;
       }
     };
-    shape(p.da, bottom_tiles(a, 32) + top_tiles(32), bottom_macs(a) + top_macs,
+    shape(p.da, tiles_a, bottom_macs(a) + top_macs,
           [&](int tile) { return bottom_tiles(a, tile) + top_tiles(tile); });
-    shape(p.db, bottom_tiles(b, 32), bottom_macs(b), [&](int tile) { return bottom_tiles(b, tile); });
+    shape(p.db, tiles_b, bottom_macs(b), [&](int tile) { return bottom_tiles(b, tile); });
     p.Ra = std::max(p.da.splits * p.da.rps, p.db.splits * p.db.rps);
   }
   const int es = elt_size(p.e);

@@ -386,12 +386,13 @@ def test_table_sgd_long_lists(n_ids, zipf_a, batch, emb):
 
 @pytest.mark.parametrize("dtype,din,widths,batch", [
     ("bf16", 40, [33, 17], 33), ("bf16", 40, [33, 17], 4096), ("bf16", 40, [33, 17], 4104),
-    ("f32", 40, [33, 17], 2048), ("f32", 40, [33, 17], 2056),
+    ("f32", 40, [33, 17], 1920), ("f32", 40, [33, 17], 1928), ("f32", 40, [33, 17], 2048),
+    ("f32", 200, [100, 17], 2048), ("f32", 200, [100, 17], 2056),
     ("bf16", 700, [648, 40], 33), ("bf16", 700, [648, 40], 1000), ("f32", 700, [648, 40], 505)])
 def test_weight_gradients_without_a_split(dtype, din, widths, batch):
     """Weight gradients of groups small enough for one block per 32 x 32 tile
-    (up to 4096 bf16 or 2048 float32 rows, and 8 rows past it, where the row
-    chunks take over): few tiles (16 wavefronts each) and more than 384 of
+    (up to 4096 bf16 or 2048 float32 rows, 1920 with few tiles, and 8 rows past
+    it, where the row chunks take over): few tiles (16 wavefronts each) and more than 384 of
     them (4 wavefronts), fewer row steps than wavefronts, partial tiles of
     inputs and outputs, and a last group of one row.  The float32 layers are
     linear, as for the tables above."""
