@@ -39,8 +39,10 @@
 // of 16 and per id 0 .. 15 with its barriers / a wavefront per part of id mod
 // 64 and per frequent id / this one: 100,000 ids 36 / 28 / 27; one id 39 / 65 /
 // 33; two 26 / 44 / 22; ten 34 / 37 / 27; multiples of 64 147 / 1059 / 27 (all
-// in one part, where one wavefront sorted 8192 keys in LDS); 30,000 samples
-// of 6 fields, 8-wide rows: 1000 ids 64 / 79 / 62, two ids 51 / 148 / 73.
+// in one part, where one wavefront sorted 8192 keys in LDS).  us a launch of
+// 30,000 samples of 6 fields, 8-wide rows (four passes), the first / this one:
+// 1000 ids 63 / 56, two 52 / 57, one 58 / 67 (the ticks 2389 / 2053, 2198 /
+// 2088 and 2276 / 2226 us per epoch of 14).
 #include <algorithm>
 
 #include "device.h"
@@ -291,14 +293,20 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
       return best >> 6;
     };
     // takes the keys of id `hot` out of list[0, n), n > 0, and sums their
-    // gradient rows; returns the keys left, sum in the lanes of group 0
-    auto take_out = [&](uint32_t* list, int n, uint32_t hot, f32x4& sum) {
+    // gradient rows; returns the keys left, sum in the lanes of group 0.
+    // one: all sampled keys are of that id
+    auto take_out = [&](uint32_t* list, int n, uint32_t hot, bool one, f32x4& sum) {
       sum = f32x4{0.f, 0.f, 0.f, 0.f};
       // rows q[0, m) (m <= kQueue) are loaded together, a lane group every
       // 16th, and added, in order, once the next ones are found
       f32x4 v[kQueue / kGroups];
       int loaded = 0;
       auto add_loaded = [&] {
+        if (loaded == kQueue) {
+#pragma unroll
+          for (int u = 0; u < kQueue / kGroups; ++u) sum += v[u];
+          return;
+        }
 #pragma unroll
         for (int u = 0; u < kQueue / kGroups; ++u)
           if (u * kGroups + grp < loaded) sum += v[u];
@@ -308,8 +316,26 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
         for (int u = 0; u < kQueue / kGroups; ++u) v[u] = grad_row(q[min(u * kGroups + grp, m - 1)]);
         loaded = m;
       };
-      int rest = 0, qn = 0;
-      for (int i0 = 0; i0 < n; i0 += 64) {
+      int rest = 0, qn = 0, i0 = 0;
+      // While the next kQueue keys are all of this id (a field of few ids has
+      // most of them in parts of their own), the rows are read straight from
+      // the list, the same ones together as through the queue: a turn of the
+      // queue is a chain of LDS reads and writes that takes as long as the
+      // gradient rows (one id, 30,000 samples of 6 fields: 83 us a launch
+      // through the queue, 67 so)
+      for (; one && i0 + kQueue <= n; i0 += kQueue) {
+        uint32_t k[kQueue / kGroups], other = 0u;
+#pragma unroll
+        for (int u = 0; u < kQueue / kGroups; ++u) k[u] = list[i0 + u * kGroups + grp];
+#pragma unroll
+        for (int u = 0; u < kQueue / kGroups; ++u) other |= (k[u] >> kRowBits) ^ hot;
+        if (__ballot(other != 0u)) break;
+        add_loaded();
+#pragma unroll
+        for (int u = 0; u < kQueue / kGroups; ++u) v[u] = grad_row(k[u] & kRowMask);
+        loaded = kQueue;
+      }
+      for (; i0 < n; i0 += 64) {
         const bool in = i0 + lane < n;
         const uint32_t key = list[min(i0 + lane, n - 1)];
         const bool is = in && (key >> kRowBits) == hot;
@@ -391,7 +417,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
         for (int w = 1; w < kWaves; ++w)
           if (wave == w) { a = at[w]; m = len[w]; }
         f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (m > 0) m = take_out(keys + a, m, hot, sum);
+        if (m > 0) m = take_out(keys + a, m, hot, share == 64, sum);
         if (lane < 4) psum[it][wave][lane] = sum;
         if (lane == 0) plen[wave] = m;
         __syncthreads();
@@ -432,9 +458,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_embed_sgd(ScatterJob j) {
 
     while (np > kHotMin) {
       uint32_t hot;
-      if (frequent(list[(lane * np) >> 6] >> kRowBits, hot) < kHotSample) break;
+      const int share = frequent(list[(lane * np) >> 6] >> kRowBits, hot);
+      if (share < kHotSample) break;
       f32x4 sum;
-      np = take_out(list, np, hot, sum);
+      np = take_out(list, np, hot, share == 64, sum);
       if (lane < EC) {
         VFL_GLOBAL f32x4* row = table_row(hot);   // (lane = chunk here)
         *row = *row - scale * sum;

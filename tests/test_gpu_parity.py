@@ -356,11 +356,13 @@ def _ids_of_part(part, vocab):
 
 @pytest.mark.parametrize("n_ids,zipf_a,batch,emb", [
     (1, 0.0, 256, 16), (1, 0.0, 257, 16), (1, 0.0, 4500, 16), (2, 0.0, 4500, 8), (6, 0.0, 700, 4),
-    (300, 1.1, 4500, 16), (900, 0.0, 4500, 12)])
+    (2, 6.0, 256, 8), (2, 9.0, 4500, 16), (300, 1.1, 4500, 16), (900, 0.0, 4500, 12)])
 def test_table_sgd_long_lists(n_ids, zipf_a, batch, emb):
     """Every id of a field in one part, so that its list is as long as the
     pass: 512 keys (one wavefront's) and 514 (all four's), one, two and six
-    ids (the list empties, or shrinks below 512 after some turns), 300 ids of
+    ids (the list empties, or shrinks below 512 after some turns), one id with
+    a rare second one (1 in 65 or 513 keys: the run of one id that is read
+    straight from the list ends inside it), 300 ids of
     which the frequent ones leave (the quarters are put together, more than
     1024 keys are sorted), 900 equally likely ones (none is frequent); two
     passes of 9000 samples.  B's second field has another part of the same
