@@ -567,6 +567,45 @@ bool pick_rt(int R, KMeta& m, F&& bytes_at) {
   return false;
 }
 
+// The pick again where its blocks take more than one round.  A chain kernel
+// has one block of more than 32 rows per CU (k_active one of 32, too), so a
+// few blocks past kMinBlocks cost as much as twice as many, and while they run
+// they leave no CU to the other party's kernels.  bf16: the next number of
+// rows that gives at most kRoundBlocks blocks, or the most rows that give one
+// round (us per tick as picked / so: 38 and 12 features, 59-53-72, 176-32-16
+// with a 48-80 top at 6600, 9500, 11900 and 14200 rows 62 / 56, 71 / 61, 77 /
+// 65, 85 / 75; 64-256-128 twice with 256: 58 / 56, 69 / 65, 75 / 68, 86 / 72;
+// six layers of 103 and 144: 98 / 93, 104 / 102, 111 / 115, 139 / 125; ten of
+// 256: 193 / 173, 227 / 201, 274 / 244, 299 / 264).  float32, whose blocks are
+// bound by their products, gains only from 64 rows instead of 48 (20 and 13
+// features, 256-64 twice with 128 at 12400 and 14200 rows 111 / 101, 126 /
+// 100, but at 6600 and 10100 rows 70 / 76, 92 / 95), and from 32 instead of
+// 64 up to kRoundsF32 blocks, which leave most of their second round idle
+// (18500 and 19500 rows 156 / 136, 164 / 139; at 24500 177 / 172, but 64 with
+// 96-64, 200-64 and 64: 137 / 147).  Past one round of 64 rows bf16 keeps them:
+// 32 and 48 rows are slower at every size tried but the first of six layers of
+// 103 and 144 (18500 rows 154 / 149 and 157; ten of 256 358 / 371 and 366).
+constexpr int kRoundBlocks = 192;
+constexpr int kRoundsF32 = 320;
+template <typename F>
+void settle_rt(const Plan& p, KMeta& m, F&& bytes_at) {
+  auto blocks = [&](int rt) { return (p.R + 16 * rt - 1) / (16 * rt); };
+  if (m.blocks <= kMinBlocks || (p.e == F32 && m.rt < 3)) return;
+  int best = 0;
+  if (p.e == F32 && m.rt == 4) {
+    if (m.blocks <= kRoundsF32) best = 2;
+  } else {
+    for (int rt = m.rt + 1; rt <= 4 && bytes_at(16 * rt) <= kLdsMax; ++rt) {
+      if (blocks(rt) <= kMinBlocks) best = rt;
+      if (blocks(rt) <= kRoundBlocks) break;
+    }
+  }
+  if (!best) return;
+  m.rt = best;
+  m.blocks = blocks(best);
+  m.lds = bytes_at(16 * best);
+}
+
 // The backward chain's rows per block, with its last delta whole or in
 // ranges of kBwdChunk columns: that delta (of B's first layer) is read by no
 // further product, so it need not take LDS for its whole width where that
@@ -842,6 +881,11 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
       p.kb.blocks = (p.R + 31) / 32;
       p.kb.lds = two.bytes;
     }
+  }
+  if (format >= 4) {
+    settle_rt(p, p.kf, [&](int BR) { FwdLds f; plan_fwd_lds(p, BR, f); return f.bytes; });
+    settle_rt(p, p.ka, act_bytes);
+    settle_rt(p, p.kb, [&](int BR) { BwdLds x; plan_bwd_lds(p, BR, p.bchunk, x); return x.bytes; });
   }
   plan_fwd_lds(p, 16 * p.kf.rt, p.lf);
   plan_act_lds(p, 16 * p.ka.rt, gextra, p.act_tight, p.la);

@@ -42,7 +42,7 @@
 // in one part, where one wavefront sorted 8192 keys in LDS).  us a launch of
 // 30,000 samples of 6 fields, 8-wide rows (four passes), the first / this one:
 // 1000 ids 63 / 56, two 52 / 57, one 58 / 67 (the ticks 2389 / 2053, 2198 /
-// 2088 and 2276 / 2226 us per epoch of 14).
+// 2088 and 2276 / 2226 us an epoch of 12).
 #include <algorithm>
 
 #include "device.h"

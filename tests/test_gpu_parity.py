@@ -430,6 +430,23 @@ def test_layer_outputs_of_whole_and_partial_blocks(dtype, rows, widths):
     _check_messages(run, recs, w)
 
 
+@pytest.mark.parametrize("dtype,rows", [("bf16", 4112), ("bf16", 6160), ("bf16", 9217), ("bf16", 12289),
+                                        ("f32", 12289), ("f32", 16385), ("f32", 20481)])
+def test_rows_per_block_past_one_round(dtype, rows):
+    """Groups just past one round of the rows per block that 256 blocks would
+    take, where the chain kernels take more rows per block (bf16: 32, 48, 64
+    and 64; float32: 64) or, at 16385 float32 rows, fewer (32, 64 again past
+    20480), each with a last block of 1 to 16 rows.  One update at lr 1, so
+    that every change is -grad; linear layers, so that no
+    row's share hangs on a pre-activation near zero."""
+    w = Workload(name="rounds", n_rows=rows, dtype=dtype,
+                 A=PartySpec(dense=24, widths=[40, 48, 16], relu=[False] * 3),
+                 B=PartySpec(dense=33, widths=[64, 24, 32], relu=[False] * 3),
+                 top=TopSpec(widths=[32, 20, 1], relu=[False] * 2), batch=rows, staleness=0, replicas=1, lr=1.0,
+                 labels="bernoulli", label_p=0.4, data_seed=100, init_seed=101, noise_seed=102)
+    _gradient_probe(w)
+
+
 def test_out_of_range_ids_are_clamped_and_counted():
     """Categorical ids outside [0, vocab) (negative and past the vocabulary,
     on both parties) are read as the nearest valid id and counted: the run
