@@ -2,6 +2,8 @@
 seeded inputs, for the five workloads at their real tick shapes, their
 full-size ragged epoch tails, odd shapes and the schedule's integer state.
 Metrics and tolerances: tests/gpu_harness.py."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -109,18 +111,53 @@ def _check_params(run, recs, w, per_tick, f64_recs=None, stated=False):
                              np.max(np.abs((v - p0) - (v64 - p0))) / d64, float("inf"), f"{k} t{t}")
 
 
-def _gradient_probe(w):
-    """One update per party; w.lr = 1, so that every parameter change is -grad."""
-    run = H.Run(w, w.rows_per_tick, 1)
+def _gradient_probe(w, params=None):
+    """One update per party; w.lr = 1, so that every parameter change is -grad.
+    B's first layer is also held to the bound on every 256 outputs by
+    themselves (and would fail it if their change were missing)."""
+    run = H.Run(w, w.rows_per_tick, 1, params=params)
     o, recs = run.oracle(_prec(w))
     _check_ints(run, o, recs)
     dtol = _dtol(w)
-    for key, v in o.p.items():
-        ok, err, bound = H.delta_ok(run.final[key], v, run.p0[key].astype(np.float64), dtol, 1)
-        d_ref = np.max(np.abs(v - run.p0[key]))
+
+    def check(key, g, v, p0):
+        p0 = p0.astype(np.float64)
+        ok, err, bound = H.delta_ok(g, v, p0, dtol, 1)
+        d_ref = np.max(np.abs(v - p0))
         if d_ref > 0:
             H.record("grad rel (lr 1)", err / d_ref, dtol, f"{key} max|grad| {d_ref:.2e}")
         assert ok, (key, err, bound)
+        return d_ref, bound
+
+    for key, v in o.p.items():
+        check(key, run.final[key], v, run.p0[key])
+    if o.p["B.W0"].shape[0] > 256:
+        for key in ("B.W0", "B.b0"):
+            for n in range(0, o.p["B.W0"].shape[0], 256):
+                at = slice(n, n + 256)
+                d_ref, bound = check(f"{key}[{n}:]", run.final[key][at], o.p[key][at], run.p0[key][at])
+                assert d_ref > 2 * bound, (key, n, d_ref, bound)
+
+
+def _columns_on_or_off(w):
+    """Start parameters whose first layers' biases are 4 or -4: every third
+    output is off and the others on for every row (the pre-activations
+    without them stay within 4), so that a ReLU's mask counts but no row's
+    share hangs on a pre-activation near zero."""
+    p = S.init_params(w)
+    for key in ("A.b0", "B.b0"):
+        p[key] = np.where(np.arange(p[key].size) % 3 == 0, -4.0, 4.0).astype(np.float32)
+    return p
+
+
+def _column_probe(w):
+    """The gradient probe of w's shapes with ReLUs after the first layers
+    alone, at _columns_on_or_off's start."""
+    def first(spec):
+        return replace(spec, relu=[l == 0 for l in range(len(spec.widths))])
+    w = replace(w, A=first(w.A), B=first(w.B), top=replace(w.top, relu=[False] * (len(w.top.widths) - 1)),
+                n_rows=w.rows_per_tick, staleness=0, lr=1.0)
+    _gradient_probe(w, _columns_on_or_off(w))
 
 
 def _full_check(run, w, per_tick=True, f64=True):
@@ -413,11 +450,12 @@ def test_layer_outputs_of_whole_and_partial_blocks(dtype, rows, widths):
     """Blocks of more than 16 rows: whole ones with widths of whole MFMA
     depths (written without a test per element) beside a last partial block
     and widths that are not such a multiple.  Losses and messages of three
-    groups, the later ones of updated parameters (lr 0.5).  The parameters
-    themselves have no tight bound here: a hidden value that rounds across
-    zero moves one row's delta, and with messages clipped to about 1e-2 and a
-    mean over 8192 rows (updates of 4e-5) one row is 4e-7 of lr / rows * |x|
-    |delta|, where the bound of the named workloads is 3.8e-7."""
+    groups, the later ones of updated parameters (lr 0.5), and every gradient
+    of one group (_column_probe: with ReLUs everywhere the parameters have no
+    tight bound, because a hidden value that rounds across zero moves one
+    row's delta, and with messages clipped to about 1e-2 and a mean over 8192
+    rows (updates of 4e-5) one row is 4e-7 of lr / rows * |x| |delta|, where
+    the bound of the named workloads is 3.8e-7)."""
     w = Workload(name="blocks", n_rows=3 * rows, dtype=dtype,
                  A=PartySpec(dense=24, widths=[96, 64, 32]), B=PartySpec(dense=40, widths=widths),
                  top=TopSpec(widths=[64, 32, 1]), batch=rows, staleness=1, replicas=1, lr=0.5,
@@ -428,6 +466,7 @@ def test_layer_outputs_of_whole_and_partial_blocks(dtype, rows, widths):
     _check_ints(run, o, recs)
     _check_losses(run, recs, w)
     _check_messages(run, recs, w)
+    _column_probe(w)
 
 
 @pytest.mark.parametrize("dtype,rows", [("bf16", 4112), ("bf16", 6160), ("bf16", 9217), ("bf16", 12289),
@@ -504,7 +543,8 @@ def test_wide_first_layer_large_product(widths, batch, clip):
     per block, at 2048 rows per tick and more: layer 1's input gradient is a
     product over the group in 256 x 256 tiles (partial tiles of outputs and
     rows, with two layers fed by the cut-layer delta).  Integers, losses and
-    messages of five groups, whose embeddings show B's updates (lr 0.5)."""
+    messages of five groups, whose embeddings show B's updates (lr 0.5), and
+    every gradient of one group, B's first layer by tiles of 256 outputs."""
     w = Workload(name="widelarge", n_rows=4 * batch + 905, dtype="bf16",
                  A=PartySpec(dense=24, widths=[32, 16]), B=PartySpec(dense=40, widths=widths),
                  top=TopSpec(widths=[20, 1]), batch=batch, staleness=1, replicas=1, lr=0.5,
@@ -515,6 +555,7 @@ def test_wide_first_layer_large_product(widths, batch, clip):
     _check_ints(run, o, recs)
     _check_losses(run, recs, w)
     _check_messages(run, recs, w)
+    _column_probe(w)
 
 
 @pytest.mark.parametrize("widths,batch,dtype", [([1300, 40], 16400, "bf16"), ([1000, 512, 24], 16500, "bf16"),
@@ -525,7 +566,8 @@ def test_backward_last_delta_in_ranges(widths, batch, dtype):
     of 20, 232 and 188 columns), which leaves room for 64 instead of 48 rows
     per block, or 32 instead of 16 (float32); a ragged last group.  Integers,
     losses and messages of four groups, whose embeddings show B's updates
-    (lr 0.5)."""
+    (lr 0.5), and every gradient of one group, B's first layer by ranges (a
+    bf16 last range of zeros stays within the bounds on embeddings)."""
     w = Workload(name="ranges", n_rows=3 * batch + 77, dtype=dtype,
                  A=PartySpec(dense=24, widths=[32, 16]), B=PartySpec(dense=33, widths=widths),
                  top=TopSpec(widths=[20, 1]), batch=batch, staleness=1, replicas=1, lr=0.5,
@@ -535,6 +577,7 @@ def test_backward_last_delta_in_ranges(widths, batch, dtype):
     _check_ints(run, o, recs)
     _check_losses(run, recs, w)
     _check_messages(run, recs, w)
+    _column_probe(w)
 
 
 def _wide_three(din, widths, s, k, clip, lr=0.5):
