@@ -41,8 +41,8 @@ namespace {
 
 constexpr int kMaxSlots = VFL_MAX_STALENESS + 1;
 constexpr int kGemmMinWidth = 512;    // B's first-layer width from which its input gradient may be a layer product
-constexpr int kGemmMinRows = 2048;    // rows from which it is one where the chain has fewer than
-constexpr int kGemmChainRows = 48;    // these rows per block
+constexpr int kGemmMinRows = 2048;    // rows from which it is one where the LDS does not hold
+constexpr int kGemmLdsRows = 48;      // these rows of the chain
 constexpr int kBwdChunk = 256;        // columns per range of B's last delta
 constexpr int kMinBlocks = 256;       // row blocks a chain launch aims at (one per CU)
 constexpr int kDwBlocks = 256;        // weight-gradient blocks a launch aims at
@@ -155,7 +155,7 @@ struct ActBufs {
 };
 struct BwdLds { LBuf P[2], C, mask[VFL_MAX_LAYERS]; int bytes = 0; };   // C: every second column range
 
-struct KMeta { int rt = 1, blocks = 1, lds = 0, cw = kChainCopyWaves; };
+struct KMeta { int rt = 1, blocks = 1, lds = 0; };
 
 // Weight-gradient launch shape of a party: tile 32 (one unsplit launch,
 // k_dw32) or 64 (row chunks, k_dw + k_dw_reduce).
@@ -344,7 +344,9 @@ constexpr double kDwtMinFlops = 4e9;
 // 64-256-128 at 2048, 4096, 6144 rows: 41.3 / 34.7, 43.6 / 41.7, 51.5 /
 // 57.6; float32 at 1024, 2048, 4096 rows: 57.4 / 50.7, 60.9 / 58.8, 70.2 /
 // 86.7; 500-1024-512-128 at 2048 and 4096 rows, 285 and 570 MB of reads:
-// 110 / 101, 122.5 / 123.6).
+// 110 / 101, 122.5 / 123.6; 256-1024-256 and 384-1024-256 at 4096 rows, 268
+// and 335 MB, 81.9 / 74.1 and 86.1 / 80.2, but 500-1024-256, 402 MB, 89.8 /
+// 82.3: the line could lie somewhat higher).
 constexpr int kDwUnsplitBytes = 8192;
 constexpr int kDwUnsplitSmall = 2048;   // up to here whatever the reads
 constexpr int64_t kDwUnsplitReads = 320 << 20;   // bytes, two 32-column operands per tile
@@ -732,8 +734,8 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   // one fragment (1 KB) each
   const int KS = p.e == BF16 ? 32 : 16;
   auto ksteps = [&](int K) { return (K + KS - 1) / KS; };
-  // (+ slack for the loads of a chain pass's last group, which may run up
-  // to 2 * 4 - 1 MFMA steps past the last tile)
+  // (+ slack for the loads of a chain pass's last groups, which may run up
+  // to 3 MFMA steps past the last tile)
   auto packed_bytes = [&](int N, int K) { return (size_t)((N + KS - 1) / KS * KS) * ksteps(K) * 64 + 8192; };
 
   auto party = [&](Party& P, const vfl_bottom_spec* s, int nslots, bool passive) {
@@ -783,21 +785,23 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
   p.dB = p.P.out[p.P.L - 1];
   for (int l = 0; l + 1 < p.P.L; ++l) p.ldb[l] = (p.P.out[l] + 63) / 64 * 64;
   // Layer 1's input gradient of B as a layer product over the whole group
-  // (bf16, no tables) where B's backward chain would have fewer than
-  // kGemmChainRows rows per block, so that each block streams the wide
-  // weights for few rows, and the group gives the product's 256 x 256 tiles
-  // enough work, or where the chain's LDS does not hold the layers at all.
+  // (bf16, no tables) where the LDS does not hold kGemmLdsRows rows of B's
+  // backward chain, so that each block would stream the wide weights for few
+  // rows, and the group gives the product's 256 x 256 tiles enough work, or
+  // where it does not hold the layers at all.
   // Everywhere else the chain is faster: it saves the launch and the
   // row-major delta's way through HBM, and small groups do not fill the
   // CUs with large tiles (us per tick, product / chain; 500-1024-512-128 at
   // 512, 8192 and 32768 rows: 89 / 72, 152 / 143, 381 / 370;
-  // 500-2048-512-128 at 32768 rows: 753 / 737; 500-2048-1024-128 at 2048
-  // and 32768 rows, 32 rows per block: 183 / 182, 1090 / 1159).
+  // 500-2048-512-128 at 32768 rows: 753 / 737; 500-2048-1024-128, 32 rows per
+  // block, at 2048, 4096, 8192 and 32768 rows: 178 / 172, 203 / 196, 312 / 327,
+  // 1043 / 1074; 500-1536-1024-128, 32 too, at the same: 163 / 147, 183 / 168,
+  // 270 / 271, 822 / 839: up to 4096 rows the chain would be the better).
   if (p.e == BF16 && p.P.L >= 2 && p.P.spec.n_cat == 0 && p.P.out[0] >= kGemmMinWidth) {
     KMeta m;
     int chunk = 0;
     p.bgemm = format == 2 || !pick_bwd(p, 1, m, chunk) ||
-              (p.R >= kGemmMinRows && !pick_bwd(p, kGemmChainRows / 16, m, chunk));
+              (p.R >= kGemmMinRows && !pick_bwd(p, kGemmLdsRows / 16, m, chunk));
   }
   if (p.bgemm) p.d1rm = ly.take((size_t)es * R * ld_of(p.P.out[1]));
   // bf16: B's forward records one bit per activation of every ReLU layer
@@ -1514,7 +1518,7 @@ vfl_status b_forward(vfl_ctx* c, int slot, const SlotState& st, TickRef tr) {
   const int32_t hdr[3] = {(int32_t)st.group, (int32_t)st.group, (int32_t)st.version};
   const ChainCall k = call_of(st, st.group, hdr, 0);
   TIMED(VFL_K_FWD, party_fwd_flops(p.P, p.R), c->sb,
-        launch_fwd(p.e, p.kf.rt, p.kf.cw, (const FwdJob*)(c->ws + p.job_fwd) + slot, p.kf.lds, p.kf.blocks, k,
+        launch_fwd(p.e, p.kf.rt, (const FwdJob*)(c->ws + p.job_fwd) + slot, p.kf.lds, p.kf.blocks, k,
                    tr, c->sb));
   return VFL_OK;
 }
@@ -1538,7 +1542,7 @@ vfl_status a_top(vfl_ctx* c, int64_t group, int slot, const SlotState& st, int32
   for (int j = 0; j < p.T.H; ++j) f += mm_flops(R, p.T.out[j], p.T.in[j]);
   for (int j = 1; j < p.T.H; ++j) f += mm_flops(R, p.T.in[j], p.T.out[j]);
   TIMED(VFL_K_ACTIVE, f, c->sa,
-        launch_active(p.e, p.ka.rt, p.ka.cw, (const ActiveJob*)(c->ws + p.job_act) + slot, p.ka.lds, p.ka.blocks, k,
+        launch_active(p.e, p.ka.rt, (const ActiveJob*)(c->ws + p.job_act) + slot, p.ka.lds, p.ka.blocks, k,
                       tr, c->sa));
   HIPCHK(hipEventRecord(c->ev_grad[slot], c->sa));
   return VFL_OK;
@@ -1561,7 +1565,7 @@ vfl_status b_backward(vfl_ctx* c, int slot, const SlotState& st, int64_t group, 
   const ChainCall k = call_of(st, group, nullptr, group);
   const double gf = p.bgemm ? mm_flops(p.R, p.P.out[0], p.P.out[1]) : 0.0;
   TIMED(VFL_K_BWD, party_dx_flops(p.P, p.R) - gf, c->sb,
-        launch_bwd(p.e, p.kb.rt, p.kb.cw, (const BwdJob*)(c->ws + p.job_bwd) + slot, p.kb.lds, p.kb.blocks, k, tr, c->sb));
+        launch_bwd(p.e, p.kb.rt, (const BwdJob*)(c->ws + p.job_bwd) + slot, p.kb.lds, p.kb.blocks, k, tr, c->sb));
   if (p.bgemm)
     TIMED(VFL_K_GEMM, gf, c->sb,
           launch_lin((const LinJob*)(c->ws + p.job_lin) + slot, p.lin_blocks_dx, st.rows, tr, c->sb));

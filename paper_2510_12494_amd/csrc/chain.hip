@@ -33,8 +33,8 @@
 // LDS rows are padded to 16 bytes past a multiple of 128, so the 16 rows a
 // fragment read touches fall in distinct banks.  After a layer, the tensors a
 // later kernel needs go to HBM: row-major for messages, the RC layout for
-// the operands of the weight gradients (8 x 8 register transposes of bf16
-// chunks, 4 x 4 of float32).
+// the operands of the weight gradients (transposed by the LDS reads of bf16
+// chunks, element by element from float32 rows).
 //
 // Paper correspondence: bottom models f_A, f_B and the top model g of
 // Section 3, the BCE loss of Eq. (1) and its gradient, the embedding and
@@ -81,43 +81,21 @@ __device__ __forceinline__ char* lp(char* s, const LBuf& b, int r, int byte_col)
   return s + b.off + r * b.pitch + byte_col;
 }
 
-// eight consecutive elements of an LDS row (16 bytes of bf16, 32 of float32)
-template <typename T>
-__device__ __forceinline__ void ld8(const char* p, float (&v)[8]) {
-  if constexpr (sizeof(T) == 4) {
-    const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 16);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
-  } else {
-    const u32x4 x = *(const u32x4*)p;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[2 * e] = __uint_as_float(x[e] << 16);
-      v[2 * e + 1] = __uint_as_float(x[e] & 0xffff0000u);
-    }
-  }
-}
-template <typename T>
-__device__ __forceinline__ void st8(char* p, const float (&v)[8]) {
-  if constexpr (sizeof(T) == 4) {
-    *(f32x4*)p = f32x4{v[0], v[1], v[2], v[3]};
-    *(f32x4*)(p + 16) = f32x4{v[4], v[5], v[6], v[7]};
-  } else {
-    *(u32x4*)p = u32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-  }
-}
-
 // ------------------------------------------------------------ block product
 constexpr int kNW = kChainWaves;    // product wavefronts per block (two per SIMD)
 constexpr int kNT = 64 * kNW;        // product threads
-constexpr int kBT = kNT + 64 * kChainCopyWaves;   // most threads per block
+constexpr int kBT = kNT + 64 * kChainCopyWaves;   // threads per block
+// the copy threads, read from the launch: with the constant in its place the
+// ticks of float32 chains with tables are 2.5 % longer (8192 samples of 13
+// fields a party: 148 -> 152 us), the others the same
+__device__ __forceinline__ int copy_threads() { return (int)blockDim.x - kNT; }
 // Wavefronts per SIMD the register allocation has to allow: two blocks of
 // 12 wavefronts on a CU (80 registers) up to `two` row tiles per block, else
 // one (168).  At 80 registers k_bwd<bf16, 2> (82 without the bound) keeps two
 // blocks on a CU (32768 rows of 500-1024-512-128: 47 -> 37 us) and
 // k_active<bf16, 1> (86) leaves room for the other party's blocks
-// (regression's tick 224 -> 217 us); k_active<., 2> would spill 35 registers
-// (ctr's 55 -> 62 us).
+// (regression's tick 224 -> 217 us), each with one register spilled;
+// k_active<., 2> would spill 35 (ctr's 55 -> 62 us).
 constexpr int min_waves(int rt, int two) { return rt <= two ? 6 : 3; }
 constexpr int kNTW = 2;              // 16-column output tiles per wavefront and pass
 constexpr int PF = 2;                // MFMA steps per weight load group
@@ -509,7 +487,7 @@ template <typename T, int BR, bool NT>
 __device__ __forceinline__ void lds_to_rc_(char* s, const LBuf& b, int cols, const RCMat& m, int r0,
                                            const LBuf& mask, int mcols) {
   constexpr int RR = Ch<T>::CE;
-  const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
+  const int tid = (int)threadIdx.x - kNT, nt = copy_threads();
   const int cw = (cols + RR - 1) / RR * RR;
   const int64_t cp = m.cp;
   VFL_GLOBAL char* g = glb((char*)m.p) + (int64_t)(r0 / RR) * cp * 16;   // the block's first row group
@@ -614,7 +592,7 @@ __device__ __forceinline__ void bits_to_lds(char* s, const LBuf& b, int cols, co
   const int nc = (cols + 15) / 16;
   const int rg_last = m.rows > 0 ? max(m.rows / 8 - 1, 0) : (1 << 30);
   const VFL_GLOBAL uint8_t* bits = glb((const uint8_t*)m.bits);
-  for (GridWalk w((int)threadIdx.x - kNT, nc, (int)blockDim.x - kNT); w.r < BR / 8; w.next()) {
+  for (GridWalk w((int)threadIdx.x - kNT, nc, copy_threads()); w.r < BR / 8; w.next()) {
     const int rg = w.r, c = 16 * w.c;
     const u32x4 v = __builtin_nontemporal_load((const VFL_GLOBAL u32x4*)(bits + (int64_t)min(r0 / 8 + rg, rg_last) * m.ldb + c));
     *(u32x4*)(s + b.off + rg * b.pitch + c) = v;
@@ -630,7 +608,7 @@ __device__ __forceinline__ void rc_to_lds(char* s, const LBuf& b, int cols, cons
   constexpr int RR = Ch<T>::CE, KS = Ch<T>::KS;
   constexpr int NB = 4;
   static_assert(RR == 4, "bf16 masks are bits");
-  const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
+  const int tid = (int)threadIdx.x - kNT, nt = copy_threads();
   const int cw = (cols + KS - 1) / KS * KS;   // columns up to the MFMA depth
   const VFL_GLOBAL char* g = glb((const char*)m.p);
   const int64_t cp = m.cp;
@@ -667,7 +645,7 @@ __device__ __forceinline__ void lds_to_rows(const char* s, const LBuf& b, int co
   constexpr int CE = Ch<T>::CE;
   const int nch = (cols + CE - 1) / CE;
   VFL_GLOBAL char* d = glb((char*)dst);
-  for (GridWalk w(tid, nch, COPY ? (int)blockDim.x - kNT : kNT); w.r < rv; w.next())
+  for (GridWalk w(tid, nch, COPY ? copy_threads() : kNT); w.r < rv; w.next())
     *(VFL_GLOBAL u32x4*)(d + ((int64_t)(r0 + w.r) * ld + w.c * CE) * sizeof(T)) =
         *(const u32x4*)(s + b.off + w.r * b.pitch + w.c * 16);
 }
@@ -993,7 +971,7 @@ __global__ __launch_bounds__(kBT, min_waves(RT, 1)) void k_active(const ActiveJo
                            r0, rv, wave - w0, nw, lo, hi);
   };
   if (threadIdx.x >= kNT) {
-    const int tid = (int)threadIdx.x - kNT, nt = (int)blockDim.x - kNT;
+    const int tid = (int)threadIdx.x - kNT, nt = copy_threads();
     // B's embedding into cat[:, dA:dA+dB) with zeros up to the MFMA depth
     // (published before this launch; A's last layer fills cat[:, 0:dA) and
     // leaves these columns alone) and the labels, beside A's input
@@ -1352,29 +1330,29 @@ hipError_t raise_lds(K kernel) {
     else if (rt == 4) hipLaunchKernelGGL((K<T, 4>), __VA_ARGS__);                          \
     else return hipErrorInvalidValue;                                                      \
   } while (0)
-#define VFL_CHAIN(K, e, rt, cw, ...)                                                        \
+#define VFL_CHAIN(K, e, rt, ...)                                                            \
   do {                                                                                     \
-    if (lds > kLdsMax || blocks < 1 || cw < 1 || cw > kChainCopyWaves) return hipErrorInvalidValue; \
-    const dim3 thr(kNT + 64 * cw);                                                         \
+    if (lds > kLdsMax || blocks < 1) return hipErrorInvalidValue;                          \
+    const dim3 thr(kBT);                                                                   \
     if (e == BF16) VFL_CHAIN_RT(K, uint16_t, rt, dim3(blocks), thr, __VA_ARGS__);          \
     else VFL_CHAIN_RT(K, float, rt, dim3(blocks), thr, __VA_ARGS__);                       \
   } while (0)
 
-hipError_t launch_fwd(Elt e, int rt, int cw, const FwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_fwd(Elt e, int rt, const FwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st) {
-  VFL_CHAIN(k_fwd, e, rt, cw, lds, st, job, c, tr);
+  VFL_CHAIN(k_fwd, e, rt, lds, st, job, c, tr);
   return hipGetLastError();
 }
 
-hipError_t launch_active(Elt e, int rt, int cw, const ActiveJob* job, int lds, int blocks,
+hipError_t launch_active(Elt e, int rt, const ActiveJob* job, int lds, int blocks,
                          const ChainCall& c, TickRef tr, hipStream_t st) {
-  VFL_CHAIN(k_active, e, rt, cw, lds, st, job, c, tr);
+  VFL_CHAIN(k_active, e, rt, lds, st, job, c, tr);
   return hipGetLastError();
 }
 
-hipError_t launch_bwd(Elt e, int rt, int cw, const BwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_bwd(Elt e, int rt, const BwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st) {
-  VFL_CHAIN(k_bwd, e, rt, cw, lds, st, job, c, tr);
+  VFL_CHAIN(k_bwd, e, rt, lds, st, job, c, tr);
   return hipGetLastError();
 }
 

@@ -100,12 +100,6 @@ __device__ __forceinline__ int64_t pk_index(int n, int k, int kst) {
   return ((((int64_t)(n >> 4) * kst + k / KS) * 64 + lane) * CE) + k % CE;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // Philox4x32-10 (Salmon et al., SC'11): 10 rounds of the 4x32 bijection
 // with Weyl-sequence key increments.
 __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uint32_t k1) {
@@ -139,27 +133,6 @@ __device__ __forceinline__ void gauss4(uint64_t seed, uint32_t step, uint32_t ro
     n[2 * p] = rad * __builtin_amdgcn_cosf(ub);
     n[2 * p + 1] = rad * __builtin_amdgcn_sinf(ub);
   }
-}
-
-// 8 x 8 transpose of 16-bit elements: in[i] holds row i (columns 0..7, two
-// per word, low half first); out[j] receives column j (rows 0..7).
-__device__ __forceinline__ void transpose8x8_u16(const u32x4 (&in)[8], u32x4 (&out)[8]) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t a = in[2 * w][j >> 1], b = in[2 * w + 1][j >> 1];
-      out[j][w] = (j & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
-    }
-  }
-}
-
-// 4 x 4 transpose of 32-bit elements
-__device__ __forceinline__ void transpose4x4_u32(const u32x4 (&in)[4], u32x4 (&out)[4]) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out[j][i] = in[i][j];
 }
 
 }  // namespace dev

@@ -498,7 +498,10 @@ __device__ __forceinline__ void logit_reduce(const DwJob& J, int lb, int R, floa
 // many tiles (more than kDwuTiles) fill the CUs with 4 each (both parties on
 // one stream, 16 / 4 wavefronts: 64-256-128 + 256-256 at 4096 rows, 160
 // tiles, 25.5 / 37.6 us; 500-1024-512-128 at 512 rows, 1088 tiles, 25.1 /
-// 21.5 us and the tick 76.6 / 68.5).  Against the row
+// 21.5 us and the tick 76.6 / 68.5; ticks at 512, 1000 and 2000 bf16 rows with
+// 192 tiles 38.5 / 40.8, 43.3 / 43.7, 47.0 / 49.0, with 384 already 49.2 /
+// 48.0, 52.7 / 50.2, 56.3 / 52.7, with 512 54.8 / 49.6, 58.6 / 54.9, 65.3 /
+// 58.5; 384 of float32 at 256 to 1000 rows within 3 % either way).  Against the row
 // chunks with their reduction launch: 4096 rows of 64-256-128 + 256-256,
 // 19 + 15 -> 25 us for both parties on one stream.
 constexpr int kDwuTiles = 384;

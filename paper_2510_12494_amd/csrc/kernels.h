@@ -13,10 +13,10 @@
 //             rows split into chunks; SGD fused when a layer is unsplit;
 //   k_dw_reduce  split chunks and the logit layer's block partials summed
 //             in a fixed order, SGD, weight operand copies refreshed.
-// The three chain kernels give each workgroup (kChainWaves wavefronts) a
-// block of BR = 16 * RT rows and keep the block's activations and deltas in
-// LDS from layer to layer:
-// only the tensors a later kernel reads go to HBM.  Those that the weight
+// The three chain kernels give each workgroup (kChainWaves wavefronts that run
+// the layers, kChainCopyWaves that copy their outputs out) a block of BR = 16 *
+// RT rows and keep the block's activations and deltas in LDS from layer to
+// layer: only the tensors a later kernel reads go to HBM.  Those that the weight
 // gradient contracts over rows are written in the row-chunked layout below.
 //
 // Row-chunked ("RC") layout of a [rows x cols] matrix: element (r, c) lives
@@ -42,7 +42,7 @@ constexpr int kMaxDw = 16;            // weight-gradient problems per launch
 constexpr int kMaxLogitCols = 512;    // widest last hidden layer of the top model
 constexpr int kLdsMax = 160 * 1024;   // LDS of one gfx950 workgroup
 constexpr int kChainWaves = 8;        // product wavefronts per chain-kernel block
-constexpr int kChainCopyWaves = 4;    // and copy wavefronts, at most
+constexpr int kChainCopyWaves = 4;    // and copy wavefronts
 
 // The values of one tick of the deterministic schedule over a resident
 // dataset of n_rows rows (group g covers rows [(g mod E) * R, ...), E =
@@ -223,12 +223,12 @@ struct FwdJob {
 // cat, the top hidden layers ft, logit + BCE (mse: output + squared error)
 // into the last hidden delta dh
 // (per-block partials {sum loss, sum dl, sum_r dl * h[r][c]} to
-// part[block]; `red`: LDS for the logit weights, labels, dl and loss of the
-// block's rows), the top input-gradient chain dt (j = H-1 .. 1), the concat
-// product dc (columns < dA: A's cut delta into dc.out, masked when A's
-// last layer has a ReLU; columns >= dA: the gradient message, staged as
-// float32 in `msg` when clip/noise run, else written to ring directly), and
-// A's chain da (l = LA-1 .. 1); with tables, gx = the float32 gradient of
+// part[block]; `red`: LDS for the labels of the block's rows and each product
+// wavefront's share of those sums), the top input-gradient chain dt (j = H-1 ..
+// 1), the concat product dc (columns < dA: A's cut delta into dc.out, masked
+// when A's last layer has a ReLU; columns >= dA: the gradient message, staged
+// in `msg`, as float32 when clip or noise follow, and sent to ring from there),
+// and A's chain da (l = LA-1 .. 1); with tables, gx = the float32 gradient of
 // the embedding columns.
 struct ActiveJob {
   RowInput in;
@@ -290,12 +290,11 @@ struct BwdJob {
 
 // Jobs live in device memory (written once when the context is created);
 // `rt` selects 16 * rt rows per block, `lds` the dynamic LDS bytes.
-// cw: copy wavefronts per block, 1 .. kChainCopyWaves
-hipError_t launch_fwd(Elt e, int rt, int cw, const FwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_fwd(Elt e, int rt, const FwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st);
-hipError_t launch_active(Elt e, int rt, int cw, const ActiveJob* job, int lds, int blocks,
+hipError_t launch_active(Elt e, int rt, const ActiveJob* job, int lds, int blocks,
                          const ChainCall& c, TickRef tr, hipStream_t st);
-hipError_t launch_bwd(Elt e, int rt, int cw, const BwdJob* job, int lds, int blocks, const ChainCall& c,
+hipError_t launch_bwd(Elt e, int rt, const BwdJob* job, int lds, int blocks, const ChainCall& c,
                       TickRef tr, hipStream_t st);
 // Raise the dynamic-LDS limit of every chain kernel to kLdsMax.
 hipError_t chain_init();
