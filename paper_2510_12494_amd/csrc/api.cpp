@@ -632,9 +632,9 @@ bool pick_bwd(const Plan& p, int rt, KMeta& m, int& chunk) {
 constexpr uint32_t kStateFormat = 4;
 
 // format: the present workspace layout, or that of a library which wrote
-// state images of format 2 or 3 (to read them)
+// state images of format 2 or 3 (to read them).  settle: settle_rt
 std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const vfl_top_spec* t,
-                       const vfl_opts* o, Plan& p, uint32_t format = kStateFormat) {
+                       const vfl_opts* o, Plan& p, uint32_t format = kStateFormat, bool settle = true) {
   std::string why;
   if (!o) return "null opts";
   // the caller's dtype as the integer it is (a C caller may pass any value;
@@ -886,7 +886,7 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
       p.kb.lds = two.bytes;
     }
   }
-  if (format >= 4) {
+  if (format >= 4 && settle) {
     settle_rt(p, p.kf, [&](int BR) { FwdLds f; plan_fwd_lds(p, BR, f); return f.bytes; });
     settle_rt(p, p.ka, act_bytes);
     settle_rt(p, p.kb, [&](int BR) { BwdLds x; plan_bwd_lds(p, BR, p.bchunk, x); return x.bytes; });
@@ -934,6 +934,13 @@ std::string build_plan(const vfl_bottom_spec* a, const vfl_bottom_spec* b, const
     p.lin_blocks_dx = lin_blocks(p.R, p.P.out[0]);
   }
   p.total = (ly.off + 255) / 256 * 256;
+  // k_active's blocks of 32 instead of 64 rows (float32) have twice the logit
+  // partials, by up to 0.5 MB: not where these take the workspace past
+  // vfl_create_static's
+  if (format >= 4 && settle && p.total > VFL_STATIC_WORKSPACE_BYTES) {
+    Plan q;
+    if (build_plan(a, b, t, o, q, format, false).empty() && q.total <= VFL_STATIC_WORKSPACE_BYTES) p = q;
+  }
   return "";
 }
 

@@ -165,6 +165,20 @@ def test_widest_one_layer_party_with_a_wide_input(V, dtype, extra, B, top, clip,
     assert not accepted(last + 8)
 
 
+@pytest.mark.parametrize("rows,B,fits", [(18640, 88, True), (18648, 88, True), (19728, 76, True), (18800, 88, False)])
+def test_rows_per_block_do_not_outgrow_the_static_workspace(V, rows, B, fits):
+    """float32 groups of 16385 to 20480 rows take 32 rows per block, with twice
+    the logit partials, but not where 64 rows fit vfl_create_static's
+    workspace and 32 do not (the first three)."""
+    from vfl_synth.workloads import Workload, PartySpec, TopSpec
+    from paper_2510_12494_amd.session import bottom_spec, top_spec, opts
+    w = Workload(name="static", n_rows=rows, dtype="f32", A=PartySpec(dense=13, widths=[16, 8]),
+                 B=PartySpec(dense=20, widths=[B]), top=TopSpec(widths=[199, 1]), batch=rows, staleness=1,
+                 replicas=1, lr=0.05)
+    size = V.vfl_workspace_size(bottom_spec(w.A), bottom_spec(w.B), top_spec(w.top), opts(w))
+    assert (size <= 64 << 20) == fits and abs(size - (64 << 20)) < 1 << 20
+
+
 def _random_shape(rng, dtype):
     from vfl_synth.workloads import Workload, PartySpec, TopSpec
     def widths(n, last_mult):
